@@ -174,21 +174,31 @@ extern "C" odwf_status odwf_solver_create(odwf_lattice L, int Ns, double m0, con
       v[CF_A_INV] = 1.0 / a;
       v[CF_C] = c;
       v[CF_CSHIFT] = cn;
+      v[CF_OMEGA2] = w(q) * w(q);
       for (int id = 0; id < NCOEF; id++) {
         c64[(chi * NCOEF + id) * Ns + q] = v[id];
         c32[(chi * NCOEF + id) * Ns + q] = (float)v[id];
       }
     }
   }
+  std::vector<double> dn;
+  if (dense_ns(Ns)) {
+    dn.resize((size_t)NDENSE * DENSE_LEN);
+    dense_tables(Ns, m0, omega, dn.data(), S->dense_q);
+  }
   if (hipMalloc(&S->coef64, c64.size() * sizeof(double)) != hipSuccess ||
-      hipMalloc(&S->coef32, c32.size() * sizeof(float)) != hipSuccess) {
+      hipMalloc(&S->coef32, c32.size() * sizeof(float)) != hipSuccess ||
+      (!dn.empty() && hipMalloc(&S->dense, dn.size() * sizeof(double)) != hipSuccess)) {
     (void)hipGetLastError();
+    if (S->coef64) (void)hipFree(S->coef64);
+    if (S->coef32) (void)hipFree(S->coef32);
     delete S;
     set_error("odwf_solver_create: out of device memory");
     return ODWF_ENOMEM;
   }
   HIPCHK(hipMemcpy(S->coef64, c64.data(), c64.size() * sizeof(double), hipMemcpyHostToDevice));
   HIPCHK(hipMemcpy(S->coef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
+  if (!dn.empty()) HIPCHK(hipMemcpy(S->dense, dn.data(), dn.size() * sizeof(double), hipMemcpyHostToDevice));
   *out = S;
   return ODWF_OK;
 }
@@ -200,6 +210,7 @@ extern "C" void odwf_solver_destroy(odwf_solver S) {
   for (auto& kv : S->ws) delete kv.second;
   if (S->coef64) (void)hipFree(S->coef64);
   if (S->coef32) (void)hipFree(S->coef32);
+  if (S->dense) (void)hipFree(S->dense);
   delete S;
 }
 
@@ -207,7 +218,8 @@ extern "C" void odwf_solver_destroy(odwf_solver S) {
 // operator application
 // ------------------------------------------------------------------------------
 
-// the half fields each operator uses, as bits: input even (1), input odd (2),
+// the half fields odwf_apply_noalloc sets aside per operator, as bits (the operators
+// take at most these): input even (1), input odd (2),
 // output even (4), output odd (8), even scratch (16), odd scratch (32)
 static int apply_needs(odwf_op op) {
   const bool full = op == ODWF_OP_D || op == ODWF_OP_DDAG || op == ODWF_OP_DDAGD;
@@ -236,67 +248,69 @@ static odwf_status apply_chunk(odwf_solver S, odwf_op op, const double* mq, int 
   c.nrhs = nrhs;
   c.noprof = noprof;
   for (int r = 0; r < MAXRHS; r++) c.kappa[r] = r < nrhs ? -mq[r0 + r] / (2.0 * S->m0) : 0.0;
-  const int needs = apply_needs(op);
-  const bool need_ie = needs & 1, need_io = needs & 2, need_oe = needs & 4, need_oo = needs & 8;
-  const bool need_te = needs & 16, need_to = needs & 32;
-  auto half = [&](bool need, const char* name) { return need ? get(name, nrhs, prec) : HV(); };
-  HV ie = half(need_ie, "ap.ie"), io = half(need_io, "ap.io");
-  HV oe = half(need_oe, "ap.oe"), oo = half(need_oo, "ap.oo");
-  HV te = half(need_te, "ap.te"), to = half(need_to, "ap.to");
-  if ((need_ie && !ie.d) || (need_io && !io.d) || (need_oe && !oe.d) || (need_oo && !oo.d) ||
-      (need_te && !te.d) || (need_to && !to.d)) {
+  // halves of the operator at hand, in the order they are taken from `get`
+  HV ie, io, te, to, oe, oo;
+  bool have = true;
+  auto take = [&](HV& v, const char* name) {
+    v = get(name, nrhs, prec);
+    have = have && v.d;
+  };
+  const bool full = op == ODWF_OP_D || op == ODWF_OP_DDAG || op == ODWF_OP_DDAGD;
+  const bool out_e = op != ODWF_OP_HOP_OE, out_o = op == ODWF_OP_HOP_OE || op == ODWF_OP_M5INV || full;
+  if (op == ODWF_OP_HOP_OE || op >= ODWF_OP_SCHUR) take(ie, "ap.ie");
+  if (op == ODWF_OP_HOP_EO) take(io, "ap.io");
+  if (full || op == ODWF_OP_SCHUR_DAG || op == ODWF_OP_SCHUR_NORMAL) take(te, "ap.te");
+  if (full || op >= ODWF_OP_SCHUR) take(to, "ap.to");
+  if (out_e) take(oe, "ap.oe");
+  if (out_o) take(oo, "ap.oo");
+  if (!have) {
     set_error("odwf_apply: out of device memory for workspaces");
     return ODWF_ENOMEM;
   }
-  if (need_ie) HIPCHK(launch_pack_spinor(prec, in, r0, ie.d, ie.sc, 0, nrhs, Ns, g, st));
-  if (need_io) HIPCHK(launch_pack_spinor(prec, in, r0, io.d, io.sc, 1, nrhs, Ns, g, st));
-  bool have_e = true, have_o = true;
   HopOpt o;
   switch (op) {
     case ODWF_OP_HOP_EO:
+      HIPCHK(pack(c, in, r0, nullptr, &io));
       HIPCHK(hop(c, 0, 0, io, &oe, o));
-      have_o = false;
       break;
     case ODWF_OP_HOP_OE:
+      HIPCHK(pack(c, in, r0, &ie, nullptr));
       HIPCHK(hop(c, 1, 0, ie, &oo, o));
-      have_e = false;
       break;
     case ODWF_OP_M5INV:
-      HIPCHK(m5(c, ie, oe, prog_ainv()));
-      HIPCHK(m5(c, io, oo, prog_ainv()));
+      HIPCHK(pack(c, in, r0, &oe, &oo, prog_ainv(), prog_ainv()));
       break;
     case ODWF_OP_D:
     case ODWF_OP_DDAGD:
-      HIPCHK(apply_D(c, ie, io, te, to, oe, oo));
+      HIPCHK(pack(c, in, r0, &te, &to, prog_1pl(), prog_1pl()));
+      HIPCHK(apply_D(c, te, to, oe, oo, op == ODWF_OP_D ? prog_omega() : prog_omega2()));
       if (op == ODWF_OP_DDAGD) {
-        HIPCHK(apply_Ddag(c, oe, oo, te, to, ie, io));
-        std::swap(oe, ie);
-        std::swap(oo, io);
+        HIPCHK(apply_Ddag(c, oe, oo, te, to));
+        std::swap(oe, te);
+        std::swap(oo, to);
       }
       break;
     case ODWF_OP_DDAG:
-      HIPCHK(apply_Ddag(c, ie, io, te, to, oe, oo));
+      HIPCHK(pack(c, in, r0, &te, &to, prog_omega(), prog_omega()));
+      HIPCHK(apply_Ddag(c, te, to, oe, oo));
       break;
     case ODWF_OP_SCHUR:
+      HIPCHK(pack(c, in, r0, &ie, nullptr));
       HIPCHK(apply_schur(c, ie, to, oe));
-      have_o = false;
       break;
     case ODWF_OP_SCHUR_DAG:
+      HIPCHK(pack(c, in, r0, &ie, nullptr));
       HIPCHK(apply_schur_dag(c, ie, te, to, oe));
-      have_o = false;
       break;
     case ODWF_OP_SCHUR_NORMAL:
+      HIPCHK(pack(c, in, r0, &ie, nullptr));
       HIPCHK(apply_normal(c, ie, to, te, oe, nullptr));
-      have_o = false;
       break;
     default:
       set_error("odwf_apply: unknown operator");
       return ODWF_EINVAL;
   }
-  if (have_e) HIPCHK(launch_unpack_spinor(prec, oe.d, oe.sc, out, r0, 0, nrhs, Ns, g, st));
-  else HIPCHK(launch_zero_canon_parity(out, r0, 0, nrhs, Ns, g, st));
-  if (have_o) HIPCHK(launch_unpack_spinor(prec, oo.d, oo.sc, out, r0, 1, nrhs, Ns, g, st));
-  else HIPCHK(launch_zero_canon_parity(out, r0, 1, nrhs, Ns, g, st));
+  HIPCHK(unpack(c, out_e ? &oe : nullptr, out_o ? &oo : nullptr, out, r0, prog_none()));
   return ODWF_OK;
 }
 
@@ -549,10 +563,14 @@ extern "C" odwf_status odwf_force(odwf_solver S, const void* chi, const void* ps
     set_error("odwf_force: out of device memory for workspaces");
     return ODWF_ENOMEM;
   }
-  HIPCHK(launch_pack_spinor(PREC64, chi, 0, ce.d, nullptr, 0, 1, Ns, g, st));
-  HIPCHK(launch_pack_spinor(PREC64, chi, 0, co.d, nullptr, 1, 1, Ns, g, st));
-  HIPCHK(launch_pack_spinor(PREC64, psi, 0, pe.d, nullptr, 0, 1, Ns, g, st));
-  HIPCHK(launch_pack_spinor(PREC64, psi, 0, po.d, nullptr, 1, 1, Ns, g, st));
+  OpCtx c;
+  c.S = S;
+  c.st = st;
+  c.prec = PREC64;
+  c.nrhs = 1;
+  for (int r = 0; r < MAXRHS; r++) c.kappa[r] = 0.0;
+  HIPCHK(pack(c, chi, 0, &ce, &co));
+  HIPCHK(pack(c, psi, 0, &pe, &po));
   HIPCHK(launch_force(ce.d, pe.d, co.d, po.d, S->lat->U64[0], F, 0, Ns, S->lat->bc_t, accumulate, g, st));
   HIPCHK(launch_force(co.d, po.d, ce.d, pe.d, S->lat->U64[1], F, 1, Ns, S->lat->bc_t, accumulate, g, st));
   return ODWF_OK;

@@ -206,10 +206,7 @@ extern "C" odwf_status odwf_batch_admit(odwf_batch B, const void* b, double mq, 
   double kap1[MAXRHS] = {-mq / (2.0 * S->m0)};
   OpCtx c1 = ctx_of(B, st, PREC64, 1, kap1);
   // f = S_e^dag phi_e,  phi_e = A^{-1}(b'_e - W_eo A^{-1} b'_o),  b' = omega^{-1} b
-  BCHK(launch_pack_spinor(PREC64, b, 0, B->s_e2.d, nullptr, 0, 1, Ns, g, st));
-  BCHK(launch_pack_spinor(PREC64, b, 0, B->s_bo.d, nullptr, 1, 1, Ns, g, st));
-  BCHK(m5(c1, B->s_e2, B->s_e2, prog_omega_inv()));
-  BCHK(m5(c1, B->s_bo, B->s_bo, prog_omega_inv()));
+  BCHK(pack(c1, b, 0, &B->s_e2, &B->s_bo, prog_omega_inv(), prog_omega_inv()));
   BCHK(m5(c1, B->s_bo, B->s_o0, prog_ainv()));
   HopOpt kp;
   kp.x = &B->s_e2;
@@ -364,10 +361,7 @@ extern "C" odwf_status odwf_batch_retire(odwf_batch B, int slot, void* x, odwf_s
   kr.cx = 1.0;
   kr.po = prog_ainv();
   BCHK(hop(c1, 1, 0, B->s_e1, &B->s_bo, kr));
-  BCHK(m5(c1, B->s_e1, B->s_e1, prog_1pl_inv()));
-  BCHK(m5(c1, B->s_bo, B->s_bo, prog_1pl_inv()));
-  BCHK(launch_unpack_spinor(PREC64, B->s_e1.d, nullptr, x, 0, 0, 1, Ns, g, st));
-  BCHK(launch_unpack_spinor(PREC64, B->s_bo.d, nullptr, x, 0, 1, 1, Ns, g, st));
+  BCHK(unpack(c1, &B->s_e1, &B->s_bo, x, 0, prog_1pl_inv()));
   // release the slot: inactive, no update pending
   CGScal z;
   std::memset(&z, 0, sizeof(z));

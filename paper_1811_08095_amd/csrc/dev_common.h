@@ -667,6 +667,146 @@ __device__ __forceinline__ void m5_run_lanes(const M5Prog& prog, cpx<float> (&y)
 }
 
 // ---------------------------------------------------------------------------
+// dense programs on the matrix cores (N_s <= 16).  A wave holds 64 5D sites:
+// four sets of 16 slice slots (one column of N_s = 16 slices, or 16 / N_s
+// columns side by side with a block-diagonal matrix), 24 reals per lane.  The
+// lane order is
+//     lane = 16 q + 4 set + u,   slice slot S = 4 q + u,
+// so that a 4 x 4 transposition inside each quad of lanes (DPP quad_perm, two
+// selects per register) turns four registers into the B operand of
+// v_mfma_*_16x16x4: element (k = q, column (set, register)) of the slots
+// S = 4 k + kk, one kk per instruction, and the same transposition turns the
+// result back.  Every output column depends on its own input column only.
+// Replaces a serial recurrence through LDS columns (FP64) or a log-depth scan
+// over DPP rows (FP32): no LDS traffic for the data, no barrier.
+// ---------------------------------------------------------------------------
+// lane -> (index of its column among the wave's 64 / NS columns, slice)
+template <int NS>
+__device__ __forceinline__ void dense_lane(int lane, int& col, int& s) {
+  static_assert(NS <= DENSE_N, "");
+  const int slot = 4 * (lane >> 4) + (lane & 3);
+  col = ((lane >> 2) & 3) * (DENSE_N / NS) + slot / NS;
+  s = slot % NS;
+}
+
+template <int CTRL>
+__device__ __forceinline__ float quad_move(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double quad_move(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
+  return __hiloint2double(hi, lo);
+}
+// r_k(lane u of the quad) <- r_u(lane k)
+template <class R>
+__device__ __forceinline__ void quad_transpose(R (&r)[4], bool u0, bool u1) {
+  constexpr int X1 = 0xB1, X2 = 0x4E;  // quad_perm: lane ^ 1, lane ^ 2
+#pragma unroll
+  for (int k = 0; k < 4; k += 2) {
+    const R a = quad_move<X1>(r[k + 1]), b = quad_move<X1>(r[k]);
+    r[k] = u0 ? a : r[k];
+    r[k + 1] = u0 ? r[k + 1] : b;
+  }
+#pragma unroll
+  for (int k = 0; k < 2; k++) {
+    const R a = quad_move<X2>(r[k + 2]), b = quad_move<X2>(r[k]);
+    r[k] = u1 ? a : r[k];
+    r[k + 2] = u1 ? r[k + 2] : b;
+  }
+}
+
+typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
+typedef double mfma_f64x4 __attribute__((ext_vector_type(4)));
+template <class R>
+struct Mfma;
+template <>
+struct Mfma<float> {
+  using V = mfma_f32x4;
+  // row of the 16 x 16 result held by operand row i: D row 4 (lane / 16) + v
+  __device__ static __forceinline__ int row(int i) { return i; }
+  __device__ static __forceinline__ V mul(float a, float b, V c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+  }
+};
+template <>
+struct Mfma<double> {
+  using V = mfma_f64x4;
+  // D row lane / 16 + 4 v: the matrix rows are permuted so that register v of
+  // lane group q holds slot 4 q + v as in FP32
+  __device__ static __forceinline__ int row(int i) { return 4 * (i & 3) + (i >> 2); }
+  __device__ static __forceinline__ V mul(double a, double b, V c) {
+    return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+  }
+};
+
+// LDS image of a program: [chirality][16 x 16] of M0 + rho u w^T, followed,
+// where the launch's right-hand sides have different masses, by the rank-1
+// matrices u w^T (the per-column rho is then applied to their product).
+template <class R, int NS>
+__device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab, double rho_p, double rho_m,
+                                            bool mixed) {
+  constexpr int NN = DENSE_N * DENSE_N;
+  for (int i = threadIdx.x; i < 2 * NN; i += blockDim.x) {
+    const int chi = i / NN, e = i % NN;
+    const double* t = tab + chi * DENSE_CHI;
+    const int row = e / DENSE_N, cl = e % DENSE_N;
+    const double uw = row / NS == cl / NS ? t[NN + row] * t[NN + DENSE_N + cl] : 0.0;  // block-diagonal
+    m[i] = (R)(mixed ? t[e] : fma(chi ? rho_m : rho_p, uw, t[e]));
+    if (mixed) m[2 * NN + i] = (R)uw;
+  }
+}
+
+// y <- M y for the 12 components of every lane's 5D site; m: LDS image,
+// rho_p / rho_m: the column's rho per chirality (mixed masses only).  Called
+// by whole waves: the matrix instructions ignore the lane mask.
+template <class R>
+__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, bool mixed, R rho_p, R rho_m) {
+  using M = Mfma<R>;
+  using V = typename M::V;
+  const int lane = threadIdx.x & 63;
+  const bool u0 = lane & 1, u1 = lane & 2;
+  const int base = M::row(lane & 15) * DENSE_N + 4 * (lane >> 4);
+#pragma unroll
+  for (int chi = 0; chi < 2; chi++) {
+    const R* mc = m + chi * DENSE_N * DENSE_N + base;
+    R a[4], b[4];
+#pragma unroll
+    for (int k = 0; k < 4; k++) a[k] = mc[k];
+    if (mixed) {
+#pragma unroll
+      for (int k = 0; k < 4; k++) b[k] = mc[2 * DENSE_N * DENSE_N + k];
+    }
+    const R rho = chi ? rho_m : rho_p;
+#pragma unroll
+    for (int c = 6 * chi; c < 6 * chi + 6; c += 2) {
+      R x[4] = {y[c].re, y[c].im, y[c + 1].re, y[c + 1].im};
+      quad_transpose(x, u0, u1);
+      V d = {R(0), R(0), R(0), R(0)};
+#pragma unroll
+      for (int k = 0; k < 4; k++) d = M::mul(a[k], x[k], d);
+      R o[4] = {d[0], d[1], d[2], d[3]};
+      if (mixed) {
+        V d1 = {R(0), R(0), R(0), R(0)};
+#pragma unroll
+        for (int k = 0; k < 4; k++) d1 = M::mul(b[k], x[k], d1);
+#pragma unroll
+        for (int k = 0; k < 4; k++) x[k] = d1[k];
+        quad_transpose(x, u0, u1);
+      }
+      quad_transpose(o, u0, u1);
+      if (mixed) {  // rho belongs to the column: after the transposition a lane is one column again
+#pragma unroll
+        for (int k = 0; k < 4; k++) o[k] = fma(rho, x[k], o[k]);
+      }
+      y[c] = {o[0], o[1]};
+      y[c + 1] = {o[2], o[3]};
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
 // column pass: buf holds [site][rhs][12 components][NS + 1] values; every
 // column (site, rhs, component) of NS values is transformed by prog.  Items
 // are ordered (chirality, site, rhs, component-of-chirality) with each

@@ -18,14 +18,20 @@ int hop_nblocks(int h, int nrhs, int Ns);
 
 // layouts (pack.hip)
 // canonical complex128 [rhs][s][t][z][y][x][4][3] (rhs offset r0, nrhs of them)
-// <-> internal half of parity `par`.
-hipError_t launch_pack_spinor(int prec, const void* canon, int r0, void* out, float* out_sc,
-                              int par, int nrhs, int Ns, const Geom& g, hipStream_t st);
-hipError_t launch_unpack_spinor(int prec, const void* in, const float* in_sc, void* canon, int r0,
-                                int par, int nrhs, int Ns, const Geom& g, hipStream_t st);
-// zero the sites of parity par of a canonical field (rhs r0 .. r0+nrhs-1)
-hipError_t launch_zero_canon_parity(void* canon, int r0, int par, int nrhs, int Ns, const Geom& g,
-                                    hipStream_t st);
+// <-> internal halves, both parities in one launch, with a fifth-dimension
+// operator per parity applied on the way (one dense program, N_s <= 16, or
+// diagonal).  Packing skips a parity whose half is null; unpacking writes zeros
+// on its sites.
+struct HalfIO {
+  void* d = nullptr;
+  float* sc = nullptr;
+  DenseArg dn = {nullptr, 0, {}};
+  const double* diag = nullptr;  // [2 chiralities, NCOEF * Ns apart][Ns], chirality - mirrored
+};
+hipError_t launch_pack(int prec, const void* canon, int r0, const HalfIO& e, const HalfIO& o, int nrhs, int Ns,
+                       const Geom& g, hipStream_t st);
+hipError_t launch_unpack(int prec, const HalfIO& e, const HalfIO& o, void* canon, int r0, int nrhs, int Ns,
+                         const Geom& g, hipStream_t st);
 // boundary maps of the effective 4D operator on canonical complex128 fields:
 // embed 4D q [r][site][12] into 5D f [r][s][site][12] (chirality minus into
 // slice 0, plus into slice Ns - 1, zeros elsewhere); project back
@@ -36,12 +42,13 @@ hipError_t launch_boundary_project(const void* f, void* q, int nrhs, int Ns, con
 hipError_t launch_pack_gauge(const void* canon, void* out, int par, int prec, const Geom& g,
                              hipStream_t st);
 
-// fifth-dimension programs on a half field (m5.hip), FP64 or FP32 storage:
-// out = c0 * prog(in) + c1 * other   (other may be null)
+// fifth-dimension programs on a half field (m5.hip):
+// out = c0 * prog(in) + c1 * other   (other may be null); dn: the program as a
+// dense matrix where it has one (N_s <= 16), diag: the coefficients of a pure scaling
 hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc,
                      const void* other, const float* other_sc, double c0, double c1,
-                     const M5Prog& prog, const void* coef, const KappaArr& kappa, long h, int nrhs,
-                     int Ns, hipStream_t st);
+                     const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
+                     int nrhs, int Ns, hipStream_t st);
 
 // BLAS-1 on half fields (blas.hip); n5 = h * nrhs * Ns five-dimensional sites
 // gate / gate_mode (GateMode) restrict the work to selected right-hand sides

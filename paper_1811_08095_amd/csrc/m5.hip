@@ -52,14 +52,63 @@ __global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in
   store_site<P>(out, out_sc, j, r, s, nrhs, NS, v);
 }
 
+// N_s <= 16: a lane's column set on the matrix cores, streaming (one load, one
+// store per 5D site, no LDS for the data).  The columns (site, right-hand side)
+// of a half field are consecutive, so a wave takes 64 / N_s of them.
+template <class P, int NS>
+__global__ void __launch_bounds__(256) m5_dense_kernel(const void* in, const float* in_sc, void* out, float* out_sc,
+                                                       const void* other, const float* other_sc, double c0,
+                                                       double c1, const DenseArg dn, const double* diag, long ncol,
+                                                       int nrhs) {
+  using R = typename P::real;
+  __shared__ R mat[4 * DENSE_N * DENSE_N];
+  int col, s;
+  dense_lane<NS>(threadIdx.x & 63, col, s);
+  const long j = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / NS) + col;
+  const bool valid = j < ncol;
+  cpx<R> v[12];
+#pragma unroll
+  for (int c = 0; c < 12; c++) v[c] = {R(0), R(0)};
+  if (valid) load_site<P>(in, in_sc, j, 0, s, 1, NS, v);
+  if (dn.tab) {
+    const int r = dn.mixed ? (int)(j % nrhs) : 0;
+    dense_stage<R, NS>(mat, dn.tab, dn.rho[0], dn.rho[MAXRHS], dn.mixed);
+    __syncthreads();
+    dense_apply<R>(v, mat, dn.mixed, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
+  }
+  if (!valid) return;
+  if (diag) {
+    const R p = (R)diag[s], m = (R)diag[NCOEF * NS + NS - 1 - s];
+#pragma unroll
+    for (int c = 0; c < 12; c++) v[c] = cscale(c < 6 ? p : m, v[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 12; c++) v[c] = cscale((R)c0, v[c]);
+  if (other) {
+    cpx<R> o[12];
+    load_site<P>(other, other_sc, j, 0, s, 1, NS, o);
+#pragma unroll
+    for (int c = 0; c < 12; c++) v[c] = cadd(v[c], cscale((R)c1, o[c]));
+  }
+  store_site<P>(out, out_sc, j, 0, s, 1, NS, v);
+}
+
 template <class P, int NS>
 static hipError_t launch_m5_t(const void* in, const float* in_sc, void* out, float* out_sc,
                               const void* other, const float* other_sc, double c0, double c1,
-                              const M5Prog& prog, const void* coef, const KappaArr& kappa, long h,
+                              const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
                               int nrhs, hipStream_t st) {
   using R = typename P::real;
   const int inner = nrhs * NS;
   if (inner > 256 || nrhs > MAXRHS) return hipErrorInvalidValue;
+  if constexpr (NS <= DENSE_N) {
+    // a program is dense, diagonal (one scaling) or absent
+    if (!dn.tab && !diag && prog.n > 0) return hipErrorInvalidValue;
+    const long ncol = h * nrhs;
+    hipLaunchKernelGGL((m5_dense_kernel<P, NS>), dim3((unsigned)((ncol * NS + 255) / 256)), dim3(256), 0, st, in, in_sc,
+                       out, out_sc, other, other_sc, c0, c1, dn, diag, ncol, nrhs);
+    return hipGetLastError();
+  } else {
   const int spb = 256 / inner;
   const int block = (spb * inner + 63) & ~63;
   const long nb = (h + spb - 1) / spb;
@@ -67,31 +116,32 @@ static hipError_t launch_m5_t(const void* in, const float* in_sc, void* out, flo
   hipLaunchKernelGGL((m5_kernel<P, NS>), dim3((unsigned)nb), dim3(block), sm, st, in, in_sc, out,
                      out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, spb);
   return hipGetLastError();
+  }
 }
 
 template <class P>
 static hipError_t launch_m5_p(const void* in, const float* in_sc, void* out, float* out_sc,
                               const void* other, const float* other_sc, double c0, double c1,
-                              const M5Prog& prog, const void* coef, const KappaArr& kappa, long h,
+                              const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
                               int nrhs, int Ns, hipStream_t st) {
   switch (Ns) {
-    case 4: return launch_m5_t<P, 4>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, st);
-    case 8: return launch_m5_t<P, 8>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, st);
-    case 16: return launch_m5_t<P, 16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, st);
-    case 32: return launch_m5_t<P, 32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, st);
+    case 4: return launch_m5_t<P, 4>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
+    case 8: return launch_m5_t<P, 8>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
+    case 16: return launch_m5_t<P, 16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
+    case 32: return launch_m5_t<P, 32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
   }
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc,
                      const void* other, const float* other_sc, double c0, double c1,
-                     const M5Prog& prog, const void* coef, const KappaArr& kappa, long h, int nrhs,
+                     const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h, int nrhs,
                      int Ns, hipStream_t st) {
   switch (prec) {
-    case PREC64: return launch_m5_p<SP64>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, Ns, st);
-    case PREC32: return launch_m5_p<SP32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, Ns, st);
-    case PREC16: return launch_m5_p<SP16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, Ns, st);
-    case PRECB16: return launch_m5_p<SPB16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, Ns, st);
+    case PREC64: return launch_m5_p<SP64>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
+    case PREC32: return launch_m5_p<SP32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
+    case PREC16: return launch_m5_p<SP16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
+    case PRECB16: return launch_m5_p<SPB16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
   }
   return hipErrorInvalidValue;
 }

@@ -39,7 +39,8 @@ enum CoefId : int8_t {
   CF_A_INV = 5,     // 1 / a_s
   CF_C = 6,         // c_s = (4 - m0) omega_s - 1
   CF_CSHIFT = 7,    // c_{s+1} (s < N-1), c_0 at s = N-1
-  NCOEF = 8
+  CF_OMEGA2 = 8,    // omega_s^2
+  NCOEF = 9
 };
 
 struct M5Op {
@@ -47,8 +48,33 @@ struct M5Op {
 };
 struct M5Prog {
   int n;
+  int dense;  // DenseId of the same operator as a dense matrix, or -1 (a scaling, or no program)
   M5Op op[4];
 };
+
+// ---- the same programs as dense matrices -------------------------------------
+// For N_s <= 16 every program with bidiagonal factors is also held as
+//     M(kappa) = M0 + rho u w^T,   rho = kappa / (1 + kappa q),
+// with M0, u, w and q independent of the mass: kappa enters each factor only
+// through its corner entry (a rank-1 term), and the rank-1 terms of a product
+// of a factor and the inverse of another share their row vector
+// (Sherman-Morrison).  Tables of 16 x 16 (N_s < 16: block-diagonal copies), in
+// slice order for both chiralities, FP64.
+enum DenseId : int {
+  DN_AINV = 0,    // A^{-1}
+  DN_AINV_T = 1,  // A^{-T}
+  DN_A = 2,       // A
+  DN_A_T = 3,     // A^T
+  DN_1PL = 4,     // 1 + L
+  DN_1PL_T = 5,   // (1 + L)^T
+  DN_1PL_INV = 6, // (1 + L)^{-1}
+  DN_AINV_WINV = 7, // A^{-1} omega^{-1}
+  NDENSE = 8
+};
+constexpr int DENSE_N = 16;
+constexpr int DENSE_CHI = DENSE_N * DENSE_N + 2 * DENSE_N;  // M0, u, w of one chirality
+constexpr int DENSE_LEN = 2 * DENSE_CHI;                    // both chiralities
+inline bool dense_ns(int Ns) { return Ns <= DENSE_N; }
 
 // ---- CG scalars, one record per right-hand side ----------------------------
 struct CGScal {
@@ -76,6 +102,32 @@ enum GateMode { GATE_NONE = 0, GATE_ACTIVE = 1, GATE_UPDATE = 2 };
 
 struct KappaArr {
   double v[MAXRHS];  // per right-hand side: -mu_r
+};
+
+// a dense program of a launch: table (null: none), rho per chirality and
+// right-hand side, and whether the right-hand sides' rho differ
+struct DenseArg {
+  const double* tab;
+  int mixed;
+  double rho[2 * MAXRHS];
+};
+
+// division of 0 <= n < 2^31 by a fixed 1 <= d < 2^31 as a multiplication:
+// with l = ceil(log2 d) and m = floor(2^(31 + l) / d) + 1, n / d = n m >> (31 + l)
+struct FastDiv {
+  uint32_t m, sh, d;
+  FastDiv() = default;
+  explicit FastDiv(uint32_t dd) {
+    uint32_t l = 0;
+    while ((uint64_t(1) << l) < dd) l++;
+    d = dd;
+    sh = 31 + l;
+    m = (uint32_t)((uint64_t(1) << sh) / dd + 1);
+  }
+#ifdef __HIPCC__
+  __host__ __device__
+#endif
+  uint32_t div(uint32_t n) const { return (uint32_t)(((uint64_t)n * m) >> sh); }
 };
 
 // ---- arguments of the fused hopping kernel ----------------------------------

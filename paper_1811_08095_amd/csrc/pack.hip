@@ -30,59 +30,193 @@ struct GeomK {
   long V, h;
 };
 
-template <class P>
-__global__ void pack_spinor_kernel(const double2* __restrict__ canon, int r0, void* out,
-                                   float* out_sc, int par, int nrhs, int Ns, GeomK g) {
-  using R = typename P::real;
-  const long n = g.h * nrhs * Ns;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int s = (int)(k % Ns);
-    const int r = (int)((k / Ns) % nrhs);
-    const long j = k / ((long)Ns * nrhs);
-    int t;
-    const long i = full_index(j, par, g.L, t);
-    const double2* src = canon + ((((long)(r0 + r) * Ns + s) * g.V + i) * 12);
-    cpx<R> v[12];
+// ---------------------------------------------------------------------------
+// canonical <-> both halves.  The canonical layout keeps slices far apart and a
+// site's 12 components together, the halves keep a site's slices together, so
+// a block transposes a tile of consecutive sites and all slices of one
+// right-hand side through LDS: the canonical side moves runs of TS * 192 bytes,
+// the half side 16-byte chunks over the slices.  One launch covers both
+// parities (an absent half is skipped on the way in, zeros on the way out) and
+// may apply a fifth-dimension operator while the tile is in registers: a
+// diagonal one, or a dense program on the matrix cores (N_s <= 16).
+// Bound: HBM (or the memory-side cache).  128 threads keep 12 16-byte loads in
+// flight each, five blocks to a CU in FP64 (26 KB of LDS); the column padding
+// keeps both sides of the transposition free of bank conflicts.  Measured
+// against one lane per 5D site reading its 192 bytes on its own, one launch per
+// parity and operator: 32^4 x 16 FP32, one parity in 499 us (was 688; 4.8 TB/s),
+// one parity and zeros out 760 us (942 + 523; 5.3 TB/s); 12x10x14x20 x 16, three
+// right-hand sides, both parities with omega in 93 us (2 x 74 + 2 x 59), out
+// 114 us (2 x 97).
+// ---------------------------------------------------------------------------
+struct TileArgs {
+  void* d[2];             // even, odd
+  float* sc[2];
+  const double* diag[2];  // coefficients of a diagonal operator, or null
+  DenseArg dn;            // dense program (tab null: none) ...
+  int dn_on;              // ... of the parities whose bit is set
+  int r0, nrhs;
+  int only;       // packing one parity alone: the tile is TS of its sites; else -1
+  long n;         // sites: V, or V / 2
+  long V;
+  FastDiv dx, dy, dz;  // Lx (Lx / 2 with only >= 0), Ly, Lz
+};
+
+template <int NS>
+struct Tile {
+  static constexpr int T = 128;       // threads: two waves
+  static constexpr int TS = T / NS;   // sites
+};
+
+// full-lattice index i, half-lattice index j and parity of site k of the launch
+__device__ __forceinline__ void site_of(const TileArgs& a, uint32_t k, uint32_t& i, uint32_t& j, int& par) {
+  const uint32_t row = a.dx.div(k), x = k - row * a.dx.d;
+  const uint32_t zt = a.dy.div(row), y = row - zt * a.dy.d;
+  const uint32_t t = a.dz.div(zt), z = zt - t * a.dz.d;
+  if (a.only >= 0) {
+    par = a.only;
+    j = k;
+    i = 2 * k + ((y + z + t + par) & 1);
+  } else {
+    par = (x + y + z + t) & 1;
+    i = k;
+    j = row * (a.dx.d >> 1) + (x >> 1);
+  }
+}
+
+// site of the tile and slice of this lane on the half side
+template <int NS>
+__device__ __forceinline__ void tile_lane(int& site, int& s) {
+  if constexpr (NS <= DENSE_N) {
+    int col;
+    dense_lane<NS>(threadIdx.x & 63, col, s);
+    site = (threadIdx.x >> 6) * (64 / NS) + col;
+  } else {
+    site = threadIdx.x / NS;
+    s = threadIdx.x % NS;
+  }
+}
+
+template <int NS, class R>
+__device__ __forceinline__ void diag_apply(cpx<R> (&v)[12], const double* diag, int s) {
+  const R p = (R)diag[s], m = (R)diag[NCOEF * NS + NS - 1 - s];
 #pragma unroll
-    for (int c = 0; c < 12; c++) {
-      double2 z = src[c];
-      v[c] = {(R)z.x, (R)z.y};
+  for (int c = 0; c < 12; c++) v[c] = cscale(c < 6 ? p : m, v[c]);
+}
+
+// the operators of the lane's parity; every lane calls it
+template <int NS, class R>
+__device__ __forceinline__ void tile_program(cpx<R> (&v)[12], const TileArgs& a, int par, int s, const R* mat) {
+  if constexpr (NS <= DENSE_N) {
+    if (a.dn.tab) {
+      cpx<R> w[12];
+#pragma unroll
+      for (int c = 0; c < 12; c++) w[c] = v[c];
+      dense_apply<R>(w, mat, false, R(0), R(0));
+      const bool on = (a.dn_on >> par) & 1;
+#pragma unroll
+      for (int c = 0; c < 12; c++) {
+        v[c].re = on ? w[c].re : v[c].re;
+        v[c].im = on ? w[c].im : v[c].im;
+      }
     }
-    store_site<P>(out, out_sc, j, r, s, nrhs, Ns, v);
   }
+  const double* diag = par ? a.diag[1] : a.diag[0];
+  if (diag) diag_apply<NS>(v, diag, s);
 }
 
-template <class P>
-__global__ void unpack_spinor_kernel(const void* in, const float* in_sc, double2* __restrict__ canon,
-                                     int r0, int par, int nrhs, int Ns, GeomK g) {
+template <int NS, class R>
+__device__ __forceinline__ void tile_stage(const TileArgs& a, int r, R* mat) {
+  if constexpr (NS <= DENSE_N)
+    if (a.dn.tab) dense_stage<R, NS>(mat, a.dn.tab, a.dn.rho[r], a.dn.rho[MAXRHS + r], false);
+}
+
+template <int NS>
+struct TileLds {
+  static constexpr int COL = NS + 1;  // padded column
+  static constexpr int N = Tile<NS>::TS * 12 * COL;
+};
+
+typedef double dbl2 __attribute__((ext_vector_type(2)));
+
+template <class P, int NS>
+__global__ void __launch_bounds__(Tile<NS>::T, 3) pack_tile_kernel(const double2* __restrict__ canon, const TileArgs a) {
   using R = typename P::real;
-  const long n = g.h * nrhs * Ns;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int s = (int)(k % Ns);
-    const int r = (int)((k / Ns) % nrhs);
-    const long j = k / ((long)Ns * nrhs);
-    int t;
-    const long i = full_index(j, par, g.L, t);
-    double2* dst = canon + ((((long)(r0 + r) * Ns + s) * g.V + i) * 12);
-    cpx<R> v[12];
-    load_site<P>(in, in_sc, j, r, s, nrhs, Ns, v);
+  constexpr int T = Tile<NS>::T, TS = Tile<NS>::TS, COL = TileLds<NS>::COL;
+  extern __shared__ __align__(16) unsigned char smem[];
+  cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem);
+  R* mat = reinterpret_cast<R*>(buf + TileLds<NS>::N);
+  const int r = blockIdx.y, tid = threadIdx.x;
+  const uint32_t k0 = blockIdx.x * TS;
+  const int n = (int)min((long)TS, a.n - (long)k0);
+  // one parity: its sites are every other one of a row, whose parity alternates
+  // with the row; a thread's 12 components lie in at most four sites
+  const dbl2* src = reinterpret_cast<const dbl2*>(canon) + (long)(a.r0 + r) * NS * a.V * 12;
+  dbl2 q[12];
 #pragma unroll
-    for (int c = 0; c < 12; c++) dst[c] = make_double2((double)v[c].re, (double)v[c].im);
+  for (int k = 0; k < 12; k++) {  // NS runs of TS * 12 components
+    const int e = tid + k * T, sl = e / (TS * 12), rem = e % (TS * 12);
+    const int sr = min(rem / 12, n - 1);
+    uint32_t i = k0 + sr;
+    if (a.only >= 0) {
+      uint32_t jj;
+      int pp;
+      site_of(a, k0 + sr, i, jj, pp);
+    }
+    q[k] = __builtin_nontemporal_load(src + ((long)sl * a.V + i) * 12 + rem % 12);
   }
+  tile_stage<NS, R>(a, r, mat);
+#pragma unroll
+  for (int k = 0; k < 12; k++) {
+    const int e = tid + k * T, sl = e / (TS * 12), rem = e % (TS * 12);
+    buf[rem * COL + sl] = {(R)q[k].x, (R)q[k].y};
+  }
+  int site, s, par;
+  uint32_t i, j;
+  tile_lane<NS>(site, s);
+  site_of(a, k0 + min(site, n - 1), i, j, par);
+  __syncthreads();
+  cpx<R> v[12];
+#pragma unroll
+  for (int c = 0; c < 12; c++) v[c] = buf[(site * 12 + c) * COL + s];
+  tile_program<NS, R>(v, a, par, s, mat);
+  if (site < n)
+    store_site<P>(par ? a.d[1] : a.d[0], par ? a.sc[1] : a.sc[0], j, r, s, a.nrhs, NS, v);
 }
 
-__global__ void zero_canon_parity_kernel(double2* __restrict__ canon, int r0, int par, int nrhs,
-                                         int Ns, GeomK g) {
-  const long n = g.h * nrhs * Ns;
-  for (long k = blockIdx.x * (long)blockDim.x + threadIdx.x; k < n; k += (long)gridDim.x * blockDim.x) {
-    const int s = (int)(k % Ns);
-    const int r = (int)((k / Ns) % nrhs);
-    const long j = k / ((long)Ns * nrhs);
-    int t;
-    const long i = full_index(j, par, g.L, t);
-    double2* dst = canon + ((((long)(r0 + r) * Ns + s) * g.V + i) * 12);
+template <class P, int NS>
+__global__ void __launch_bounds__(Tile<NS>::T, 3) unpack_tile_kernel(double2* __restrict__ canon, const TileArgs a) {
+  using R = typename P::real;
+  constexpr int T = Tile<NS>::T, TS = Tile<NS>::TS, COL = TileLds<NS>::COL;
+  extern __shared__ __align__(16) unsigned char smem[];
+  cpx<R>* buf = reinterpret_cast<cpx<R>*>(smem);
+  R* mat = reinterpret_cast<R*>(buf + TileLds<NS>::N);
+  const int r = blockIdx.y, tid = threadIdx.x;
+  const uint32_t i0 = blockIdx.x * TS;
+  const int n = (int)min((long)TS, a.V - (long)i0);
+  int site, s, par;
+  uint32_t i, j;
+  tile_lane<NS>(site, s);
+  site_of(a, i0 + min(site, n - 1), i, j, par);
+  const void* half = par ? a.d[1] : a.d[0];
+  cpx<R> v[12];
 #pragma unroll
-    for (int c = 0; c < 12; c++) dst[c] = make_double2(0.0, 0.0);
+  for (int c = 0; c < 12; c++) v[c] = {R(0), R(0)};
+  if (half) load_site<P>(half, par ? a.sc[1] : a.sc[0], j, r, s, a.nrhs, NS, v);
+  tile_stage<NS, R>(a, r, mat);
+  __syncthreads();
+  tile_program<NS, R>(v, a, par, s, mat);
+#pragma unroll
+  for (int c = 0; c < 12; c++) buf[(site * 12 + c) * COL + s] = v[c];
+  __syncthreads();
+  dbl2* dst = reinterpret_cast<dbl2*>(canon) + ((long)(a.r0 + r) * NS * a.V + i0) * 12;
+#pragma unroll
+  for (int k = 0; k < 12; k++) {
+    const int e = tid + k * T, sl = e / (TS * 12), rem = e % (TS * 12);
+    if (rem < n * 12) {
+      const cpx<R> z = buf[rem * COL + sl];
+      const dbl2 w = {(double)z.re, (double)z.im};
+      __builtin_nontemporal_store(w, dst + (long)sl * a.V * 12 + rem);
+    }
   }
 }
 
@@ -178,42 +312,64 @@ static dim3 grid_for(long n, int block) {
   return dim3((unsigned)b);
 }
 
-hipError_t launch_pack_spinor(int prec, const void* canon, int r0, void* out, float* out_sc, int par,
-                              int nrhs, int Ns, const Geom& g, hipStream_t st) {
-  const long n = g.h * nrhs * Ns;
-  const dim3 gr = grid_for(n, 256);
-  const double2* c = reinterpret_cast<const double2*>(canon);
-  switch (prec) {
-    case PREC64: hipLaunchKernelGGL(pack_spinor_kernel<SP64>, gr, dim3(256), 0, st, c, r0, out, out_sc, par, nrhs, Ns, gk(g)); break;
-    case PREC32: hipLaunchKernelGGL(pack_spinor_kernel<SP32>, gr, dim3(256), 0, st, c, r0, out, out_sc, par, nrhs, Ns, gk(g)); break;
-    case PREC16: hipLaunchKernelGGL(pack_spinor_kernel<SP16>, gr, dim3(256), 0, st, c, r0, out, out_sc, par, nrhs, Ns, gk(g)); break;
-    case PRECB16: hipLaunchKernelGGL(pack_spinor_kernel<SPB16>, gr, dim3(256), 0, st, c, r0, out, out_sc, par, nrhs, Ns, gk(g)); break;
-    default: return hipErrorInvalidValue;
-  }
-  return hipGetLastError();
-}
-
-hipError_t launch_unpack_spinor(int prec, const void* in, const float* in_sc, void* canon, int r0,
-                                int par, int nrhs, int Ns, const Geom& g, hipStream_t st) {
-  const long n = g.h * nrhs * Ns;
-  const dim3 gr = grid_for(n, 256);
+template <class P, int NS>
+static hipError_t launch_tile(bool pack, void* canon, const TileArgs& a, hipStream_t st) {
+  using R = typename P::real;
+  constexpr int TS = Tile<NS>::TS;
+  if (a.dn.tab && NS > DENSE_N) return hipErrorInvalidValue;
+  const size_t sm = TileLds<NS>::N * sizeof(cpx<R>) + (a.dn.tab ? 2 * DENSE_N * DENSE_N * sizeof(R) : 0);
+  const dim3 grid((unsigned)((a.n + TS - 1) / TS), a.nrhs);
   double2* c = reinterpret_cast<double2*>(canon);
-  switch (prec) {
-    case PREC64: hipLaunchKernelGGL(unpack_spinor_kernel<SP64>, gr, dim3(256), 0, st, in, in_sc, c, r0, par, nrhs, Ns, gk(g)); break;
-    case PREC32: hipLaunchKernelGGL(unpack_spinor_kernel<SP32>, gr, dim3(256), 0, st, in, in_sc, c, r0, par, nrhs, Ns, gk(g)); break;
-    case PREC16: hipLaunchKernelGGL(unpack_spinor_kernel<SP16>, gr, dim3(256), 0, st, in, in_sc, c, r0, par, nrhs, Ns, gk(g)); break;
-    case PRECB16: hipLaunchKernelGGL(unpack_spinor_kernel<SPB16>, gr, dim3(256), 0, st, in, in_sc, c, r0, par, nrhs, Ns, gk(g)); break;
-    default: return hipErrorInvalidValue;
-  }
+  if (pack) hipLaunchKernelGGL((pack_tile_kernel<P, NS>), grid, dim3(Tile<NS>::T), sm, st, c, a);
+  else hipLaunchKernelGGL((unpack_tile_kernel<P, NS>), grid, dim3(Tile<NS>::T), sm, st, c, a);
   return hipGetLastError();
 }
 
-hipError_t launch_zero_canon_parity(void* canon, int r0, int par, int nrhs, int Ns, const Geom& g,
-                                    hipStream_t st) {
-  const long n = g.h * nrhs * Ns;
-  hipLaunchKernelGGL(zero_canon_parity_kernel, grid_for(n, 256), dim3(256), 0, st,
-                     reinterpret_cast<double2*>(canon), r0, par, nrhs, Ns, gk(g));
-  return hipGetLastError();
+template <class P>
+static hipError_t launch_tile_p(bool pack, void* canon, const TileArgs& a, int Ns, hipStream_t st) {
+  switch (Ns) {
+    case 4: return launch_tile<P, 4>(pack, canon, a, st);
+    case 8: return launch_tile<P, 8>(pack, canon, a, st);
+    case 16: return launch_tile<P, 16>(pack, canon, a, st);
+    case 32: return launch_tile<P, 32>(pack, canon, a, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+static hipError_t tile_any(bool pack, int prec, void* canon, int r0, const HalfIO& e, const HalfIO& o, int nrhs,
+                           int Ns, const Geom& g, hipStream_t st) {
+  TileArgs a;
+  if (e.dn.tab && o.dn.tab && e.dn.tab != o.dn.tab) return hipErrorInvalidValue;  // one dense program a launch
+  a.dn = e.dn.tab ? e.dn : o.dn;
+  a.dn_on = (e.dn.tab ? 1 : 0) | (o.dn.tab ? 2 : 0);
+  a.d[0] = e.d, a.d[1] = o.d;
+  a.sc[0] = e.sc, a.sc[1] = o.sc;
+  a.diag[0] = e.diag, a.diag[1] = o.diag;
+  a.r0 = r0;
+  a.nrhs = nrhs;
+  a.V = g.V;
+  a.only = !pack || (e.d && o.d) ? -1 : (e.d ? 0 : 1);
+  a.n = a.only >= 0 ? g.h : g.V;
+  a.dx = FastDiv(a.only >= 0 ? g.L[0] / 2 : g.L[0]);
+  a.dy = FastDiv(g.L[1]);
+  a.dz = FastDiv(g.L[2]);
+  switch (prec) {
+    case PREC64: return launch_tile_p<SP64>(pack, canon, a, Ns, st);
+    case PREC32: return launch_tile_p<SP32>(pack, canon, a, Ns, st);
+    case PREC16: return launch_tile_p<SP16>(pack, canon, a, Ns, st);
+    case PRECB16: return launch_tile_p<SPB16>(pack, canon, a, Ns, st);
+  }
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_pack(int prec, const void* canon, int r0, const HalfIO& e, const HalfIO& o, int nrhs, int Ns,
+                       const Geom& g, hipStream_t st) {
+  return tile_any(true, prec, const_cast<void*>(canon), r0, e, o, nrhs, Ns, g, st);
+}
+
+hipError_t launch_unpack(int prec, const HalfIO& e, const HalfIO& o, void* canon, int r0, int nrhs, int Ns,
+                         const Geom& g, hipStream_t st) {
+  return tile_any(false, prec, canon, r0, e, o, nrhs, Ns, g, st);
 }
 
 hipError_t launch_boundary_embed(const void* q, void* f, int nrhs, int Ns, const Geom& g, hipStream_t st) {

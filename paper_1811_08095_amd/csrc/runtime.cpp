@@ -69,10 +69,11 @@ size_t Workspace::total() const {
 
 // ---- fifth-dimension programs -------------------------------------------------
 
-static M5Prog mk(std::initializer_list<M5Op> ops) {
+static M5Prog mk(std::initializer_list<M5Op> ops, int dense = -1) {
   M5Prog p;
   std::memset(&p, 0, sizeof(p));
   p.n = 0;
+  p.dense = dense;
   for (const M5Op& o : ops) p.op[p.n++] = o;
   return p;
 }
@@ -81,25 +82,132 @@ static M5Op op(M5Type t, CoefId d, CoefId e = CF_ONE) { return M5Op{t, d, e, 0};
 M5Prog prog_none() { return mk({}); }
 // A^{-1} = (1 + L) B^{-1} omega,  B = a + c L
 M5Prog prog_ainv() {
-  return mk({op(M5_SCALE, CF_OMEGA), op(M5_SOLVE_LO, CF_A_INV, CF_C), op(M5_MUL_LO, CF_ONE, CF_ONE)});
+  return mk({op(M5_SCALE, CF_OMEGA), op(M5_SOLVE_LO, CF_A_INV, CF_C), op(M5_MUL_LO, CF_ONE, CF_ONE)}, DN_AINV);
 }
 // A^{-T} = omega B^{-T} (1 + L)^T
 M5Prog prog_ainv_t() {
-  return mk({op(M5_MUL_UP, CF_ONE, CF_ONE), op(M5_SOLVE_UP, CF_A_INV, CF_CSHIFT), op(M5_SCALE, CF_OMEGA)});
+  return mk({op(M5_MUL_UP, CF_ONE, CF_ONE), op(M5_SOLVE_UP, CF_A_INV, CF_CSHIFT), op(M5_SCALE, CF_OMEGA)}, DN_AINV_T);
 }
 // A = omega^{-1} B (1 + L)^{-1}
 M5Prog prog_a() {
-  return mk({op(M5_SOLVE_LO, CF_ONE, CF_ONE), op(M5_MUL_LO, CF_A, CF_C), op(M5_SCALE, CF_OMEGA_INV)});
+  return mk({op(M5_SOLVE_LO, CF_ONE, CF_ONE), op(M5_MUL_LO, CF_A, CF_C), op(M5_SCALE, CF_OMEGA_INV)}, DN_A);
 }
 // A^T = (1 + L)^{-T} B^T omega^{-1}
 M5Prog prog_a_t() {
-  return mk({op(M5_SCALE, CF_OMEGA_INV), op(M5_MUL_UP, CF_A, CF_CSHIFT), op(M5_SOLVE_UP, CF_ONE, CF_ONE)});
+  return mk({op(M5_SCALE, CF_OMEGA_INV), op(M5_MUL_UP, CF_A, CF_CSHIFT), op(M5_SOLVE_UP, CF_ONE, CF_ONE)}, DN_A_T);
 }
 M5Prog prog_omega() { return mk({op(M5_SCALE, CF_OMEGA)}); }
 M5Prog prog_omega_inv() { return mk({op(M5_SCALE, CF_OMEGA_INV)}); }
-M5Prog prog_1pl() { return mk({op(M5_MUL_LO, CF_ONE, CF_ONE)}); }
-M5Prog prog_1pl_inv() { return mk({op(M5_SOLVE_LO, CF_ONE, CF_ONE)}); }
-M5Prog prog_1pl_t() { return mk({op(M5_MUL_UP, CF_ONE, CF_ONE)}); }
+M5Prog prog_1pl() { return mk({op(M5_MUL_LO, CF_ONE, CF_ONE)}, DN_1PL); }
+M5Prog prog_1pl_inv() { return mk({op(M5_SOLVE_LO, CF_ONE, CF_ONE)}, DN_1PL_INV); }
+M5Prog prog_1pl_t() { return mk({op(M5_MUL_UP, CF_ONE, CF_ONE)}, DN_1PL_T); }
+M5Prog prog_ainv_winv() {
+  return mk({op(M5_SOLVE_LO, CF_A_INV, CF_C), op(M5_MUL_LO, CF_ONE, CF_ONE)}, DN_AINV_WINV);
+}
+M5Prog prog_omega2() { return mk({op(M5_SCALE, CF_OMEGA2)}); }
+
+// The dense forms, in the chirality-local order of the programs.  With L_k the
+// shift (corner kappa) and e_l the last unit vector,
+//     P = 1 + L = P0 + kappa e_0 e_l^T,   B = a + c L = B0 + kappa c_0 e_0 e_l^T,
+//     (X0 + kappa x e_0 e_l^T)^{-1} = X0^{-1} - kappa x / (1 + kappa x e_l^T X0^{-1} e_0) X0^{-1} e_0 e_l^T X0^{-1},
+// and a product of one factor and the inverse of the other collapses to one
+// rank-1 term: A^{-1} = P B^{-1} omega has u = e_0 - c_0 P0 B0^{-1} e_0,
+// w^T = e_l^T B0^{-1} omega, q = c_0 (B0^{-1})_{l0}; A = omega^{-1} B P^{-1} has
+// u = omega^{-1} (c_0 e_0 - B0 P0^{-1} e_0), w^T = e_l^T P0^{-1}, q = (P0^{-1})_{l0}.
+void dense_tables(int Ns, double m0, const double* omega, double* tab, double q[][2]) {
+  using ld = long double;
+  using Mat = std::vector<std::vector<ld>>;
+  const int N = Ns, l = Ns - 1;
+  auto zeros = [&]() { return Mat(N, std::vector<ld>(N, 0.0L)); };
+  auto mul = [&](const Mat& x, const Mat& y) {
+    Mat z = zeros();
+    for (int i = 0; i < N; i++)
+      for (int k = 0; k < N; k++)
+        for (int j = 0; j < N; j++) z[i][j] += x[i][k] * y[k][j];
+    return z;
+  };
+  auto inv_lo = [&](const Mat& x) {  // inverse of a lower bidiagonal matrix
+    Mat z = zeros();
+    for (int j = 0; j < N; j++) {
+      z[j][j] = 1.0L / x[j][j];
+      for (int i = j + 1; i < N; i++) z[i][j] = -x[i][i - 1] * z[i - 1][j] / x[i][i];
+    }
+    return z;
+  };
+  std::memset(tab, 0, sizeof(double) * NDENSE * DENSE_LEN);
+  const int rep = DENSE_N / N;
+  for (int chi = 0; chi < 2; chi++) {
+    std::vector<ld> w(N), c(N);
+    Mat P0 = zeros(), B0 = zeros();
+    for (int s = 0; s < N; s++) {
+      w[s] = omega[chi ? N - 1 - s : s];
+      c[s] = (4.0L - m0) * w[s] - 1.0L;
+      P0[s][s] = 1.0L;
+      B0[s][s] = (4.0L - m0) * w[s] + 1.0L;
+      if (s > 0) P0[s][s - 1] = 1.0L, B0[s][s - 1] = c[s];
+    }
+    const Mat Pi = inv_lo(P0), Bi = inv_lo(B0);
+    auto put = [&](int id, const Mat& m, const std::vector<ld>& u, const std::vector<ld>& v, ld qq, bool tr) {
+      double* t = tab + (size_t)id * DENSE_LEN + chi * DENSE_CHI;
+      auto sl = [&](int s) { return chi ? N - 1 - s : s; };  // local index of slice s
+      for (int b = 0; b < rep; b++)
+        for (int i = 0; i < N; i++) {
+          for (int j = 0; j < N; j++)
+            t[(b * N + i) * DENSE_N + b * N + j] = (double)(tr ? m[sl(j)][sl(i)] : m[sl(i)][sl(j)]);
+          t[DENSE_N * DENSE_N + b * N + i] = (double)(tr ? v[sl(i)] : u[sl(i)]);
+          t[DENSE_N * DENSE_N + DENSE_N + b * N + i] = (double)(tr ? u[sl(i)] : v[sl(i)]);
+        }
+      q[id][chi] = (double)qq;
+    };
+    std::vector<ld> u(N), v(N);
+    // A^{-1}, A^{-T}, A^{-1} omega^{-1}
+    Mat m = mul(P0, Bi);
+    for (int s = 0; s < N; s++) {
+      u[s] = (s == 0 ? 1.0L : 0.0L) - c[0] * m[s][0];
+      v[s] = Bi[l][s];
+    }
+    put(DN_AINV_WINV, m, u, v, c[0] * Bi[l][0], false);
+    for (int i = 0; i < N; i++)
+      for (int s = 0; s < N; s++) m[i][s] *= w[s];
+    for (int s = 0; s < N; s++) v[s] *= w[s];
+    put(DN_AINV, m, u, v, c[0] * Bi[l][0], false);
+    put(DN_AINV_T, m, u, v, c[0] * Bi[l][0], true);
+    // A, A^T
+    m = mul(B0, Pi);
+    for (int s = 0; s < N; s++) {
+      u[s] = ((s == 0 ? c[0] : 0.0L) - m[s][0]) / w[s];
+      v[s] = Pi[l][s];
+    }
+    for (int i = 0; i < N; i++)
+      for (int s = 0; s < N; s++) m[i][s] /= w[i];
+    put(DN_A, m, u, v, Pi[l][0], false);
+    put(DN_A_T, m, u, v, Pi[l][0], true);
+    // (1 + L)^{-1}, 1 + L, (1 + L)^T
+    for (int s = 0; s < N; s++) u[s] = -Pi[s][0];
+    put(DN_1PL_INV, Pi, u, v, Pi[l][0], false);
+    for (int s = 0; s < N; s++) u[s] = s == 0, v[s] = s == l;
+    put(DN_1PL, P0, u, v, 0.0L, false);
+    put(DN_1PL_T, P0, u, v, 0.0L, true);
+  }
+}
+
+DenseArg dense_arg(const OpCtx& c, const M5Prog& p) {
+  DenseArg d;
+  std::memset(&d, 0, sizeof(d));
+  if (!dense_ns(c.Ns()) || p.n == 0 || p.dense < 0) return d;
+  d.tab = c.S->dense + (size_t)p.dense * DENSE_LEN;
+  for (int chi = 0; chi < 2; chi++)
+    for (int r = 0; r < c.nrhs; r++) {
+      d.rho[chi * MAXRHS + r] = c.kappa[r] / (1.0 + c.kappa[r] * c.S->dense_q[p.dense][chi]);
+      if (c.kappa[r] != c.kappa[0]) d.mixed = 1;
+    }
+  return d;
+}
+
+const double* diag_of(const OpCtx& c, const M5Prog& p) {
+  if (p.n != 1 || p.op[0].type != M5_SCALE) return nullptr;
+  return reinterpret_cast<const double*>(c.S->coef64) + p.op[0].d * c.Ns();
+}
 
 // ---- kernel helpers -------------------------------------------------------------
 
@@ -216,7 +324,36 @@ hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p, doub
   KappaArr k;
   for (int r = 0; r < MAXRHS; r++) k.v[r] = r < c.nrhs ? c.kappa[r] : 0.0;
   return launch_m5(c.prec, in.d, in.sc, out.d, out.sc, other ? other->d : nullptr,
-                   other ? other->sc : nullptr, c0, c1, p, c.coef(), k, c.h(), c.nrhs, c.Ns(), c.st);
+                   other ? other->sc : nullptr, c0, c1, p, dense_arg(c, p), diag_of(c, p), c.coef(), k, c.h(),
+                   c.nrhs, c.Ns(), c.st);
+}
+
+// a program that runs inside the layout kernels: none, a scaling, or a dense one
+static bool in_tile(const OpCtx& c, const M5Prog& p) { return p.n == 0 || diag_of(c, p) || dense_ns(c.Ns()); }
+static HalfIO half_io(const OpCtx& c, const HV* v, const M5Prog& p) {
+  HalfIO h;
+  if (!v) return h;
+  h.d = v->d;
+  h.sc = v->sc;
+  if (in_tile(c, p)) {
+    h.dn = dense_arg(c, p);
+    h.diag = diag_of(c, p);
+  }
+  return h;
+}
+
+hipError_t pack(const OpCtx& c, const void* canon, int r0, const HV* e, const HV* o, const M5Prog& pe,
+                const M5Prog& po) {
+  HIPRET(launch_pack(c.prec, canon, r0, half_io(c, e, pe), half_io(c, o, po), c.nrhs, c.Ns(), c.S->lat->g, c.st));
+  if (e && !in_tile(c, pe)) HIPRET(m5(c, *e, *e, pe));
+  if (o && !in_tile(c, po)) HIPRET(m5(c, *o, *o, po));
+  return hipSuccess;
+}
+
+hipError_t unpack(const OpCtx& c, const HV* e, const HV* o, void* canon, int r0, const M5Prog& p) {
+  if (e && !in_tile(c, p)) HIPRET(m5(c, *e, *e, p));
+  if (o && !in_tile(c, p)) HIPRET(m5(c, *o, *o, p));
+  return launch_unpack(c.prec, half_io(c, e, p), half_io(c, o, p), canon, r0, c.nrhs, c.Ns(), c.S->lat->g, c.st);
 }
 
 // ---- profiler -------------------------------------------------------------------

@@ -67,6 +67,8 @@ struct odwf_solver_s {
   std::vector<double> omega;
   void* coef64 = nullptr;  // [2][NCOEF][Ns] double
   void* coef32 = nullptr;  // [2][NCOEF][Ns] float
+  double* dense = nullptr; // [NDENSE][DENSE_LEN] dense programs (Ns <= 16)
+  double dense_q[odwf::NDENSE][2] = {};  // their q per chirality
   std::mutex mtx;
   std::map<hipStream_t, odwf::Workspace*> ws;
   odwf::Workspace& workspace(hipStream_t st);
@@ -85,6 +87,11 @@ M5Prog prog_omega_inv();
 M5Prog prog_1pl();       // 1 + L
 M5Prog prog_1pl_inv();   // (1 + L)^{-1}
 M5Prog prog_1pl_t();     // (1 + L)^dag
+M5Prog prog_ainv_winv(); // A^{-1} omega^{-1}
+M5Prog prog_omega2();    // omega^2
+
+// tables of the dense programs of a solver (host; Ns <= 16): tab [NDENSE][DENSE_LEN], q [NDENSE][2]
+void dense_tables(int Ns, double m0, const double* omega, double* tab, double q[][2]);
 
 // per-call operator context (one chunk of <= MAXRHS right-hand sides)
 struct OpCtx {
@@ -116,6 +123,18 @@ struct HopOpt {
 };
 
 hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out, const HopOpt& o);
+// a program as the kernels take it: its dense form (table null: none) and its
+// coefficients when it is a pure scaling (null: not one)
+DenseArg dense_arg(const OpCtx& c, const M5Prog& p);
+const double* diag_of(const OpCtx& c, const M5Prog& p);
+
+// canonical <-> halves (null halves skipped / zeroed), each parity through its program
+hipError_t pack(const OpCtx& c, const void* canon, int r0, const HV* e, const HV* o, const M5Prog& pe, const M5Prog& po);
+hipError_t unpack(const OpCtx& c, const HV* e, const HV* o, void* canon, int r0, const M5Prog& p);
+inline hipError_t pack(const OpCtx& c, const void* canon, int r0, const HV* e, const HV* o) {
+  return pack(c, canon, r0, e, o, prog_none(), prog_none());
+}
+
 hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p, double c0 = 1.0,
               const HV* other = nullptr, double c1 = 0.0);
 

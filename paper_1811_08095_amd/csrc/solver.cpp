@@ -23,34 +23,24 @@
 
 namespace odwf {
 
-hipError_t apply_D(const OpCtx& c, const HV& ie, const HV& io, const HV& te, const HV& to,
-                   const HV& oe, const HV& oo) {
-  // y = (1 + L) psi; out = omega (A y_site + W y)
-  HIPRET(m5(c, ie, te, prog_1pl()));
-  HIPRET(m5(c, io, to, prog_1pl()));
+hipError_t apply_D(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo, const M5Prog& po) {
   HopOpt o;
   o.px = prog_a();
-  o.po = prog_omega();
-  o.x = &te;
-  HIPRET(hop(c, 0, 0, to, &oe, o));
-  o.x = &to;
-  HIPRET(hop(c, 1, 0, te, &oo, o));
-  return hipSuccess;
+  o.po = po;
+  o.x = &ye;
+  HIPRET(hop(c, 0, 0, yo, &oe, o));
+  o.x = &yo;
+  return hop(c, 1, 0, ye, &oo, o);
 }
 
-hipError_t apply_Ddag(const OpCtx& c, const HV& ie, const HV& io, const HV& te, const HV& to,
-                      const HV& oe, const HV& oo) {
-  // y = omega psi; out = (1 + L)^dag (A^dag y_site + W^dag y)
-  HIPRET(m5(c, ie, te, prog_omega()));
-  HIPRET(m5(c, io, to, prog_omega()));
+hipError_t apply_Ddag(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo) {
   HopOpt o;
   o.px = prog_a_t();
   o.po = prog_1pl_t();
-  o.x = &te;
-  HIPRET(hop(c, 0, 1, to, &oe, o));
-  o.x = &to;
-  HIPRET(hop(c, 1, 1, te, &oo, o));
-  return hipSuccess;
+  o.x = &ye;
+  HIPRET(hop(c, 0, 1, yo, &oe, o));
+  o.x = &yo;
+  return hop(c, 1, 1, ye, &oo, o);
 }
 
 hipError_t apply_schur(const OpCtx& c, const HV& in, const HV& to, const HV& out) {
@@ -247,11 +237,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   // ---- right-hand side f of the iterated system, initial guess y ----------
   if (mode == ODWF_SOLVE_FULL) {
     // b' = omega^{-1} b; phi_e = A^{-1}(b'_e - W_eo A^{-1} b'_o); f = S_e^dag phi_e
-    CHK(launch_pack_spinor(PREC64, b, r0, e2.d, nullptr, 0, nrhs, Ns, g, st));
-    CHK(launch_pack_spinor(PREC64, b, r0, o0.d, nullptr, 1, nrhs, Ns, g, st));
-    CHK(m5(c64, e2, e2, prog_omega_inv()));
-    CHK(m5(c64, o0, o0, prog_omega_inv()));
-    CHK(m5(c64, o0, o0, prog_ainv()));
+    CHK(pack(c64, b, r0, &e2, &o0, prog_omega_inv(), prog_ainv_winv()));
     HopOpt k;
     k.x = &e2;
     k.ch = -1.0;
@@ -260,24 +246,25 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
     CHK(hop(c64, 0, 0, o0, &e1, k));  // phi in e1
     CHK(apply_schur_dag(c64, e1, e2, o0, e0));
     if (use_x0) {
-      CHK(launch_pack_spinor(PREC64, x, r0, e1.d, nullptr, 0, nrhs, Ns, g, st));
-      CHK(m5(c64, e1, e1, prog_1pl()));
+      CHK(pack(c64, x, r0, &e1, nullptr, prog_1pl(), prog_none()));
     } else {
       CHK(launch_vec_zero(PREC64, e1.d, nullptr, h, nrhs, Ns, st));
     }
   } else {
     if (io.bcast_b) {
       // one source for every right-hand side of the chunk (several masses)
-      CHK(launch_pack_spinor(PREC64, b, 0, o0.d, nullptr, 0, 1, Ns, g, st));
+      OpCtx one = c64;
+      one.nrhs = 1;
+      CHK(pack(one, b, 0, &o0, nullptr));
       for (int q = 0; q < nrhs; q++)
         CHK(launch_vec_copy_rhs(PREC64, o0.d, nullptr, 1, 0, PREC64, e0.d, nullptr, nrhs, q, h, Ns, st));
     } else {
-      CHK(launch_pack_spinor(PREC64, b, r0, e0.d, nullptr, 0, nrhs, Ns, g, st));
+      CHK(pack(c64, b, r0, &e0, nullptr));
     }
     if (io.y_packed) {
       if (!use_x0) CHK(launch_vec_zero(PREC64, e1.d, nullptr, h, nrhs, Ns, st));
     } else if (use_x0) {
-      CHK(launch_pack_spinor(PREC64, x, r0, e1.d, nullptr, 0, nrhs, Ns, g, st));
+      CHK(pack(c64, x, r0, &e1, nullptr));
     } else {
       CHK(launch_vec_zero(PREC64, e1.d, nullptr, h, nrhs, Ns, st));
     }
@@ -445,46 +432,40 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   for (int q = 0; q < nrhs; q++) full_res[q] = -1.0;
   if (mode == ODWF_SOLVE_FULL) {
     // y_o = A^{-1}(b'_o - W_oe y_e)
-    CHK(launch_pack_spinor(PREC64, b, r0, o0.d, nullptr, 1, nrhs, Ns, g, st));
-    CHK(m5(c64, o0, o0, prog_omega_inv()));
+    CHK(pack(c64, b, r0, nullptr, &o0, prog_none(), prog_omega_inv()));
     HopOpt k;
     k.x = &o0;
     k.ch = -1.0;
     k.cx = 1.0;
     k.po = prog_ainv();
     CHK(hop(c64, 1, 0, e1, &o0, k));
-    // |b - D x| with D x = omega (A + W) y, parity by parity (e0 reused as scratch)
-    double nr[MAXRHS], nb2[MAXRHS];
-    for (int q = 0; q < nrhs; q++) nr[q] = nb2[q] = 0.0;
+    // |b - D x| with D x = omega (A + W) y, parity by parity (b in e2, e0): only
+    // its norm is formed
+    CHK(pack(c64, b, r0, &e2, &e0));
     for (int par = 0; par < 2; par++) {
+      const HV& bp = par == 0 ? e2 : e0;
+      CHK(launch_vec_norm2(PREC64, bp.d, nullptr, partial, h, nrhs, Ns, &nb_vec, st));
+      CHK(launch_fin(FIN_SUM, partial, nb_vec, nrhs, nullptr, dres + (2 + par) * MAXRHS, st));
       HopOpt kd;
       kd.px = prog_a();
       kd.po = prog_omega();
       kd.x = par == 0 ? &e1 : &o0;
-      CHK(hop(c64, par, 0, par == 0 ? o0 : e1, &e0, kd));
-      CHK(launch_pack_spinor(PREC64, b, r0, e2.d, nullptr, par, nrhs, Ns, g, st));
-      CHK(launch_vec_norm2(PREC64, e2.d, nullptr, partial, h, nrhs, Ns, &nb_vec, st));
-      CHK(launch_fin(FIN_SUM, partial, nb_vec, nrhs, nullptr, dres + 2 * MAXRHS, st));
-      CHK(m5(c64, e0, e0, prog_none(), -1.0, &e2, 1.0));
-      CHK(launch_vec_norm2(PREC64, e0.d, nullptr, partial, h, nrhs, Ns, &nb_vec, st));
-      CHK(launch_fin(FIN_SUM, partial, nb_vec, nrhs, nullptr, dres + MAXRHS, st));
-      double hr[4 * MAXRHS];
-      CHK(hipMemcpyAsync(hr, dres, sizeof(hr), hipMemcpyDeviceToHost, st));
-      CHK(hipStreamSynchronize(st));
-      for (int q = 0; q < nrhs; q++) {
-        nr[q] += hr[MAXRHS + q];
-        nb2[q] += hr[2 * MAXRHS + q];
-      }
+      kd.cg_p = &bp;
+      kd.partial = partial;
+      CHK(hop(c64, par, 0, par == 0 ? o0 : e1, nullptr, kd));
+      CHK(launch_fin(FIN_SUM, partial, nbh, nrhs, nullptr, dres + par * MAXRHS, st));
     }
-    for (int q = 0; q < nrhs; q++) full_res[q] = nb2[q] > 0 ? std::sqrt(nr[q] / nb2[q]) : 0.0;
     // x = (1 + L)^{-1} y
-    CHK(m5(c64, e1, e1, prog_1pl_inv()));
-    CHK(m5(c64, o0, o0, prog_1pl_inv()));
-    CHK(launch_unpack_spinor(PREC64, e1.d, nullptr, x, r0, 0, nrhs, Ns, g, st));
-    CHK(launch_unpack_spinor(PREC64, o0.d, nullptr, x, r0, 1, nrhs, Ns, g, st));
+    CHK(unpack(c64, &e1, &o0, x, r0, prog_1pl_inv()));
+    double hr[4 * MAXRHS];
+    CHK(hipMemcpyAsync(hr, dres, sizeof(hr), hipMemcpyDeviceToHost, st));
+    CHK(hipStreamSynchronize(st));
+    for (int q = 0; q < nrhs; q++) {
+      const double nr = hr[q] + hr[MAXRHS + q], nb2 = hr[2 * MAXRHS + q] + hr[3 * MAXRHS + q];
+      full_res[q] = nb2 > 0 ? std::sqrt(nr / nb2) : 0.0;
+    }
   } else if (!io.y_packed) {
-    CHK(launch_unpack_spinor(PREC64, e1.d, nullptr, x, r0, 0, nrhs, Ns, g, st));
-    CHK(launch_zero_canon_parity(x, r0, 1, nrhs, Ns, g, st));
+    CHK(unpack(c64, &e1, nullptr, x, r0, prog_none()));
   }
   CHK(hipStreamSynchronize(st));
   const double secs =

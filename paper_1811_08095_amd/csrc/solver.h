@@ -4,13 +4,11 @@
 
 namespace odwf {
 
-// D = omega (A + W)(1 + L) on full fields given as (even, odd) halves;
-// te/to are scratch halves.
-hipError_t apply_D(const OpCtx& c, const HV& ie, const HV& io, const HV& te, const HV& to,
-                   const HV& oe, const HV& oo);
-// D^dag = (1 + L)^dag (A^dag + W^dag) omega
-hipError_t apply_Ddag(const OpCtx& c, const HV& ie, const HV& io, const HV& te, const HV& to,
-                      const HV& oe, const HV& oo);
+// D = omega (A + W)(1 + L) from y = (1 + L) psi, given and returned as (even,
+// odd) halves; po: omega, or omega^2 for D^dag's input omega D psi
+hipError_t apply_D(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo, const M5Prog& po);
+// D^dag = (1 + L)^dag (A^dag + W^dag) omega from y = omega psi
+hipError_t apply_Ddag(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo);
 // S_e in (to: odd scratch)
 hipError_t apply_schur(const OpCtx& c, const HV& in, const HV& to, const HV& out);
 // S_e^dag in
