@@ -280,9 +280,7 @@ static hipError_t batch_iteration(odwf_batch B, hipStream_t st) {
                             Ns, st));
   // gated update: y += x_s, x_s = 0, r = f - N y (FP64), true |r|^2
   if (B->inner != PREC64) {
-    HIPRET(launch_vec_convert(B->inner, B->x.d, B->x.sc, PREC64, B->y.d, nullptr, 1, h, k, Ns, st,
-                              B->dscal, GATE_UPDATE));
-    HIPRET(launch_vec_zero(B->inner, B->x.d, B->x.sc, h, k, Ns, st, B->dscal, GATE_UPDATE));
+    HIPRET(launch_vec_flush(B->inner, B->x.d, B->x.sc, B->y.d, 1, h, k, Ns, st, B->dscal, GATE_UPDATE));
   }
   HopOpt kr;
   kr.partial = B->partial;

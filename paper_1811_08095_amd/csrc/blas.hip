@@ -22,23 +22,148 @@ int vec_nblocks(long h, int nrhs, int Ns) {
   return (int)nb;
 }
 
-template <class P>
-__global__ void vec_zero_kernel(void* v, float* sc, const CGScal* gate, int gate_mode, long h, int nrhs,
-                                int Ns) {
-  using R = typename P::real;
-  const int inner = nrhs * Ns;
-  const int spb = blockDim.x / inner;
-  const int sl = threadIdx.x / inner, lr = threadIdx.x % inner, r = lr / Ns, s = lr % Ns;
+// ---------------------------------------------------------------------------
+// streaming kernels over 16-byte chunks: where no value depends on its 5D site
+// as a whole (FP64 and FP32 storage have no scale) a thread takes UNROLL chunks
+// a block apart, so a wave's accesses are contiguous and a thread holds few
+// registers.  One lane per 5D site (12 chunks of FP64 a lane for each of x, p, r)
+// spilled 500 bytes a lane at the default bounds: the FP64 CG step of 32^3 x 16 x 16
+// took 1432 us (4.0 GB), the chunk form 660 us (6.1 TB/s).
+// grid.y is the right-hand side; its rows (one site's chunks) lie nrhs rows apart.
+// ---------------------------------------------------------------------------
+constexpr int UNROLL = 4;
+struct ChunkGeom {
+  long n;       // chunks of one right-hand side
+  FastDiv row;  // chunks of one site
+  int nrhs;
+  // chunk k of right-hand side r in the field
+  __device__ long at(long k, int r) const {
+    if (nrhs == 1) return k;
+    const long j = k < (1L << 31) ? (long)row.div((uint32_t)k) : k / row.d;
+    return k + (j * (nrhs - 1) + r) * row.d;
+  }
+};
+static ChunkGeom chunk_geom(int cpb, long h, int nrhs, int Ns) {
+  ChunkGeom g;
+  g.row = FastDiv((uint32_t)(12 / cpb * Ns));
+  g.n = h * (12 / cpb) * Ns;
+  g.nrhs = nrhs;
+  return g;
+}
+static dim3 chunk_grid(const ChunkGeom& g) { return dim3((unsigned)((g.n + 256 * UNROLL - 1) / (256 * UNROLL)), g.nrhs); }
+__device__ __forceinline__ long chunk_first() { return (long)blockIdx.x * 256 * UNROLL + threadIdx.x; }
+
+__global__ void __launch_bounds__(256) chunk_zero_kernel(uint4* v, const CGScal* gate, int gate_mode, ChunkGeom g) {
+  const int r = blockIdx.y;
   if (!gate_on(gate, gate_mode, r)) return;
-  cpx<R> z[12];
 #pragma unroll
-  for (int c = 0; c < 12; c++) z[c] = {R(0), R(0)};
-  for (long j = (long)blockIdx.x * spb + sl; j < h; j += (long)gridDim.x * spb)
-    store_site<P>(v, sc, j, r, s, nrhs, Ns, z);
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k < g.n) v[g.at(k, r)] = make_uint4(0, 0, 0, 0);
+  }
+}
+__global__ void __launch_bounds__(256) scale_zero_kernel(float* sc, const CGScal* gate, int gate_mode, long h, int nrhs,
+                                                         int Ns) {
+  const long k = (long)blockIdx.x * 256 + threadIdx.x;
+  if (k < h * nrhs * Ns && gate_on(gate, gate_mode, (int)(k / Ns % nrhs))) sc[k] = 0.f;
+}
+
+// FP64 <- FP32: dst = src or dst += src, and src = 0 behind it when clear
+__global__ void __launch_bounds__(256) chunk_32_to_64_kernel(uint4* src, uint4* dst, int accumulate, int clear,
+                                                             const CGScal* gate, int gate_mode, ChunkGeom g, int lg) {
+  const int r = blockIdx.y;
+  if (!gate_on(gate, gate_mode, r)) return;
+#pragma unroll 2
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k >= g.n) break;
+    // FP32 chunk (cg, s) of a site holds components 2 cg, 2 cg + 1: FP64 chunks (2 cg, s), (2 cg + 1, s)
+    const long at = g.at(k, r);
+    const long cg = at >> lg;  // row * 6 + chunk group; Ns = 2^lg
+    const long d0 = at + (cg << lg);
+    cpx<float> a[2];
+    unpack_chunk<SP32>(src[at], a);
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+      cpx<double> b = {(double)a[c].re, (double)a[c].im};
+      if (accumulate) {
+        cpx<double> o;
+        unpack_chunk<SP64>(dst[d0 + (c << lg)], &o);
+        b = cadd(o, b);
+      }
+      dst[d0 + (c << lg)] = pack_chunk<SP64>(&b, 1.0);
+    }
+    if (clear) src[at] = make_uint4(0, 0, 0, 0);
+  }
+}
+__global__ void __launch_bounds__(256) chunk_64_to_32_kernel(const uint4* src, uint4* dst, const CGScal* gate,
+                                                             int gate_mode, ChunkGeom g, int lg) {
+  const int r = blockIdx.y;
+  if (!gate_on(gate, gate_mode, r)) return;
+#pragma unroll
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k >= g.n) break;
+    const long at = g.at(k, r), s0 = at + (at >> lg << lg);
+    cpx<float> b[2];
+#pragma unroll
+    for (int c = 0; c < 2; c++) {
+      cpx<double> a;
+      unpack_chunk<SP64>(src[s0 + (c << lg)], &a);
+      b[c] = {(float)a.re, (float)a.im};
+    }
+    dst[at] = pack_chunk<SP32>(b, 1.0f);
+  }
+}
+__global__ void __launch_bounds__(256) chunk_copy_kernel(const uint4* src, uint4* dst, const CGScal* gate, int gate_mode,
+                                                         ChunkGeom g) {
+  const int r = blockIdx.y;
+  if (!gate_on(gate, gate_mode, r)) return;
+#pragma unroll
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k < g.n) dst[g.at(k, r)] = src[g.at(k, r)];
+  }
+}
+
+// the CG vector step of vec_cg_step_kernel for the unscaled formats
+template <class P>
+__global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uint4* p_, uint4* x_, const CGScal* scal,
+                                                            ChunkGeom g) {
+  using R = typename P::real;
+  constexpr int N = P::CPB;
+  const int r = blockIdx.y;
+  const bool act = scal[r].active != 0;
+  const double alpha = scal[r].alpha;
+  if (!act && alpha == 0.0) return;
+  const R al = (R)alpha, beta = (R)scal[r].beta;
+  cpx<R> p[UNROLL][N], x[UNROLL][N], rv[UNROLL][N];
+#pragma unroll
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k >= g.n) continue;
+    const long at = g.at(k, r);
+    unpack_chunk<P>(p_[at], p[u]);
+    if (alpha != 0.0) unpack_chunk<P>(x_[at], x[u]);
+    if (act) unpack_chunk<P>(r_[at], rv[u]);
+  }
+#pragma unroll
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k >= g.n) continue;
+    const long at = g.at(k, r);
+#pragma unroll
+    for (int c = 0; c < N; c++) {
+      if (alpha != 0.0) x[u][c] = cadd(x[u][c], cscale(al, p[u][c]));
+      if (act) p[u][c] = cadd(rv[u][c], cscale(beta, p[u][c]));
+    }
+    if (alpha != 0.0) x_[at] = pack_chunk<P>(x[u], R(1));
+    if (act) p_[at] = pack_chunk<P>(p[u], R(1));
+  }
 }
 
 template <class PS, class PD>
-__global__ void vec_convert_kernel(const void* src, const float* src_sc, void* dst, float* dst_sc,
+__global__ void __launch_bounds__(256) vec_convert_kernel(const void* src, const float* src_sc, void* dst, float* dst_sc,
                                    int accumulate, const CGScal* gate, int gate_mode, long h, int nrhs,
                                    int Ns) {
   using RS = typename PS::real;
@@ -63,12 +188,13 @@ __global__ void vec_convert_kernel(const void* src, const float* src_sc, void* d
   }
 }
 
-// CG vector step after the scalars of the iteration are known:
+// CG vector step after the scalars of the iteration are known (scaled formats;
+// the others take chunk_cg_step_kernel):
 //   x += alpha p   (for every right-hand side that iterated: alpha != 0, which
 //                   includes one that converged at this iteration's beta)
 //   p  = r + beta p (for the right-hand sides still active)
 template <class P>
-__global__ void vec_cg_step_kernel(const void* r_, const float* r_sc, void* p_, float* p_sc, void* x_,
+__global__ void __launch_bounds__(256) vec_cg_step_kernel(const void* r_, const float* r_sc, void* p_, float* p_sc, void* x_,
                                    float* x_sc, const CGScal* scal, long h, int nrhs, int Ns) {
   using R = typename P::real;
   const int inner = nrhs * Ns;
@@ -99,8 +225,8 @@ __global__ void vec_cg_step_kernel(const void* r_, const float* r_sc, void* p_, 
 }
 
 template <class P>
-__global__ void vec_norm2_kernel(const void* v, const float* sc, double* partial, long h, int nrhs,
-                                 int Ns) {
+__global__ void __launch_bounds__(256) vec_norm2_kernel(const void* v, const float* sc, double* partial, long h, int nrhs,
+                                                        int Ns) {
   using R = typename P::real;
   __shared__ double red[1024];
   const int inner = nrhs * Ns;
@@ -128,9 +254,11 @@ __global__ void vec_norm2_kernel(const void* v, const float* sc, double* partial
 
 hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st,
                            const CGScal* gate, int gate_mode) {
-  const int block = vec_spb(nrhs, Ns) * nrhs * Ns;
-  const dim3 gr(vec_nblocks(h, nrhs, Ns));
-  ODWF_PREC_SWITCH(prec, vec_zero_kernel, gr, dim3(block), 0, st, v, sc, gate, gate_mode, h, nrhs, Ns);
+  const ChunkGeom g = chunk_geom(prec == PREC64 ? 1 : prec == PREC32 ? 2 : 4, h, nrhs, Ns);
+  hipLaunchKernelGGL(chunk_zero_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(v), gate, gate_mode, g);
+  if (sc)
+    hipLaunchKernelGGL(scale_zero_kernel, dim3((unsigned)((h * nrhs * Ns + 255) / 256)), dim3(256), 0, st, sc, gate,
+                       gate_mode, h, nrhs, Ns);
   return hipGetLastError();
 }
 
@@ -142,7 +270,6 @@ static hipError_t convert_to(int prec_dst, const void* src, const float* src_sc,
   const dim3 gr(vec_nblocks(h, nrhs, Ns));
   switch (prec_dst) {
     case PREC64: hipLaunchKernelGGL((vec_convert_kernel<PS, SP64>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
-    case PREC32: hipLaunchKernelGGL((vec_convert_kernel<PS, SP32>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
     case PREC16: hipLaunchKernelGGL((vec_convert_kernel<PS, SP16>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
     case PRECB16: hipLaunchKernelGGL((vec_convert_kernel<PS, SPB16>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
     default: return hipErrorInvalidValue;
@@ -153,21 +280,55 @@ static hipError_t convert_to(int prec_dst, const void* src, const float* src_sc,
 hipError_t launch_vec_convert(int prec_src, const void* src, const float* src_sc, int prec_dst,
                               void* dst, float* dst_sc, int accumulate, long h, int nrhs, int Ns,
                               hipStream_t st, const CGScal* gate, int gate_mode) {
+  const uint4* s4 = reinterpret_cast<const uint4*>(src);
+  uint4* d4 = reinterpret_cast<uint4*>(dst);
+  if (prec_src == PREC64 && prec_dst == PREC32 && !accumulate) {
+    const ChunkGeom g = chunk_geom(2, h, nrhs, Ns);
+    hipLaunchKernelGGL(chunk_64_to_32_kernel, chunk_grid(g), dim3(256), 0, st, s4, d4, gate, gate_mode, g, __builtin_ctz(Ns));
+    return hipGetLastError();
+  }
+  if (prec_src == prec_dst && (prec_src == PREC64 || prec_src == PREC32) && !accumulate) {
+    const ChunkGeom g = chunk_geom(prec_src == PREC64 ? 1 : 2, h, nrhs, Ns);
+    hipLaunchKernelGGL(chunk_copy_kernel, chunk_grid(g), dim3(256), 0, st, s4, d4, gate, gate_mode, g);
+    return hipGetLastError();
+  }
   switch (prec_src) {
     case PREC64: return convert_to<SP64>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
-    case PREC32: return convert_to<SP32>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
     case PREC16: return convert_to<SP16>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
     case PRECB16: return convert_to<SPB16>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
   }
   return hipErrorInvalidValue;
 }
 
+hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, long h, int nrhs, int Ns,
+                            hipStream_t st, const CGScal* gate, int gate_mode) {
+  if (prec == PREC32) {
+    const ChunkGeom g = chunk_geom(2, h, nrhs, Ns);
+    hipLaunchKernelGGL(chunk_32_to_64_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(x),
+                       reinterpret_cast<uint4*>(y), 1, clear, gate, gate_mode, g, __builtin_ctz(Ns));
+    return hipGetLastError();
+  }
+  const hipError_t e =
+      launch_vec_convert(prec, x, x_sc, PREC64, y, nullptr, 1, h, nrhs, Ns, st, gate, gate_mode);
+  if (e != hipSuccess || !clear) return e;
+  return launch_vec_zero(prec, x, x_sc, h, nrhs, Ns, st, gate, gate_mode);
+}
+
 hipError_t launch_vec_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x,
                               float* x_sc, const CGScal* scal, long h, int nrhs, int Ns, hipStream_t st) {
+  if (prec == PREC64 || prec == PREC32) {
+    const ChunkGeom g = chunk_geom(prec == PREC64 ? 1 : 2, h, nrhs, Ns);
+    const uint4* r4 = reinterpret_cast<const uint4*>(r);
+    uint4 *p4 = reinterpret_cast<uint4*>(p), *x4 = reinterpret_cast<uint4*>(x);
+    if (prec == PREC64) hipLaunchKernelGGL(chunk_cg_step_kernel<SP64>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, scal, g);
+    else hipLaunchKernelGGL(chunk_cg_step_kernel<SP32>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, scal, g);
+    return hipGetLastError();
+  }
   const int block = vec_spb(nrhs, Ns) * nrhs * Ns;
   const dim3 gr(vec_nblocks(h, nrhs, Ns));
-  ODWF_PREC_SWITCH(prec, vec_cg_step_kernel, gr, dim3(block), 0, st, r, r_sc, p, p_sc, x, x_sc, scal, h, nrhs,
-                   Ns);
+  if (prec == PREC16) hipLaunchKernelGGL(vec_cg_step_kernel<SP16>, gr, dim3(block), 0, st, r, r_sc, p, p_sc, x, x_sc, scal, h, nrhs, Ns);
+  else if (prec == PRECB16) hipLaunchKernelGGL(vec_cg_step_kernel<SPB16>, gr, dim3(block), 0, st, r, r_sc, p, p_sc, x, x_sc, scal, h, nrhs, Ns);
+  else return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
@@ -184,7 +345,7 @@ hipError_t launch_vec_norm2(int prec, const void* v, const float* sc, double* pa
 // of an nrhs_dst field (same parity, any storage precisions); src == nullptr
 // writes zeros
 template <class PS, class PD>
-__global__ void vec_copy_rhs_kernel(const void* src, const float* src_sc, int nrhs_src, int r_src,
+__global__ void __launch_bounds__(256) vec_copy_rhs_kernel(const void* src, const float* src_sc, int nrhs_src, int r_src,
                                     void* dst, float* dst_sc, int nrhs_dst, int r_dst, long h, int Ns) {
   using RS = typename PS::real;
   using RD = typename PD::real;

@@ -54,10 +54,14 @@ hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, fl
 // gate / gate_mode (GateMode) restrict the work to selected right-hand sides
 hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st,
                            const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
-// dst = src (accumulate: dst += src), converting storage precision
+// dst = src (accumulate: dst += src), converting storage precision: between FP64 and a
+// scaled format, FP64 to FP32, or a copy
 hipError_t launch_vec_convert(int prec_src, const void* src, const float* src_sc, int prec_dst,
                               void* dst, float* dst_sc, int accumulate, long h, int nrhs, int Ns,
                               hipStream_t st, const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
+// y (FP64) += x, and x = 0 behind it when clear
+hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, long h, int nrhs, int Ns,
+                            hipStream_t st, const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
 // one right-hand side of a field into one right-hand side of another (zeros if src null)
 hipError_t launch_vec_copy_rhs(int prec_src, const void* src, const float* src_sc, int nrhs_src,
                                int r_src, int prec_dst, void* dst, float* dst_sc, int nrhs_dst,
