@@ -585,7 +585,7 @@ extern "C" odwf_status odwf_solver_reserve(odwf_solver S, int nrhs, odwf_prec in
   std::lock_guard<std::mutex> lk(S->mtx);
   SolveBufs B;
   const int n = std::min(nrhs, max_rhs_per_launch(S->Ns));
-  if (!solve_buffers(S->workspace(st), S->lat->g.h, n, S->Ns, (int)inner, B)) {
+  if (!solve_buffers(S->workspace(st), S->lat->g, n, S->Ns, (int)inner, B)) {
     set_error("odwf_solver_reserve: out of device memory");
     return ODWF_ENOMEM;
   }
@@ -596,8 +596,7 @@ extern "C" odwf_status odwf_footprint(const int dims[4], int Ns, int nrhs, odwf_
                                       size_t* bytes) {
   REQUIRE(dims && bytes, "odwf_footprint: null argument");
   REQUIRE(ns_supported(Ns) && nrhs >= 1, "odwf_footprint: bad Ns or nrhs");
-  const long h = (long)dims[0] * dims[1] * dims[2] * dims[3] / 2;
-  *bytes = solve_workspace_bytes(h, Ns, std::min(nrhs, max_rhs_per_launch(Ns)), (int)inner);
+  *bytes = solve_workspace_bytes(geom_of(dims), Ns, std::min(nrhs, max_rhs_per_launch(Ns)), (int)inner);
   return ODWF_OK;
 }
 

@@ -78,13 +78,14 @@ static void kappas(odwf_batch B, double* kap) {
 }
 
 // device bytes a batch engine allocates (the buffers of odwf_batch_create)
-static size_t batch_footprint_bytes(long h, int Ns, int k, int inner) {
+static size_t batch_footprint_bytes(const Geom& g, int Ns, int k, int inner) {
+  const long h = g.h;
   auto buf = [](size_t b) { return b ? b : size_t(16); };
   size_t t = 5 * buf(half_bytes(h, k, Ns, PREC64));  // f, y, e2, o0, bo
   const int ninner = inner == PREC64 ? 4 : 5;       // p, r, t, v (+ x)
   t += ninner * buf(half_bytes(h, k, Ns, inner));
   if (k > 1) t += 5 * buf(half_bytes(h, 1, Ns, PREC64));  // admission / retirement scratch
-  const int nb = std::max(hop_nblocks((int)h, k, Ns), vec_nblocks(h, k, Ns));
+  const int nb = std::max(hop_nblocks(g, k, Ns), vec_nblocks(h, k, Ns));
   t += partial_bytes(nb, k) + MAXRHS * sizeof(CGScal) + 4 * MAXRHS * sizeof(double);
   return t;
 }
@@ -96,8 +97,7 @@ extern "C" odwf_status odwf_batch_footprint(const int dims[4], int Ns, int max_s
   BREQ(max_slots >= 1 && max_slots <= max_rhs_per_launch(Ns), "odwf_batch_footprint: bad max_slots");
   BREQ(inner == ODWF_FP64 || inner == ODWF_FP32, "odwf_batch_footprint: inner must be FP64 or FP32");
   for (int d = 0; d < 4; d++) BREQ(dims[d] >= 2 && dims[d] % 2 == 0, "odwf_batch_footprint: bad extent");
-  const long h = (long)dims[0] * dims[1] * dims[2] * dims[3] / 2;
-  *bytes = batch_footprint_bytes(h, Ns, max_slots, (int)inner);
+  *bytes = batch_footprint_bytes(geom_of(dims), Ns, max_slots, (int)inner);
   return ODWF_OK;
 }
 
@@ -148,7 +148,7 @@ extern "C" odwf_status odwf_batch_create(odwf_solver S, int max_slots, odwf_prec
     B->s_o0 = W.half("s_o0", h, 1, Ns, PREC64);
     B->s_bo = W.half("s_bo", h, 1, Ns, PREC64);
   }
-  const int nb = std::max(hop_nblocks((int)h, k, Ns), vec_nblocks(h, k, Ns));
+  const int nb = std::max(hop_nblocks(S->lat->g, k, Ns), vec_nblocks(h, k, Ns));
   B->partial = (double*)W.get("partial", partial_bytes(nb, k));
   B->dscal = (CGScal*)W.get("scal", MAXRHS * sizeof(CGScal));
   B->dres = (double*)W.get("res", 4 * MAXRHS * sizeof(double));
@@ -268,7 +268,7 @@ static hipError_t batch_iteration(odwf_batch B, hipStream_t st) {
   kappas(B, kap);
   OpCtx cin = ctx_of(B, st, B->inner, k, kap);
   OpCtx c64 = ctx_of(B, st, PREC64, k, kap);
-  const int nbh = hop_nblocks((int)h, k, Ns);
+  const int nbh = hop_nblocks(S->lat->g, k, Ns);
   HV* xacc = B->inner == PREC64 ? &B->y : &B->x;
   HopOpt k4;
   k4.cg_r = &B->r;

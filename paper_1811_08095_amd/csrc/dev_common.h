@@ -207,46 +207,6 @@ __device__ __forceinline__ void load_site(const void* base, const float* scale, 
   }
 }
 
-// cached variant: for neighbour reads that other sites re-use
-template <class P>
-__device__ __forceinline__ void load_site_cached(const void* base, const float* scale, long j, int r,
-                                                 int s, int nrhs, int Ns,
-                                                 cpx<typename P::real> (&v)[12]) {
-  constexpr int NCG = 12 / P::CPB;
-  const uint4* b = reinterpret_cast<const uint4*>(base);
-  const long off = ((j * nrhs + r) * NCG) * Ns + s;
-  uint4 q[NCG];
-#pragma unroll
-  for (int cg = 0; cg < NCG; cg++) q[cg] = b[off + cg * Ns];
-#pragma unroll
-  for (int cg = 0; cg < NCG; cg++) unpack_chunk<P>(q[cg], &v[cg * P::CPB]);
-  if constexpr (P::SCALED) {
-    float sc = scale[(j * nrhs + r) * Ns + s];
-#pragma unroll
-    for (int c = 0; c < 12; c++) v[c] = cscale(sc, v[c]);
-  }
-}
-
-// cached neighbour read without the per-site scale applied: v holds the
-// stored values, *sc the site's scale (1 for unscaled formats), so that the
-// caller can apply the scale after its linear algebra on fewer numbers
-template <class P>
-__device__ __forceinline__ void load_site_cached_raw(const void* base, const float* scale, long j,
-                                                     int r, int s, int nrhs, int Ns,
-                                                     cpx<typename P::real> (&v)[12],
-                                                     typename P::real& sc) {
-  constexpr int NCG = 12 / P::CPB;
-  const uint4* b = reinterpret_cast<const uint4*>(base);
-  const long off = ((j * nrhs + r) * NCG) * Ns + s;
-  uint4 q[NCG];
-#pragma unroll
-  for (int cg = 0; cg < NCG; cg++) q[cg] = b[off + cg * Ns];
-#pragma unroll
-  for (int cg = 0; cg < NCG; cg++) unpack_chunk<P>(q[cg], &v[cg * P::CPB]);
-  if constexpr (P::SCALED) sc = scale[(j * nrhs + r) * Ns + s];
-  else sc = typename P::real(1);
-}
-
 // NT = 1: nontemporal stores (written once, not re-read by this launch)
 #ifndef ODWF_NT_STORE
 #define ODWF_NT_STORE 0
@@ -510,213 +470,26 @@ __device__ __forceinline__ void m5_run_lds(const M5Prog& prog, cpx<R>* col, int 
 }
 
 // ---------------------------------------------------------------------------
-// the same programs with the column spread over lanes: for N_s = 16 the 16
-// slices of one (site, right-hand side) are the 16 lanes of one DPP row, so
-// every lane keeps its own slice of all 12 components in registers and the
-// fifth-dimension couplings become cross-lane moves inside the row.  The
-// bidiagonal products need the neighbouring slice (a row rotation); the cyclic
-// bidiagonal solves are first-order linear recurrences x_u = a_u x_{u-1} + b_u,
-// solved by a log2(16)-step scan over the affine maps (a, b), closed around the
-// cycle with x_last = b_last / (1 - a_last) and one broadcast in the row.
-// FP32 arithmetic only; chirality + runs in slice order, chirality - in the
-// mirrored order (as in m5_run).
-// ---------------------------------------------------------------------------
-#ifndef ODWF_LANE_PASS
-#define ODWF_LANE_PASS 1
-#endif
-template <class R, int NS>
-struct LanePass {
-  static constexpr bool on = ODWF_LANE_PASS && sizeof(R) == 4 && NS == 16;
-};
-
-// DPP16 row controls: lane i reads lane i - n (SHR), i + n (SHL), (i - n) mod 16
-// (ROR) or lane n of its row (NEWBCAST, gfx90a and later)
-constexpr int DPP_SHL(int n) { return 0x100 + n; }
-constexpr int DPP_SHR(int n) { return 0x110 + n; }
-constexpr int DPP_ROR(int n) { return 0x120 + n; }
-constexpr int DPP_NEWBCAST(int n) { return 0x150 + n; }
-
-// value of v in the lane given by CTRL; lanes whose source lies outside the
-// row read 0 (bound_ctrl), so no register has to be preset with an old value
-template <int CTRL>
-__device__ __forceinline__ float row_move0(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-// the same with a chosen value `old` for lanes whose source lies outside the row
-template <int CTRL>
-__device__ __forceinline__ float row_move(float old, float v) {
-  return __int_as_float(
-      __builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(v), CTRL, 0xF, 0xF, false));
-}
-// value of v in lane 15 (LAST) or lane 0 of the lane's row: a DPP row
-// broadcast, no trip through the LDS crossbar
-template <bool LAST>
-__device__ __forceinline__ float row_bcast(float v) {
-  return row_move0<DPP_NEWBCAST(LAST ? 15 : 0)>(v);
-}
-
-// y[c0 .. c0+5] = d y + e y_nb, with y_nb the value of the neighbouring slice
-template <int CTRL>
-__device__ __forceinline__ void lane_mul(cpx<float> (&y)[12], int c0, float d, float e) {
-#pragma unroll
-  for (int c = c0; c < c0 + 6; c++) {
-    const float nr = row_move0<CTRL>(y[c].re), ni = row_move0<CTRL>(y[c].im);
-    y[c] = {d * y[c].re + e * nr, d * y[c].im + e * ni};
-  }
-}
-
-// y[c0 .. c0+5] <- solution of x_u = a x_{u-1} + b_u (b_u = y on entry) around
-// the cycle; DOWN: element u - 1 sits in the next lower lane (else the next
-// higher one); LAST: the final element in scan order sits in lane 15 (else 0)
-template <bool DOWN, bool LAST>
-__device__ __forceinline__ void lane_solve(cpx<float> (&y)[12], int c0, float a) {
-#pragma unroll
-  for (int k = 1; k < 16; k <<= 1) {
-    float pa;
-#pragma unroll
-    for (int c = c0; c < c0 + 6; c++) {
-      float pr, pi;
-      // lanes before the start of the scan read 0: their term vanishes
-      if (k == 1) {
-        pr = DOWN ? row_move0<DPP_SHR(1)>(y[c].re) : row_move0<DPP_SHL(1)>(y[c].re);
-        pi = DOWN ? row_move0<DPP_SHR(1)>(y[c].im) : row_move0<DPP_SHL(1)>(y[c].im);
-      } else if (k == 2) {
-        pr = DOWN ? row_move0<DPP_SHR(2)>(y[c].re) : row_move0<DPP_SHL(2)>(y[c].re);
-        pi = DOWN ? row_move0<DPP_SHR(2)>(y[c].im) : row_move0<DPP_SHL(2)>(y[c].im);
-      } else if (k == 4) {
-        pr = DOWN ? row_move0<DPP_SHR(4)>(y[c].re) : row_move0<DPP_SHL(4)>(y[c].re);
-        pi = DOWN ? row_move0<DPP_SHR(4)>(y[c].im) : row_move0<DPP_SHL(4)>(y[c].im);
-      } else {
-        pr = DOWN ? row_move0<DPP_SHR(8)>(y[c].re) : row_move0<DPP_SHL(8)>(y[c].re);
-        pi = DOWN ? row_move0<DPP_SHR(8)>(y[c].im) : row_move0<DPP_SHL(8)>(y[c].im);
-      }
-      y[c] = {y[c].re + a * pr, y[c].im + a * pi};
-    }
-    if (k == 1) pa = DOWN ? row_move<DPP_SHR(1)>(1.f, a) : row_move<DPP_SHL(1)>(1.f, a);
-    else if (k == 2) pa = DOWN ? row_move<DPP_SHR(2)>(1.f, a) : row_move<DPP_SHL(2)>(1.f, a);
-    else if (k == 4) pa = DOWN ? row_move<DPP_SHR(4)>(1.f, a) : row_move<DPP_SHL(4)>(1.f, a);
-    else pa = DOWN ? row_move<DPP_SHR(8)>(1.f, a) : row_move<DPP_SHL(8)>(1.f, a);
-    a *= pa;
-  }
-  // a is now the product of the step factors up to this lane; close the cycle
-  const float g = 1.f / (1.f - a);
-#pragma unroll
-  for (int c = c0; c < c0 + 6; c++) {
-    const float xr = row_bcast<LAST>(g * y[c].re), xi = row_bcast<LAST>(g * y[c].im);
-    y[c] = {y[c].re + a * xr, y[c].im + a * xi};
-  }
-}
-
-// the program loop unrolled over its four op slots (1, default), so the
-// coefficient reads of a step can be issued before the previous step ends
-#ifndef ODWF_M5_UNROLL
-#define ODWF_M5_UNROLL 1
-#endif
-template <int NS>
-__device__ __forceinline__ void m5_run_lanes(const M5Prog& prog, cpx<float> (&y)[12],
-                                             const float* __restrict__ cf, float kappa, int s) {
-  static_assert(NS == 16, "one DPP row per column");
-  const int up = s, um = NS - 1 - s;  // chirality-local slice index, chirality + and -
-  const float* cfm = cf + NCOEF * NS;
-#if ODWF_M5_UNROLL
-#pragma unroll
-  for (int k = 0; k < (int)(sizeof(prog.op) / sizeof(prog.op[0])); k++) {
-    if (k >= prog.n) break;
-#else
-  for (int k = 0; k < prog.n; k++) {
-#endif
-    const M5Op op = prog.op[k];
-    const float dp = cf[op.d * NS + up], dm = cfm[op.d * NS + um];
-    float ep = cf[op.e * NS + up], em = cfm[op.e * NS + um];
-    switch (op.type) {
-      case M5_SCALE: {
-#pragma unroll
-        for (int c = 0; c < 12; c++) y[c] = cscale(c < 6 ? dp : dm, y[c]);
-      } break;
-      case M5_MUL_LO: {  // local u - 1: lane s - 1 (chirality +), s + 1 (chirality -)
-        if (up == 0) ep *= kappa;
-        if (um == 0) em *= kappa;
-        lane_mul<DPP_ROR(1)>(y, 0, dp, ep);
-        lane_mul<DPP_ROR(15)>(y, 6, dm, em);
-      } break;
-      case M5_MUL_UP: {  // local u + 1: lane s + 1 (chirality +), s - 1 (chirality -)
-        if (up == NS - 1) ep *= kappa;
-        if (um == NS - 1) em *= kappa;
-        lane_mul<DPP_ROR(15)>(y, 0, dp, ep);
-        lane_mul<DPP_ROR(1)>(y, 6, dm, em);
-      } break;
-      case M5_SOLVE_LO: {  // x_u = d_u (y_u - e_u x_{u-1}), x_{-1} = x_{N-1} with e_0 -> kappa e_0
-        if (up == 0) ep *= kappa;
-        if (um == 0) em *= kappa;
-#pragma unroll
-        for (int c = 0; c < 12; c++) y[c] = cscale(c < 6 ? dp : dm, y[c]);
-        lane_solve<true, true>(y, 0, -dp * ep);    // chirality +: from lane s - 1, ends at lane 15
-        lane_solve<false, false>(y, 6, -dm * em);  // chirality -: from lane s + 1, ends at lane 0
-      } break;
-      case M5_SOLVE_UP: {  // x_u = d_u (y_u - e_u x_{u+1}), x_N = x_0 with e_{N-1} -> kappa e_{N-1}
-        if (up == NS - 1) ep *= kappa;
-        if (um == NS - 1) em *= kappa;
-#pragma unroll
-        for (int c = 0; c < 12; c++) y[c] = cscale(c < 6 ? dp : dm, y[c]);
-        lane_solve<false, false>(y, 0, -dp * ep);  // chirality +: from lane s + 1, ends at lane 0
-        lane_solve<true, true>(y, 6, -dm * em);    // chirality -: from lane s - 1, ends at lane 15
-      } break;
-      default: break;
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
 // dense programs on the matrix cores (N_s <= 16).  A wave holds 64 5D sites:
-// four sets of 16 slice slots (one column of N_s = 16 slices, or 16 / N_s
-// columns side by side with a block-diagonal matrix), 24 reals per lane.  The
-// lane order is
-//     lane = 16 q + 4 set + u,   slice slot S = 4 q + u,
-// so that a 4 x 4 transposition inside each quad of lanes (DPP quad_perm, two
-// selects per register) turns four registers into the B operand of
-// v_mfma_*_16x16x4: element (k = q, column (set, register)) of the slots
-// S = 4 k + kk, one kk per instruction, and the same transposition turns the
-// result back.  Every output column depends on its own input column only.
-// Replaces a serial recurrence through LDS columns (FP64) or a log-depth scan
-// over DPP rows (FP32): no LDS traffic for the data, no barrier.
+// four sets (lane / 16) of 16 slice slots (lane % 16; one column of N_s = 16
+// slices, or 16 / N_s columns side by side with a block-diagonal matrix), 24
+// reals per lane.  v_mfma_*_16x16x4 contracts over lane / 16, so the slots have
+// to move there: each wave passes its reals through LDS of its own (one b32 /
+// b64 write per real, the four slots of a lane's operand element back in one or
+// two b128 reads, rows padded so that neither side meets bank conflicts; LDS
+// operations of one wave are in order, so there is no barrier), takes the
+// data as the first operand (row = set and real, k = lane / 16 for the slots
+// 4 k .. 4 k + 3) and the transposed matrix as the second, and finds the result
+// in the lanes and registers it started from.  Every output row depends on its
+// own input row only.
+// Replaces a serial recurrence through LDS columns (FP64: 190-224 VGPRs, two
+// barriers per program) or a log-depth scan over DPP rows (FP32: 350 vector
+// instructions per program, now 70; 16-bit storage the same).  Fused launches,
+// before and after: FP64 32^3 x 16 x 16 1064 / 920 -> 755 / 784 us, 4^4 x 8
+// 21.8 / 18.6 -> 16.1 / 15.5 us; FP32 32^3 x 16 x 16 302 / 310 -> 303 / 302 us;
+// FP16S 24^4 x 16 167 / 157 -> 165 / 152 us (DPP quads for the transposition,
+// without LDS, took 172 / 157 us: 280 vector instructions per program).
 // ---------------------------------------------------------------------------
-// lane -> (index of its column among the wave's 64 / NS columns, slice)
-template <int NS>
-__device__ __forceinline__ void dense_lane(int lane, int& col, int& s) {
-  static_assert(NS <= DENSE_N, "");
-  const int slot = 4 * (lane >> 4) + (lane & 3);
-  col = ((lane >> 2) & 3) * (DENSE_N / NS) + slot / NS;
-  s = slot % NS;
-}
-
-template <int CTRL>
-__device__ __forceinline__ float quad_move(float v) {
-  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
-}
-template <int CTRL>
-__device__ __forceinline__ double quad_move(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xF, 0xF, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xF, 0xF, true);
-  return __hiloint2double(hi, lo);
-}
-// r_k(lane u of the quad) <- r_u(lane k)
-template <class R>
-__device__ __forceinline__ void quad_transpose(R (&r)[4], bool u0, bool u1) {
-  constexpr int X1 = 0xB1, X2 = 0x4E;  // quad_perm: lane ^ 1, lane ^ 2
-#pragma unroll
-  for (int k = 0; k < 4; k += 2) {
-    const R a = quad_move<X1>(r[k + 1]), b = quad_move<X1>(r[k]);
-    r[k] = u0 ? a : r[k];
-    r[k + 1] = u0 ? r[k + 1] : b;
-  }
-#pragma unroll
-  for (int k = 0; k < 2; k++) {
-    const R a = quad_move<X2>(r[k + 2]), b = quad_move<X2>(r[k]);
-    r[k] = u1 ? a : r[k];
-    r[k + 2] = u1 ? r[k + 2] : b;
-  }
-}
-
 typedef float mfma_f32x4 __attribute__((ext_vector_type(4)));
 typedef double mfma_f64x4 __attribute__((ext_vector_type(4)));
 template <class R>
@@ -724,8 +497,11 @@ struct Mfma;
 template <>
 struct Mfma<float> {
   using V = mfma_f32x4;
-  // row of the 16 x 16 result held by operand row i: D row 4 (lane / 16) + v
-  __device__ static __forceinline__ int row(int i) { return i; }
+  static constexpr int ROW = 20;           // scratch: reals between two rows of 16 slots
+  static constexpr int SET = 12 * ROW;     // reals between two sets
+  // register v of lane group g is result row 4 g + v: row = 4 set + real
+  __device__ static __forceinline__ int set_of(int row) { return row >> 2; }
+  __device__ static __forceinline__ int real_of(int row) { return row & 3; }
   __device__ static __forceinline__ V mul(float a, float b, V c) {
     return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
   }
@@ -733,75 +509,78 @@ struct Mfma<float> {
 template <>
 struct Mfma<double> {
   using V = mfma_f64x4;
-  // D row lane / 16 + 4 v: the matrix rows are permuted so that register v of
-  // lane group q holds slot 4 q + v as in FP32
-  __device__ static __forceinline__ int row(int i) { return 4 * (i & 3) + (i >> 2); }
+  static constexpr int ROW = 18;
+  static constexpr int SET = 12 * ROW + 24;
+  // register v of lane group g is result row 4 v + g: row = 4 real + set
+  __device__ static __forceinline__ int set_of(int row) { return row & 3; }
+  __device__ static __forceinline__ int real_of(int row) { return row >> 2; }
   __device__ static __forceinline__ V mul(double a, double b, V c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
   }
 };
+// reals of LDS scratch per wave
+template <class R>
+constexpr int DENSE_SCRATCH = 4 * Mfma<R>::SET;
 
-// LDS image of a program: [chirality][16 x 16] of M0 + rho u w^T, followed,
-// where the launch's right-hand sides have different masses, by the rank-1
-// matrices u w^T (the per-column rho is then applied to their product).
-template <class R, int NS>
-__device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab, double rho_p, double rho_m,
-                                            bool mixed) {
-  constexpr int NN = DENSE_N * DENSE_N;
-  for (int i = threadIdx.x; i < 2 * NN; i += blockDim.x) {
-    const int chi = i / NN, e = i % NN;
-    const double* t = tab + chi * DENSE_CHI;
-    const int row = e / DENSE_N, cl = e % DENSE_N;
-    const double uw = row / NS == cl / NS ? t[NN + row] * t[NN + DENSE_N + cl] : 0.0;  // block-diagonal
-    m[i] = (R)(mixed ? t[e] : fma(chi ? rho_m : rho_p, uw, t[e]));
-    if (mixed) m[2 * NN + i] = (R)uw;
-  }
+// LDS image of a program: its table (M0, u, w per chirality) in the arithmetic
+// type.  Nothing in it depends on the mass, so one image serves every
+// right-hand side of a launch.
+template <class R>
+__device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab) {
+  for (int i = threadIdx.x; i < DENSE_LEN; i += blockDim.x) m[i] = (R)tab[i];
 }
 
-// y <- M y for the 12 components of every lane's 5D site; m: LDS image,
-// rho_p / rho_m: the column's rho per chirality (mixed masses only).  Called
-// by whole waves: the matrix instructions ignore the lane mask.
-template <class R>
-__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, bool mixed, R rho_p, R rho_m) {
+// y <- M y for the 12 components of every lane's 5D site; m: LDS image; scr:
+// DENSE_SCRATCH reals of this wave (16-byte aligned); rho_p / rho_m: rho of the
+// lane's right-hand side per chirality.  The rank-1 term rho u w^T rides on a
+// fifth matrix instruction: lane group k contributes rho times its part of
+// w . x (slots 4 k .. 4 k + 3) as element k of the operand row, and u in every
+// row of the second operand sums the parts.  Right-hand sides of any masses
+// share the instruction, and each one's result is the same bits whatever the
+// others are.  Called by whole waves: the matrix instructions ignore the lane
+// mask.
+template <int NS, class R>
+__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m) {
   using M = Mfma<R>;
   using V = typename M::V;
-  const int lane = threadIdx.x & 63;
-  const bool u0 = lane & 1, u1 = lane & 2;
-  const int base = M::row(lane & 15) * DENSE_N + 4 * (lane >> 4);
+  constexpr int NN = DENSE_N * DENSE_N;
+  const int lane = threadIdx.x & 63, slot = lane & 15, k = lane >> 4;
+  R* put = scr + k * M::SET + slot;
+  const int set_i = M::set_of(slot);
+  const R* get = scr + set_i * M::SET + M::real_of(slot) * M::ROW + 4 * k;
+  const int src = 16 * set_i + 4 * k;  // a lane of the operand element's column
+  const R rho[2] = {__shfl(rho_p, src, 64), __shfl(rho_m, src, 64)};
+  const bool same = slot / NS == 4 * k / NS;  // result slot and operand slots belong to one column
 #pragma unroll
   for (int chi = 0; chi < 2; chi++) {
-    const R* mc = m + chi * DENSE_N * DENSE_N + base;
-    R a[4], b[4];
+    const R* mc = m + chi * DENSE_CHI;
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int k = 0; k < 4; k++) a[k] = mc[k];
-    if (mixed) {
-#pragma unroll
-      for (int k = 0; k < 4; k++) b[k] = mc[2 * DENSE_N * DENSE_N + k];
+    for (int c = 0; c < 6; c++) {
+      put[(2 * c) * M::ROW] = y[6 * chi + c].re;
+      put[(2 * c + 1) * M::ROW] = y[6 * chi + c].im;
     }
-    const R rho = chi ? rho_m : rho_p;
+    __builtin_amdgcn_wave_barrier();
+    R b[4], w[4];
 #pragma unroll
-    for (int c = 6 * chi; c < 6 * chi + 6; c += 2) {
-      R x[4] = {y[c].re, y[c].im, y[c + 1].re, y[c + 1].im};
-      quad_transpose(x, u0, u1);
+    for (int e = 0; e < 4; e++) b[e] = mc[slot * DENSE_N + 4 * k + e];
+#pragma unroll
+    for (int e = 0; e < 4; e++) w[e] = mc[NN + DENSE_N + 4 * k + e];
+    const R u = same ? mc[NN + slot] : R(0);
+#pragma unroll
+    for (int g = 0; g < 3; g++) {
+      R x[4];
+#pragma unroll
+      for (int e = 0; e < 4; e++) x[e] = get[4 * g * M::ROW + e];
       V d = {R(0), R(0), R(0), R(0)};
 #pragma unroll
-      for (int k = 0; k < 4; k++) d = M::mul(a[k], x[k], d);
-      R o[4] = {d[0], d[1], d[2], d[3]};
-      if (mixed) {
-        V d1 = {R(0), R(0), R(0), R(0)};
+      for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
+      R t = w[0] * x[0];
 #pragma unroll
-        for (int k = 0; k < 4; k++) d1 = M::mul(b[k], x[k], d1);
-#pragma unroll
-        for (int k = 0; k < 4; k++) x[k] = d1[k];
-        quad_transpose(x, u0, u1);
-      }
-      quad_transpose(o, u0, u1);
-      if (mixed) {  // rho belongs to the column: after the transposition a lane is one column again
-#pragma unroll
-        for (int k = 0; k < 4; k++) o[k] = fma(rho, x[k], o[k]);
-      }
-      y[c] = {o[0], o[1]};
-      y[c + 1] = {o[2], o[3]};
+      for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
+      d = M::mul(rho[chi] * t, u, d);
+      y[6 * chi + 2 * g] = {d[0], d[1]};
+      y[6 * chi + 2 * g + 1] = {d[2], d[3]};
     }
   }
 }
@@ -848,14 +627,14 @@ __device__ __forceinline__ void column_pass_lds(cpx<R>* buf, int nsb, int nrhs, 
 
 // ---------------------------------------------------------------------------
 // deterministic per-right-hand-side block reduction of one double per lane.
-// Lanes are laid out (site slot sl, right-hand side r, slice s) with s fastest,
-// tid = (sl * nrhs + r) * Ns + s (Ns a power of two dividing 64, so the Ns
-// lanes of one (site, r) lie in one wave).  Those Ns lanes add their values by
-// a fixed xor butterfly of cross-lane moves (no LDS traffic; every lane ends
-// with the same bits, each pairwise addition being commutative); lane s = 0
-// puts the sum in tmp[sl * nrhs + r]; one lane per right-hand side then adds
-// the nsl site sums in site order and writes partial[slot * nrhs + r].
-// All threads of the block call it; padded threads (g >= nsl * nrhs) pass 0.
+// A lane's column is col = site slot * nrhs + right-hand side, its slice s; the
+// Ns lanes of a column are consecutive in one wave (Ns a power of two).  They
+// add their values by a fixed xor butterfly of cross-lane moves (no LDS
+// traffic; every lane ends with the same bits, each pairwise addition being
+// commutative); lane s = 0 puts the sum in tmp[col]; one lane per right-hand
+// side then adds the nsl site sums in site order and writes
+// partial[slot * nrhs + r].
+// All threads of the block call it; padded threads (col >= nsl * nrhs) pass 0.
 // tmp: LDS of at least nsl * nrhs doubles.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void block_reduce_rhs(double v, int Ns, int nsl, int nrhs, double* tmp,

@@ -12,9 +12,20 @@ struct Geom {
   long V, h;
 };
 
+inline Geom geom_of(const int dims[4]) {
+  Geom g;
+  for (int d = 0; d < 4; d++) g.L[d] = dims[d];
+  g.V = (long)dims[0] * dims[1] * dims[2] * dims[3];
+  g.h = g.V / 2;
+  return g;
+}
+
 // hopping kernel (hop.hip)
 hipError_t launch_hop(const HopArgs& a, int prec, int Ns, hipStream_t st);
-int hop_nblocks(int h, int nrhs, int Ns);
+// blocks of a fused launch (one partial sum per block and right-hand side), and
+// sites per block of a launch
+int hop_nblocks(const Geom& g, int nrhs, int Ns);
+int hop_launch_spb(int hx, int nrhs, int Ns, int prec, bool plain);
 
 // layouts (pack.hip)
 // canonical complex128 [rhs][s][t][z][y][x][4][3] (rhs offset r0, nrhs of them)
@@ -25,7 +36,7 @@ int hop_nblocks(int h, int nrhs, int Ns);
 struct HalfIO {
   void* d = nullptr;
   float* sc = nullptr;
-  DenseArg dn = {nullptr, 0, {}};
+  DenseArg dn = {nullptr, {}};
   const double* diag = nullptr;  // [2 chiralities, NCOEF * Ns apart][Ns], chirality - mirrored
 };
 hipError_t launch_pack(int prec, const void* canon, int r0, const HalfIO& e, const HalfIO& o, int nrhs, int Ns,

@@ -61,20 +61,20 @@ __global__ void __launch_bounds__(256) m5_dense_kernel(const void* in, const flo
                                                        double c1, const DenseArg dn, const double* diag, long ncol,
                                                        int nrhs) {
   using R = typename P::real;
-  __shared__ R mat[4 * DENSE_N * DENSE_N];
-  int col, s;
-  dense_lane<NS>(threadIdx.x & 63, col, s);
-  const long j = ((long)blockIdx.x * 4 + (threadIdx.x >> 6)) * (64 / NS) + col;
+  __shared__ __align__(16) R mat[DENSE_LEN];
+  __shared__ __align__(16) R scr[4 * DENSE_SCRATCH<R>];
+  const int s = threadIdx.x % NS;
+  const long j = (long)blockIdx.x * (256 / NS) + threadIdx.x / NS;
   const bool valid = j < ncol;
   cpx<R> v[12];
 #pragma unroll
   for (int c = 0; c < 12; c++) v[c] = {R(0), R(0)};
   if (valid) load_site<P>(in, in_sc, j, 0, s, 1, NS, v);
   if (dn.tab) {
-    const int r = dn.mixed ? (int)(j % nrhs) : 0;
-    dense_stage<R, NS>(mat, dn.tab, dn.rho[0], dn.rho[MAXRHS], dn.mixed);
+    const int r = nrhs > 1 ? (int)(j % nrhs) : 0;
+    dense_stage<R>(mat, dn.tab);
     __syncthreads();
-    dense_apply<R>(v, mat, dn.mixed, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
+    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
   }
   if (!valid) return;
   if (diag) {
@@ -105,8 +105,9 @@ static hipError_t launch_m5_t(const void* in, const float* in_sc, void* out, flo
     // a program is dense, diagonal (one scaling) or absent
     if (!dn.tab && !diag && prog.n > 0) return hipErrorInvalidValue;
     const long ncol = h * nrhs;
-    hipLaunchKernelGGL((m5_dense_kernel<P, NS>), dim3((unsigned)((ncol * NS + 255) / 256)), dim3(256), 0, st, in, in_sc,
-                       out, out_sc, other, other_sc, c0, c1, dn, diag, ncol, nrhs);
+    const dim3 grid((unsigned)((ncol * NS + 255) / 256));
+    hipLaunchKernelGGL((m5_dense_kernel<P, NS>), grid, dim3(256), 0, st, in, in_sc, out, out_sc, other, other_sc, c0, c1,
+                       dn, diag, ncol, nrhs);
     return hipGetLastError();
   } else {
   const int spb = 256 / inner;

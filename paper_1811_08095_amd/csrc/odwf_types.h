@@ -104,11 +104,10 @@ struct KappaArr {
   double v[MAXRHS];  // per right-hand side: -mu_r
 };
 
-// a dense program of a launch: table (null: none), rho per chirality and
-// right-hand side, and whether the right-hand sides' rho differ
+// a dense program of a launch: table (null: none) and rho per chirality and
+// right-hand side
 struct DenseArg {
   const double* tab;
-  int mixed;
   double rho[2 * MAXRHS];
 };
 
@@ -149,11 +148,16 @@ struct HopArgs {
   double* partial;      // per block, per right-hand side
   const void* coef;     // [2][NCOEF][Ns], compute precision
   double kappa[MAXRHS]; // per right-hand side: -mu_r
-  M5Prog prog_h;        // applied to the hopping result
-  M5Prog prog_x;        // applied to the x term
-  M5Prog prog_o;        // applied to the combination
+  // fifth-dimension programs on the hopping result (h), the x term (x) and the
+  // combination (o): N_s <= 16 takes the dense forms (o may be a scaling,
+  // diag_o), N_s = 32 the factored ones
+  DenseArg dn_h, dn_x, dn_o;
+  const double* diag_o;
+  M5Prog prog_h, prog_x, prog_o;
   double c_h, c_x;      // combination c_h * prog_h(W in) + c_x * prog_x(x)
   int h, nrhs, spb, out_par, bc_t, dag;
+  int plain;  // the hop alone: no program, x term, factor or partial sums
+  int rows;   // every block is a segment of one x-row
   int L[4];
   int nblocks;
   // block traversal: xcd != 0 gives each of the 8 XCDs a contiguous range of
@@ -165,6 +169,10 @@ struct HopArgs {
   // walking all tiles before the next chunk starts
   int xcd, tile_y, tile_z, tile_t, tile_x;
   int xcd_gy;  // xcd = 2: tiles of a lockstep group along y (1, 2, 4 or 8)
+  // divisors of the index arithmetic, set with the launch geometry: L_x / 2, L_y,
+  // L_z; of the tiled walk: segments and rows of a tile, t slices, blocks of a
+  // tile, and tiles (xcd = 2: groups of tiles) along y, z and x
+  FastDiv d_hx, d_y, d_z, d_tx, d_ty, d_tz, d_tl, d_per, d_ny, d_nz, d_nx;
   // gating: lanes of right-hand sides not selected by gate_mode do no work
   const CGScal* gate;
   int gate_mode;

@@ -83,19 +83,6 @@ __device__ __forceinline__ void site_of(const TileArgs& a, uint32_t k, uint32_t&
   }
 }
 
-// site of the tile and slice of this lane on the half side
-template <int NS>
-__device__ __forceinline__ void tile_lane(int& site, int& s) {
-  if constexpr (NS <= DENSE_N) {
-    int col;
-    dense_lane<NS>(threadIdx.x & 63, col, s);
-    site = (threadIdx.x >> 6) * (64 / NS) + col;
-  } else {
-    site = threadIdx.x / NS;
-    s = threadIdx.x % NS;
-  }
-}
-
 template <int NS, class R>
 __device__ __forceinline__ void diag_apply(cpx<R> (&v)[12], const double* diag, int s) {
   const R p = (R)diag[s], m = (R)diag[NCOEF * NS + NS - 1 - s];
@@ -103,15 +90,16 @@ __device__ __forceinline__ void diag_apply(cpx<R> (&v)[12], const double* diag, 
   for (int c = 0; c < 12; c++) v[c] = cscale(c < 6 ? p : m, v[c]);
 }
 
-// the operators of the lane's parity; every lane calls it
+// the operators of the lane's parity; every lane calls it.  scr: the wave's own
+// sites of the tile, which hold nothing while their values are in registers
 template <int NS, class R>
-__device__ __forceinline__ void tile_program(cpx<R> (&v)[12], const TileArgs& a, int par, int s, const R* mat) {
+__device__ __forceinline__ void tile_program(cpx<R> (&v)[12], const TileArgs& a, int r, int par, int s, const R* mat, R* scr) {
   if constexpr (NS <= DENSE_N) {
     if (a.dn.tab) {
       cpx<R> w[12];
 #pragma unroll
       for (int c = 0; c < 12; c++) w[c] = v[c];
-      dense_apply<R>(w, mat, false, R(0), R(0));
+      dense_apply<NS>(w, mat, scr, (R)a.dn.rho[r], (R)a.dn.rho[MAXRHS + r]);
       const bool on = (a.dn_on >> par) & 1;
 #pragma unroll
       for (int c = 0; c < 12; c++) {
@@ -125,9 +113,9 @@ __device__ __forceinline__ void tile_program(cpx<R> (&v)[12], const TileArgs& a,
 }
 
 template <int NS, class R>
-__device__ __forceinline__ void tile_stage(const TileArgs& a, int r, R* mat) {
+__device__ __forceinline__ void tile_stage(const TileArgs& a, R* mat) {
   if constexpr (NS <= DENSE_N)
-    if (a.dn.tab) dense_stage<R, NS>(mat, a.dn.tab, a.dn.rho[r], a.dn.rho[MAXRHS + r], false);
+    if (a.dn.tab) dense_stage<R>(mat, a.dn.tab);
 }
 
 template <int NS>
@@ -135,6 +123,7 @@ struct TileLds {
   static constexpr int COL = NS + 1;  // padded column
   static constexpr int N = Tile<NS>::TS * 12 * COL;
 };
+static_assert(DENSE_SCRATCH<double> <= TileLds<16>::N && DENSE_SCRATCH<float> <= TileLds<16>::N, "a wave's half tile");
 
 typedef double dbl2 __attribute__((ext_vector_type(2)));
 
@@ -164,21 +153,21 @@ __global__ void __launch_bounds__(Tile<NS>::T, 3) pack_tile_kernel(const double2
     }
     q[k] = __builtin_nontemporal_load(src + ((long)sl * a.V + i) * 12 + rem % 12);
   }
-  tile_stage<NS, R>(a, r, mat);
+  tile_stage<NS, R>(a, mat);
 #pragma unroll
   for (int k = 0; k < 12; k++) {
     const int e = tid + k * T, sl = e / (TS * 12), rem = e % (TS * 12);
     buf[rem * COL + sl] = {(R)q[k].x, (R)q[k].y};
   }
-  int site, s, par;
+  const int site = tid / NS, s = tid % NS;
+  int par;
   uint32_t i, j;
-  tile_lane<NS>(site, s);
   site_of(a, k0 + min(site, n - 1), i, j, par);
   __syncthreads();
   cpx<R> v[12];
 #pragma unroll
   for (int c = 0; c < 12; c++) v[c] = buf[(site * 12 + c) * COL + s];
-  tile_program<NS, R>(v, a, par, s, mat);
+  tile_program<NS, R>(v, a, r, par, s, mat, reinterpret_cast<R*>(buf + (tid >> 6) * (TileLds<NS>::N / 2)));
   if (site < n)
     store_site<P>(par ? a.d[1] : a.d[0], par ? a.sc[1] : a.sc[0], j, r, s, a.nrhs, NS, v);
 }
@@ -193,18 +182,18 @@ __global__ void __launch_bounds__(Tile<NS>::T, 3) unpack_tile_kernel(double2* __
   const int r = blockIdx.y, tid = threadIdx.x;
   const uint32_t i0 = blockIdx.x * TS;
   const int n = (int)min((long)TS, a.V - (long)i0);
-  int site, s, par;
+  const int site = tid / NS, s = tid % NS;
+  int par;
   uint32_t i, j;
-  tile_lane<NS>(site, s);
   site_of(a, i0 + min(site, n - 1), i, j, par);
   const void* half = par ? a.d[1] : a.d[0];
   cpx<R> v[12];
 #pragma unroll
   for (int c = 0; c < 12; c++) v[c] = {R(0), R(0)};
   if (half) load_site<P>(half, par ? a.sc[1] : a.sc[0], j, r, s, a.nrhs, NS, v);
-  tile_stage<NS, R>(a, r, mat);
+  tile_stage<NS, R>(a, mat);
   __syncthreads();
-  tile_program<NS, R>(v, a, par, s, mat);
+  tile_program<NS, R>(v, a, r, par, s, mat, reinterpret_cast<R*>(buf + (tid >> 6) * (TileLds<NS>::N / 2)));
 #pragma unroll
   for (int c = 0; c < 12; c++) buf[(site * 12 + c) * COL + s] = v[c];
   __syncthreads();
@@ -317,7 +306,7 @@ static hipError_t launch_tile(bool pack, void* canon, const TileArgs& a, hipStre
   using R = typename P::real;
   constexpr int TS = Tile<NS>::TS;
   if (a.dn.tab && NS > DENSE_N) return hipErrorInvalidValue;
-  const size_t sm = TileLds<NS>::N * sizeof(cpx<R>) + (a.dn.tab ? 2 * DENSE_N * DENSE_N * sizeof(R) : 0);
+  const size_t sm = TileLds<NS>::N * sizeof(cpx<R>) + (a.dn.tab ? DENSE_LEN * sizeof(R) : 0);
   const dim3 grid((unsigned)((a.n + TS - 1) / TS), a.nrhs);
   double2* c = reinterpret_cast<double2*>(canon);
   if (pack) hipLaunchKernelGGL((pack_tile_kernel<P, NS>), grid, dim3(Tile<NS>::T), sm, st, c, a);

@@ -197,10 +197,8 @@ DenseArg dense_arg(const OpCtx& c, const M5Prog& p) {
   if (!dense_ns(c.Ns()) || p.n == 0 || p.dense < 0) return d;
   d.tab = c.S->dense + (size_t)p.dense * DENSE_LEN;
   for (int chi = 0; chi < 2; chi++)
-    for (int r = 0; r < c.nrhs; r++) {
+    for (int r = 0; r < c.nrhs; r++)
       d.rho[chi * MAXRHS + r] = c.kappa[r] / (1.0 + c.kappa[r] * c.S->dense_q[p.dense][chi]);
-      if (c.kappa[r] != c.kappa[0]) d.mixed = 1;
-    }
   return d;
 }
 
@@ -224,9 +222,8 @@ static size_t site_bytes(int prec) {
 // ODWF_TRAVERSAL ("linear", "xcd", "Ty,Tz", "Ty,Tz,Tt" or "Ty,Tz,Tt,Tx"; Tx = 0
 // is the whole row) and ODWF_XCD ("contiguous", "lockstep" or "lockstep:Gy",
 // Gy the tiles of a group along y) override for tuning.
-static void traversal(HopArgs& a, int Ns) {
-  const int inner = a.nrhs * Ns;
-  const int spb = 256 / inner;
+static void traversal(HopArgs& a) {
+  const int spb = a.spb;
   const int hx = a.L[0] / 2;
   a.xcd = 1;
   a.tile_y = a.tile_z = a.tile_t = a.tile_x = 0;
@@ -301,7 +298,35 @@ hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out
   a.bc_t = L->bc_t;
   a.dag = dag;
   for (int d = 0; d < 4; d++) a.L[d] = L->g.L[d];
-  traversal(a, c.S->Ns);
+  a.dn_h = dense_arg(c, o.ph);
+  a.dn_x = dense_arg(c, o.px);
+  a.dn_o = dense_arg(c, o.po);
+  a.diag_o = diag_of(c, o.po);
+  // N_s <= 16 has kernels for dense programs, and for scalings of the result
+  if (dense_ns(c.Ns()) && ((o.ph.n > 0 && !a.dn_h.tab) || (o.px.n > 0 && !a.dn_x.tab) ||
+                           (o.po.n > 0 && !a.dn_o.tab && !a.diag_o)))
+    return hipErrorInvalidValue;
+  const int hx = a.L[0] / 2;
+  a.plain = o.ph.n == 0 && o.po.n == 0 && !o.x && !o.partial && o.ch == 1.0;
+  a.spb = hop_launch_spb(hx, c.nrhs, c.Ns(), c.prec, a.plain);
+  a.nblocks = (a.h + a.spb - 1) / a.spb;
+  a.rows = hx % a.spb == 0 && a.L[0] <= 256;
+  traversal(a);
+  a.d_hx = FastDiv(hx);
+  a.d_y = FastDiv(a.L[1]);
+  a.d_z = FastDiv(a.L[2]);
+  if (a.tile_y > 0) {
+    const int nseg = hx / a.spb, tx = a.tile_x > 0 ? a.tile_x : nseg, tl = a.tile_t > 0 ? a.tile_t : a.L[3];
+    const int gy = a.xcd == 2 ? a.xcd_gy : 1, gz = a.xcd == 2 ? 8 / a.xcd_gy : 1;
+    a.d_tx = FastDiv(tx);
+    a.d_ty = FastDiv(a.tile_y);
+    a.d_tz = FastDiv(a.tile_z);
+    a.d_tl = FastDiv(tl);
+    a.d_per = FastDiv(tx * a.tile_y * a.tile_z * tl);
+    a.d_ny = FastDiv(a.L[1] / a.tile_y / gy);
+    a.d_nz = FastDiv(a.L[2] / a.tile_z / gz);
+    a.d_nx = FastDiv(nseg / tx);
+  }
   // launches gated to the active right-hand sides of a batch are counted with
   // the bytes of all nrhs (exact while every slot is active); launches gated to
   // pending reliable updates mostly exit at once and are not counted

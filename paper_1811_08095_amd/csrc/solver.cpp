@@ -86,7 +86,7 @@ hipError_t apply_normal(const OpCtx& c, const HV& p, const HV& t, const HV& v, c
   k2.gate_mode = gate_mode;
   HIPRET(hop(c, 0, 0, t, &v, k2));
   if (partial_u && k4opt && k4opt->scal && k4opt->cg_r)
-    HIPRET(launch_fin(FIN_ALPHA, partial_u, hop_nblocks((int)c.h(), c.nrhs, c.Ns()), c.nrhs,
+    HIPRET(launch_fin(FIN_ALPHA, partial_u, hop_nblocks(c.S->lat->g, c.nrhs, c.Ns()), c.nrhs,
                       const_cast<CGScal*>(k4opt->scal), nullptr, c.st));
   HopOpt k3;
   k3.ph = prog_ainv_t();
@@ -144,24 +144,26 @@ static hipError_t read_scal(const CGScal* d, CGScal* h, int nrhs, hipStream_t st
   return hipStreamSynchronize(st);
 }
 
-size_t solve_workspace_bytes(long h, int Ns, int nrhs, int inner) {
+size_t solve_workspace_bytes(const Geom& g, int Ns, int nrhs, int inner) {
+  const long h = g.h;
   size_t b = 4 * half_bytes(h, nrhs, Ns, PREC64);  // f, y, two FP64 temporaries
   if (inner == PREC64) {
     b += 2 * half_bytes(h, nrhs, Ns, PREC64);  // r, p
   } else {
     b += 5 * (half_bytes(h, nrhs, Ns, inner) + scale_bytes(h, nrhs, Ns, inner));
   }
-  const int nb = std::max(hop_nblocks((int)h, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
+  const int nb = std::max(hop_nblocks(g, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
   b += partial_bytes(nb, nrhs) + 64 * 1024;
   return b;
 }
 
-bool solve_buffers(Workspace& W, long h, int nrhs, int Ns, int inner, SolveBufs& B, bool own_y) {
+bool solve_buffers(Workspace& W, const Geom& g, int nrhs, int Ns, int inner, SolveBufs& B, bool own_y) {
+  const long h = g.h;
   B.e0 = W.half("s.e0", h, nrhs, Ns, PREC64);  // f
   if (own_y) B.e1 = W.half("s.e1", h, nrhs, Ns, PREC64);  // y (else the caller's packed field)
   B.e2 = W.half("s.e2", h, nrhs, Ns, PREC64);  // FP64 even scratch / residual
   B.o0 = W.half("s.o0", h, nrhs, Ns, PREC64);  // FP64 odd scratch
-  const int nbmax = std::max(hop_nblocks((int)h, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
+  const int nbmax = std::max(hop_nblocks(g, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
   B.partial = (double*)W.get("s.partial", partial_bytes(nbmax, nrhs));
   B.scal = (CGScal*)W.get("s.scal", 2 * MAXRHS * sizeof(CGScal));
   B.res = (double*)W.get("s.res", 4 * MAXRHS * sizeof(double));
@@ -187,7 +189,7 @@ static hipError_t true_residual(const OpCtx& c64, const HV& f, const HV& y, cons
   k4.partial = partial;
   k4.cg_p = &f;
   HIPRET(apply_normal(c64, y, t, v, v, nullptr, &k4));
-  return launch_fin(FIN_INIT, partial, hop_nblocks((int)c64.h(), c64.nrhs, c64.Ns()), c64.nrhs,
+  return launch_fin(FIN_INIT, partial, hop_nblocks(c64.S->lat->g, c64.nrhs, c64.Ns()), c64.nrhs,
                     scal, out, c64.st);
 }
 
@@ -218,7 +220,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   } while (0)
 
   SolveBufs B;
-  if (!solve_buffers(W, h, nrhs, Ns, inner, B, io.y_packed == nullptr)) {
+  if (!solve_buffers(W, g, nrhs, Ns, inner, B, io.y_packed == nullptr)) {
     set_error("odwf_solve: out of device memory for workspaces");
     return ODWF_ENOMEM;
   }
@@ -307,7 +309,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
     return launch_fin(FIN_INIT, partial, nb_vec, nrhs, sc, dres, st);
   };
 
-  const int nbh = hop_nblocks((int)h, nrhs, Ns);
+  const int nbh = hop_nblocks(g, nrhs, Ns);
   auto any = [&](const CGScal* s, int which) {
     for (int r = 0; r < nrhs; r++) {
       if (which == 0 && s[r].active) return true;

@@ -36,7 +36,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
                         int nrhs, int inner, int maxiter, const void* b, void* x, int use_x0,
                         odwf_stats* stats, hipStream_t st, const SolveIO& io = SolveIO());
 
-size_t solve_workspace_bytes(long h, int Ns, int nrhs, int inner);
+size_t solve_workspace_bytes(const Geom& g, int Ns, int nrhs, int inner);
 
 // device buffers of a solve chunk of nrhs right-hand sides (named workspace
 // entries, allocated on first use and kept)
@@ -47,6 +47,6 @@ struct SolveBufs {
   CGScal* scal = nullptr;
   double* res = nullptr;
 };
-bool solve_buffers(Workspace& W, long h, int nrhs, int Ns, int inner, SolveBufs& B, bool own_y = true);
+bool solve_buffers(Workspace& W, const Geom& g, int nrhs, int Ns, int inner, SolveBufs& B, bool own_y = true);
 
 }  // namespace odwf

@@ -30,7 +30,7 @@ import sys
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 # the sources that define the hopping kernel, its data layout and its launch shape
-HOP_SOURCES = ["csrc/hop.hip", "csrc/dev_common.h", "csrc/odwf_types.h", "csrc/runtime.cpp"]
+HOP_SOURCES = ["csrc/hop.hip", "csrc/hop_kernel.h", "csrc/dev_common.h", "csrc/odwf_types.h", "csrc/runtime.cpp"]
 COPY_RE = re.compile(r"copyBuffer|direct_copy|CatArray|copy_kernel", re.I)
 
 
