@@ -86,7 +86,7 @@ static size_t batch_footprint_bytes(const Geom& g, int Ns, int k, int inner) {
   t += ninner * buf(half_bytes(h, k, Ns, inner));
   if (k > 1) t += 5 * buf(half_bytes(h, 1, Ns, PREC64));  // admission / retirement scratch
   const int nb = std::max(hop_nblocks(g, k, Ns), vec_nblocks(h, k, Ns));
-  t += partial_bytes(nb, k) + MAXRHS * sizeof(CGScal) + 4 * MAXRHS * sizeof(double);
+  t += partial_bytes(nb, k) + 2 * MAXRHS * sizeof(CGScal) + 4 * MAXRHS * sizeof(double);
   return t;
 }
 
@@ -150,7 +150,7 @@ extern "C" odwf_status odwf_batch_create(odwf_solver S, int max_slots, odwf_prec
   }
   const int nb = std::max(hop_nblocks(S->lat->g, k, Ns), vec_nblocks(h, k, Ns));
   B->partial = (double*)W.get("partial", partial_bytes(nb, k));
-  B->dscal = (CGScal*)W.get("scal", MAXRHS * sizeof(CGScal));
+  B->dscal = (CGScal*)W.get("scal", 2 * MAXRHS * sizeof(CGScal));
   B->dres = (double*)W.get("res", 4 * MAXRHS * sizeof(double));
   bool ok = B->f.d && B->y.d && B->e2.d && B->o0.d && B->bo.d && B->p.d && B->r.d && B->t.d &&
             B->v.d && ((int)inner == PREC64 || B->x.d) && B->s_e0.d && B->s_e1.d && B->s_e2.d &&
@@ -165,10 +165,10 @@ extern "C" odwf_status odwf_batch_create(odwf_solver S, int max_slots, odwf_prec
     set_error("odwf_batch_create: out of device memory");
     return ODWF_ENOMEM;
   }
-  std::vector<CGScal> z(MAXRHS);
+  std::vector<CGScal> z(2 * MAXRHS);
   std::memset(z.data(), 0, z.size() * sizeof(CGScal));
   BCHK(hipMemcpy(B->dscal, z.data(), z.size() * sizeof(CGScal), hipMemcpyHostToDevice));
-  std::memcpy(B->hscal, z.data(), z.size() * sizeof(CGScal));
+  std::memcpy(B->hscal, z.data(), MAXRHS * sizeof(CGScal));
   B->cache_valid = true;
   B->used.assign(k, 0);
   B->mq.assign(k, 0.0);
@@ -275,13 +275,9 @@ static hipError_t batch_iteration(odwf_batch B, hipStream_t st) {
   k4.scal = B->dscal;
   k4.partial = B->partial;
   HIPRET(apply_normal(cin, B->p, B->t, B->v, B->v, B->partial, &k4, B->dscal, GATE_ACTIVE));
-  HIPRET(launch_fin(FIN_BETA, B->partial, nbh, k, B->dscal, nullptr, st));
-  HIPRET(launch_vec_cg_step(B->inner, B->r.d, B->r.sc, B->p.d, B->p.sc, xacc->d, xacc->sc, B->dscal, h, k,
-                            Ns, st));
-  // gated update: y += x_s, x_s = 0, r = f - N y (FP64), true |r|^2
-  if (B->inner != PREC64) {
-    HIPRET(launch_vec_flush(B->inner, B->x.d, B->x.sc, B->y.d, 1, h, k, Ns, st, B->dscal, GATE_UPDATE));
-  }
+  // gated update: y += x_s, x_s = 0 (in the step), r = f - N y (FP64), true |r|^2
+  HIPRET(launch_cg_step(B->inner, B->r.d, B->r.sc, B->p.d, B->p.sc, xacc->d, xacc->sc,
+                        B->inner == PREC64 ? nullptr : B->y.d, B->partial, nbh, B->dscal, nullptr, h, k, Ns, st));
   HopOpt kr;
   kr.partial = B->partial;
   kr.cg_p = &B->f;

@@ -126,38 +126,88 @@ __global__ void __launch_bounds__(256) chunk_copy_kernel(const uint4* src, uint4
   }
 }
 
-// the CG vector step of vec_cg_step_kernel for the unscaled formats
+// The scalars of a CG vector step: the records as they are, or (partial != null)
+// formed here from the partial |r|^2 and the records' copies, by every block for
+// its right-hand side, one of them writing the record (and its host mirror).
+struct StepScal {
+  CGScal* scal;
+  const double* partial;
+  int nblocks;
+  CGScal* host;  // pinned mirror, or null
+};
+__device__ __forceinline__ CGScal step_scal(const StepScal& a, int r, int nrhs, bool writer) {
+  if (!a.partial) return a.scal[r];
+  __shared__ double tmp[256];
+  CGScal c = a.scal[SCAL_COPY + r];
+  double v = 0.0;
+  for (int b = threadIdx.x; b < a.nblocks; b += 256) v += a.partial[(long)b * nrhs + r];
+  tmp[threadIdx.x] = v;
+  __syncthreads();
+  for (int w = 128; w > 0; w >>= 1) {
+    if ((int)threadIdx.x < w) tmp[threadIdx.x] += tmp[threadIdx.x + w];
+    __syncthreads();
+  }
+  fin_beta(c, tmp[0]);
+  if (writer && threadIdx.x == 0) {
+    a.scal[r] = c;
+    if (a.host) a.host[r] = c;
+  }
+  return c;
+}
+
+// CG vector step:
+//   x += alpha p   (for every right-hand side that iterated: alpha != 0, which
+//                   includes one that converged at this iteration's beta)
+//   p  = r + beta p (for the right-hand sides still active)
+//   y += x, x = 0   (FP32 with y: for the right-hand sides that asked for an update)
 template <class P>
-__global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uint4* p_, uint4* x_, const CGScal* scal,
-                                                            ChunkGeom g) {
+__global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uint4* p_, uint4* x_, uint4* y_, StepScal sa,
+                                                            ChunkGeom g, int lg) {
   using R = typename P::real;
   constexpr int N = P::CPB;
   const int r = blockIdx.y;
-  const bool act = scal[r].active != 0;
-  const double alpha = scal[r].alpha;
-  if (!act && alpha == 0.0) return;
-  const R al = (R)alpha, beta = (R)scal[r].beta;
   cpx<R> p[UNROLL][N], x[UNROLL][N], rv[UNROLL][N];
+  // the vectors travel while the scalars are formed (a block of a right-hand
+  // side that does not iterate leaves below without using them)
+  const bool idle = sa.partial ? !sa.scal[SCAL_COPY + r].active : (!sa.scal[r].active && sa.scal[r].alpha == 0.0);
+  if (!idle) {
 #pragma unroll
-  for (int u = 0; u < UNROLL; u++) {
-    const long k = chunk_first() + u * 256;
-    if (k >= g.n) continue;
-    const long at = g.at(k, r);
-    unpack_chunk<P>(p_[at], p[u]);
-    if (alpha != 0.0) unpack_chunk<P>(x_[at], x[u]);
-    if (act) unpack_chunk<P>(r_[at], rv[u]);
-  }
-#pragma unroll
-  for (int u = 0; u < UNROLL; u++) {
-    const long k = chunk_first() + u * 256;
-    if (k >= g.n) continue;
-    const long at = g.at(k, r);
-#pragma unroll
-    for (int c = 0; c < N; c++) {
-      if (alpha != 0.0) x[u][c] = cadd(x[u][c], cscale(al, p[u][c]));
-      if (act) p[u][c] = cadd(rv[u][c], cscale(beta, p[u][c]));
+    for (int u = 0; u < UNROLL; u++) {
+      const long k = chunk_first() + u * 256;
+      if (k >= g.n) continue;
+      const long at = g.at(k, r);
+      unpack_chunk<P>(p_[at], p[u]);
+      unpack_chunk<P>(x_[at], x[u]);
+      unpack_chunk<P>(r_[at], rv[u]);
     }
-    if (alpha != 0.0) x_[at] = pack_chunk<P>(x[u], R(1));
+  }
+  const CGScal c = step_scal(sa, r, g.nrhs, blockIdx.x == 0);
+  const bool act = c.active != 0;
+  const bool flush = y_ && c.update;
+  if (!act && c.alpha == 0.0) return;
+  const R al = (R)c.alpha, beta = (R)c.beta;
+#pragma unroll
+  for (int u = 0; u < UNROLL; u++) {
+    const long k = chunk_first() + u * 256;
+    if (k >= g.n) continue;
+    const long at = g.at(k, r);
+#pragma unroll
+    for (int q = 0; q < N; q++) {
+      if (c.alpha != 0.0) x[u][q] = cadd(x[u][q], cscale(al, p[u][q]));
+      if (act) p[u][q] = cadd(rv[u][q], cscale(beta, p[u][q]));
+    }
+    if (P::CPB == 2 && flush) {
+      const long d0 = at + (at >> lg << lg);
+#pragma unroll
+      for (int q = 0; q < N; q++) {
+        cpx<double> o;
+        unpack_chunk<SP64>(y_[d0 + (q << lg)], &o);
+        o = cadd(o, cpx<double>{(double)x[u][q].re, (double)x[u][q].im});
+        y_[d0 + (q << lg)] = pack_chunk<SP64>(&o, 1.0);
+        x[u][q] = {R(0), R(0)};
+      }
+    }
+    if (c.alpha != 0.0) x_[at] = pack_chunk<P>(x[u], R(1));
     if (act) p_[at] = pack_chunk<P>(p[u], R(1));
   }
 }
@@ -314,14 +364,28 @@ hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, 
   return launch_vec_zero(prec, x, x_sc, h, nrhs, Ns, st, gate, gate_mode);
 }
 
-hipError_t launch_vec_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x,
-                              float* x_sc, const CGScal* scal, long h, int nrhs, int Ns, hipStream_t st) {
-  if (prec == PREC64 || prec == PREC32) {
+// beta is formed inside the vector step while a block of it reads at most this
+// many partial sums (two loads a thread, the scalar launch and its gap saved:
+// 4-6 us of a 4^4 x 8 iteration); above, by a launch of its own
+constexpr int STEP_BLOCKS = 512;
+
+hipError_t launch_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x, float* x_sc,
+                          void* y, const double* partial, int nblocks, CGScal* scal, CGScal* host, long h, int nrhs,
+                          int Ns, hipStream_t st) {
+  StepScal a = {scal, partial, nblocks, host};
+  const bool chunks = prec == PREC64 || prec == PREC32;
+  if (!chunks || nblocks > STEP_BLOCKS) {
+    const hipError_t e = launch_fin(FIN_BETA, partial, nblocks, nrhs, scal, nullptr, st, 0, host);
+    if (e != hipSuccess) return e;
+    a.partial = nullptr;
+  }
+  if (chunks) {
     const ChunkGeom g = chunk_geom(prec == PREC64 ? 1 : 2, h, nrhs, Ns);
     const uint4* r4 = reinterpret_cast<const uint4*>(r);
-    uint4 *p4 = reinterpret_cast<uint4*>(p), *x4 = reinterpret_cast<uint4*>(x);
-    if (prec == PREC64) hipLaunchKernelGGL(chunk_cg_step_kernel<SP64>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, scal, g);
-    else hipLaunchKernelGGL(chunk_cg_step_kernel<SP32>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, scal, g);
+    uint4 *p4 = reinterpret_cast<uint4*>(p), *x4 = reinterpret_cast<uint4*>(x), *y4 = reinterpret_cast<uint4*>(y);
+    const int lg = __builtin_ctz(Ns);
+    if (prec == PREC64) hipLaunchKernelGGL(chunk_cg_step_kernel<SP64>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, nullptr, a, g, lg);
+    else hipLaunchKernelGGL(chunk_cg_step_kernel<SP32>, chunk_grid(g), dim3(256), 0, st, r4, p4, x4, y4, a, g, lg);
     return hipGetLastError();
   }
   const int block = vec_spb(nrhs, Ns) * nrhs * Ns;
@@ -396,88 +460,25 @@ hipError_t launch_vec_copy_rhs(int prec_src, const void* src, const float* src_s
 }
 
 // ---------------------------------------------------------------------------
-// finalisation: one block of 256 threads
+// finalisation: one block of 1024 threads
 // ---------------------------------------------------------------------------
-__global__ void fin_kernel(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
-                           double* out, int gated) {
-  // all right-hand sides in one pass: thread t adds the partials of blocks
-  // t, t + 256, ... per right-hand side, then one fixed tree over the threads
-  __shared__ double red[MAXRHS * 256];
-  __shared__ double sums[MAXRHS];
-  double acc[MAXRHS];
-#pragma unroll
-  for (int r = 0; r < MAXRHS; r++) acc[r] = 0.0;
-  for (int b = threadIdx.x; b < nblocks; b += blockDim.x) {
-#pragma unroll
-    for (int r = 0; r < MAXRHS; r++)
-      if (r < nrhs) acc[r] += partial[(long)b * nrhs + r];
-  }
-#pragma unroll
-  for (int r = 0; r < MAXRHS; r++)
-    if (r < nrhs) red[r * 256 + threadIdx.x] = acc[r];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      for (int r = 0; r < nrhs; r++) red[r * 256 + threadIdx.x] += red[r * 256 + threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if ((int)threadIdx.x < nrhs) sums[threadIdx.x] = red[threadIdx.x * 256];
-  __syncthreads();
+__global__ void __launch_bounds__(1024) fin_kernel(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
+                                                   double* out, int gated, CGScal* host) {
+  __shared__ double tmp[1024];
+  const double v = partial_sum(partial, nblocks, nrhs, tmp);
   if ((int)threadIdx.x >= nrhs) return;
   const int r = threadIdx.x;
-  const double v = sums[r];
   if (out) out[r] = v;
   if (!scal) return;
-  CGScal c = scal[r];
+  CGScal c = scal[(kind == FIN_BETA ? SCAL_COPY : 0) + r];
   if (gated && !c.update) return;  // only the right-hand sides that asked for it
   const bool finite = isfinite(v);
   switch (kind) {
     case FIN_F2:
       c.f2 = v;
       break;
-    case FIN_ALPHA:
-      c.pAp = v;
-      if (c.active) {
-        if (!finite || !(v > 0.0)) {
-          c.nan = !finite;
-          c.active = 0;
-          c.alpha = 0.0;
-        } else {
-          c.alpha = c.rr / v;
-        }
-      } else {
-        c.alpha = 0.0;
-      }
-      break;
     case FIN_BETA:
-      if (c.active) {
-        c.iters += 1;
-        if (!finite) {
-          c.nan = 1;
-          c.active = 0;
-          c.beta = 0.0;
-        } else {
-          c.beta = v / c.rr;
-          c.rr = v;
-          if (v > c.rmax2) c.rmax2 = v;
-          const bool met = v <= c.tol2 * c.f2;
-          const bool capped = c.iters >= c.maxiter;
-          if (c.confirm) {
-            // the decision is left to the true residual of the update that follows
-            if (met || capped) c.update = 1;
-            if (capped) c.active = 0;
-          } else if (met) {
-            c.converged = 1;
-            c.active = 0;
-          } else if (capped) {
-            c.active = 0;
-          }
-          if (c.delta2 > 0.0 && v < c.delta2 * c.rmax2) c.update = 1;
-        }
-      } else {
-        c.beta = 0.0;
-      }
+      fin_beta(c, v);
       break;
     case FIN_INIT:
       // v = |r|^2 of a freshly computed true residual
@@ -503,34 +504,17 @@ __global__ void fin_kernel(int kind, const double* partial, int nblocks, int nrh
       break;
   }
   scal[r] = c;
+  if (host) host[r] = c;
 }
 
 // first stage of the finalisation for long partial arrays: block b sums the
 // partials of blocks [b * 1024, (b + 1) * 1024) per right-hand side in a fixed
 // tree and writes them to dst[b * nrhs + r]
-__global__ void partial_reduce_kernel(const double* partial, int nblocks, int nrhs, double* dst) {
-  __shared__ double red[MAXRHS * 256];
+__global__ void __launch_bounds__(256) partial_reduce_kernel(const double* partial, int nblocks, int nrhs, double* dst) {
+  __shared__ double tmp[256];
   const int b0 = blockIdx.x * 1024;
-  const int b1 = min(b0 + 1024, nblocks);
-  double acc[MAXRHS];
-#pragma unroll
-  for (int r = 0; r < MAXRHS; r++) acc[r] = 0.0;
-  for (int b = b0 + threadIdx.x; b < b1; b += blockDim.x) {
-#pragma unroll
-    for (int r = 0; r < MAXRHS; r++)
-      if (r < nrhs) acc[r] += partial[(long)b * nrhs + r];
-  }
-#pragma unroll
-  for (int r = 0; r < MAXRHS; r++)
-    if (r < nrhs) red[r * 256 + threadIdx.x] = acc[r];
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      for (int r = 0; r < nrhs; r++) red[r * 256 + threadIdx.x] += red[r * 256 + threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if ((int)threadIdx.x < nrhs) dst[(long)blockIdx.x * nrhs + threadIdx.x] = red[threadIdx.x * 256];
+  const double v = partial_sum(partial + (long)b0 * nrhs, min(1024, nblocks - b0), nrhs, tmp);
+  if ((int)threadIdx.x < nrhs) dst[(long)blockIdx.x * nrhs + threadIdx.x] = v;
 }
 
 size_t partial_bytes(int nblocks, int nrhs) {
@@ -538,17 +522,17 @@ size_t partial_bytes(int nblocks, int nrhs) {
 }
 
 hipError_t launch_fin(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
-                      double* out, hipStream_t st, int gated) {
-  if (nblocks > 2048) {
-    // two stages; the second-stage inputs live behind the first-stage partials
+                      double* out, hipStream_t st, int gated, CGScal* host) {
+  // one block reads up to 16384 values at 16 a thread; longer arrays take two stages
+  if ((long)nblocks * nrhs > 16384) {
+    // the second-stage inputs live behind the first-stage partials
     double* dst = const_cast<double*>(partial) + (size_t)nblocks * nrhs;
     const int nb2 = (nblocks + 1023) / 1024;
     hipLaunchKernelGGL(partial_reduce_kernel, dim3(nb2), dim3(256), 0, st, partial, nblocks, nrhs, dst);
     partial = dst;
     nblocks = nb2;
   }
-  hipLaunchKernelGGL(fin_kernel, dim3(1), dim3(256), 0, st, kind, partial, nblocks, nrhs, scal, out,
-                     gated);
+  hipLaunchKernelGGL(fin_kernel, dim3(1), dim3(1024), 0, st, kind, partial, nblocks, nrhs, scal, out, gated, host);
   return hipGetLastError();
 }
 

@@ -652,4 +652,80 @@ __device__ __forceinline__ void block_reduce_rhs(double v, int Ns, int nsl, int 
   }
 }
 
+// ---------------------------------------------------------------------------
+// CG scalars from partial sums: the sum in a fixed order, and the update of a
+// right-hand side's record
+// ---------------------------------------------------------------------------
+// sum over blocks of partial[b * nrhs + r]; thread r < nrhs returns right-hand
+// side r's.  Threads take consecutive doubles (a thread keeps one right-hand
+// side), then a fixed tree.  Every thread of the block calls it; tmp: LDS of
+// blockDim.x doubles.
+__device__ __forceinline__ double partial_sum(const double* __restrict__ partial, int nblocks, int nrhs, double* tmp) {
+  const int tid = threadIdx.x;
+  int n = blockDim.x / nrhs;
+  const int used = n * nrhs;
+  double acc = 0.0;
+  if (tid < used) {
+    const long total = (long)nblocks * nrhs;
+    long i = tid;
+    for (; i + 7L * used < total; i += 8L * used) {  // eight loads in flight
+      double v[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) v[u] = partial[i + (long)u * used];
+#pragma unroll
+      for (int u = 0; u < 8; u++) acc += v[u];
+    }
+    for (; i < total; i += used) acc += partial[i];
+  }
+  __syncthreads();  // tmp may alias LDS the block used before
+  tmp[tid] = acc;
+  __syncthreads();
+  while (n > 1) {
+    const int half = (n + 1) / 2;
+    if (tid < (n - half) * nrhs) tmp[tid] += tmp[tid + half * nrhs];
+    __syncthreads();
+    n = half;
+  }
+  return tmp[tid];
+}
+
+__device__ __forceinline__ void fin_alpha(CGScal& c, double v) {  // v = <p, N p>
+  c.pAp = v;
+  c.alpha = 0.0;
+  if (!c.active) return;
+  if (!isfinite(v) || !(v > 0.0)) {
+    c.nan = !isfinite(v);
+    c.active = 0;
+  } else {
+    c.alpha = c.rr / v;
+  }
+}
+
+__device__ __forceinline__ void fin_beta(CGScal& c, double v) {  // v = |r|^2 after the step
+  c.beta = 0.0;
+  if (!c.active) return;
+  c.iters += 1;
+  if (!isfinite(v)) {
+    c.nan = 1;
+    c.active = 0;
+    return;
+  }
+  c.beta = v / c.rr;
+  c.rr = v;
+  if (v > c.rmax2) c.rmax2 = v;
+  const bool met = v <= c.tol2 * c.f2;
+  const bool capped = c.iters >= c.maxiter;
+  if (c.confirm) {
+    // the decision is left to the true residual of the update that follows
+    if (met || capped) c.update = 1;
+    if (capped) c.active = 0;
+  } else if (met) {
+    c.converged = 1;
+    c.active = 0;
+  } else if (capped) {
+    c.active = 0;
+  }
+  if (c.delta2 > 0.0 && v < c.delta2 * c.rmax2) c.update = 1;
+}
+
 }  // namespace odwf

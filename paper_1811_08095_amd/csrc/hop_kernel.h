@@ -23,6 +23,7 @@
 // is a string of 3x3 complex mat-vecs; its time is set by the traffic between
 // the L2 caches and memory (FP32, FP64) or by VALU issue (FP16, BF16 storage).
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "dev_common.h"
@@ -214,13 +215,12 @@ __device__ __forceinline__ void hop_one_scaled(const cpx<R> (&psi)[12], R sc, co
 // group of xgy (y) x 8 / xgy (z) adjacent tiles at the same time, block for
 // block, so the halo rows two XCDs share are fetched by both at about the same
 // time and the second read is served by the memory-side cache.
-__device__ __forceinline__ uint32_t block_first_site(const HopArgs& a) {
+__device__ __forceinline__ uint32_t block_first_site(const HopArgs& a, uint32_t lb) {
   auto split = [](uint32_t& n, const FastDiv& d) {  // n mod d, n <- n / d
     const uint32_t q = d.div(n), r = n - q * d.d;
     n = q;
     return r;
   };
-  uint32_t lb = blockIdx.x;
   const uint32_t hx = a.d_hx.d;
   if (a.xcd == 1) {
     const uint32_t q = a.nblocks >> 3, rem = a.nblocks & 7;
@@ -400,7 +400,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
         }
         store_site<P, ODWF_NT_FUSED>(a.cg_r, a.cg_r_sc, j, r, s, nrhs, NS, rv);
       }
-      // x += alpha p runs in the vector step after beta (vec_cg_step_kernel),
+      // x += alpha p runs in the vector step after beta (launch_cg_step),
       // which reads p there anyway
     }
   } else if (valid && a.out) {
@@ -708,6 +708,18 @@ struct HopWaves {
       sizeof(typename P::real) == 8 ? ODWF_HOP_WAVES64 : ((PLAIN || NS <= DENSE_N) ? ODWF_HOP_WAVES32 : 2);
 };
 
+// alpha of the iteration from the partial sums of an earlier launch, into the
+// records' copies that the rest of the iteration works from (the records
+// themselves stay: other blocks of this launch read their gates)
+__device__ __forceinline__ void fin_block(const HopArgs& a, double* tmp) {
+  const double v = partial_sum(a.fin_partial, a.fin_nblocks, a.nrhs, tmp);
+  const int r = threadIdx.x;
+  if (r >= a.nrhs) return;
+  CGScal c = a.fin_scal[r];
+  fin_alpha(c, v);
+  a.fin_scal[SCAL_COPY + r] = c;
+}
+
 template <class P, int NS, bool DAG, bool PLAIN>
 __global__ void __launch_bounds__(256, (HopWaves<P, NS, PLAIN>::W)) hop_kernel(const HopArgs a) {
   using R = typename P::real;
@@ -718,8 +730,18 @@ __global__ void __launch_bounds__(256, (HopWaves<P, NS, PLAIN>::W)) hop_kernel(c
   const int col = tid / NS, s = tid - col * NS;  // column (site, right-hand side) of the block, and slice
   const int sl = nrhs == 1 ? col : col / nrhs;
   const int r = col - sl * nrhs;
+  uint32_t lb = blockIdx.x;
+  if constexpr (!PLAIN) {
+    if (a.fin_partial) {  // the first block forms the step lengths
+      if (lb == 0) {
+        fin_block(a, reinterpret_cast<double*>(smem));
+        return;
+      }
+      lb -= 1;
+    }
+  }
   if (!gate_any(a.gate, a.gate_mode, nrhs)) return;  // whole block idle
-  const uint32_t j0 = block_first_site(a);
+  const uint32_t j0 = block_first_site(a, lb);
   const int nsb = min(a.spb, a.h - (int)j0);
   // padded threads have sl >= spb >= nsb; gated-off right-hand sides do no work
   const bool valid = sl < nsb && gate_on(a.gate, a.gate_mode, r);
@@ -795,7 +817,7 @@ __global__ void __launch_bounds__(256, (HopWaves<P, NS, PLAIN>::W)) hop_kernel(c
   asm volatile("" : "+v"(slr));
   const double nval =
       fused_tail<P, NS>(a, acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap, x_first ? X_LDS : X_LOAD);
-  if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, blockIdx.x);
+  if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, lb);
 }
 
 // extra LDS per block (plain / fused kernels): caps the blocks resident per CU
@@ -814,8 +836,10 @@ static size_t hop_smem(const HopArgs& a, bool plain) {
          (size_t)((a.spb * a.nrhs * NS + 63) / 64) * DENSE_SCRATCH<R>;
   else if (!plain)
     n += (size_t)a.spb * a.nrhs * 12 * (NS + 1) * 2 + MAXRHS;
-  return n * sizeof(R) + (plain ? 0 : (size_t)a.spb * a.nrhs * sizeof(double)) +
-         (plain ? ODWF_HOP_SMEM_PAD : ODWF_HOP_SMEM_PAD_F);
+  n = n * sizeof(R) + (plain ? 0 : (size_t)a.spb * a.nrhs * sizeof(double));
+  // a launch with a scalar block: one double a thread
+  if (a.fin_partial) n = std::max(n, (size_t)256 * sizeof(double));
+  return n + (plain ? ODWF_HOP_SMEM_PAD : ODWF_HOP_SMEM_PAD_F);
 }
 
 template <class P, int NS>
@@ -824,7 +848,7 @@ static hipError_t launch_hop_t(HopArgs a, int dag, hipStream_t st) {
   if (inner > 256 || a.nrhs > MAXRHS) return hipErrorInvalidValue;
   const int block = (a.spb * inner + 63) & ~63;  // whole waves, <= 256
   const size_t sm = hop_smem<P, NS>(a, a.plain);
-  const dim3 grid(a.nblocks);
+  const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0));
   if (a.plain) {
     if (dag) hipLaunchKernelGGL((hop_kernel<P, NS, true, true>), grid, dim3(block), sm, st, a);
     else hipLaunchKernelGGL((hop_kernel<P, NS, false, true>), grid, dim3(block), sm, st, a);

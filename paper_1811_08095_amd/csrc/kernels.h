@@ -77,10 +77,14 @@ hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, 
 hipError_t launch_vec_copy_rhs(int prec_src, const void* src, const float* src_sc, int nrhs_src,
                                int r_src, int prec_dst, void* dst, float* dst_sc, int nrhs_dst,
                                int r_dst, long h, int Ns, hipStream_t st);
-// CG vector step: x += alpha_r p for right-hand sides that iterated (alpha != 0),
-// then p = r + beta_r p for the active ones
-hipError_t launch_vec_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x,
-                              float* x_sc, const CGScal* scal, long h, int nrhs, int Ns, hipStream_t st);
+// End of a CG iteration: beta_r and the convergence decisions from the partial
+// |r|^2 (nblocks blocks) and the records' copies (SCAL_COPY), into the records
+// and, when host is given, their pinned mirror; then x += alpha_r p for
+// right-hand sides that iterated, p = r + beta_r p for the active ones and, with
+// y (FP32: the FP64 solution), y += x, x = 0 for those that asked for an update.
+hipError_t launch_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x, float* x_sc,
+                          void* y, const double* partial, int nblocks, CGScal* scal, CGScal* host, long h, int nrhs,
+                          int Ns, hipStream_t st);
 // per-block partial sums of |v|^2 per right-hand side
 hipError_t launch_vec_norm2(int prec, const void* v, const float* sc, double* partial, long h,
                             int nrhs, int Ns, int* nblocks_out, hipStream_t st);
@@ -94,12 +98,12 @@ hipError_t launch_force(const void* chi_own, const void* psi_own, const void* ch
                         hipStream_t st);
 
 // scalar finalisation (blas.hip), one block
-enum FinKind { FIN_SUM = 0, FIN_ALPHA = 1, FIN_BETA = 2, FIN_INIT = 3, FIN_F2 = 4, FIN_TRUE = 5 };
+enum FinKind { FIN_SUM = 0, FIN_BETA = 2, FIN_INIT = 3, FIN_F2 = 4 };
 // bytes a partial-sum buffer for nblocks blocks needs (includes the second
 // reduction stage used for long partial arrays)
 size_t partial_bytes(int nblocks, int nrhs);
 // gated != 0: only right-hand sides whose update flag is set are finalised
 hipError_t launch_fin(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
-                      double* out, hipStream_t st, int gated = 0);
+                      double* out, hipStream_t st, int gated = 0, CGScal* host = nullptr);
 
 }  // namespace odwf

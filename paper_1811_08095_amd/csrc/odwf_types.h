@@ -97,6 +97,13 @@ struct CGScal {
   int upd_iters;  // iteration count at its last true-residual update
 };
 
+// Scalar arrays hold 2 * MAXRHS records: the current ones, and from MAXRHS on
+// the copies that get this iteration's alpha.  The current records do not change
+// until beta: the launch that forms alpha still reads their gates, and the step
+// forms beta from the copies alone, so any block of it may do so at any time
+// while one of them writes the current record.
+constexpr int SCAL_COPY = MAXRHS;
+
 // which right-hand sides a gated kernel works on
 enum GateMode { GATE_NONE = 0, GATE_ACTIVE = 1, GATE_UPDATE = 2 };
 
@@ -146,6 +153,11 @@ struct HopArgs {
   const float* cg_p_sc;
   const CGScal* scal;
   double* partial;      // per block, per right-hand side
+  // a finished launch's partial sums that block 0 of this one (an extra block)
+  // turns into the step lengths alpha while the others work (null: no such block)
+  const double* fin_partial;
+  int fin_nblocks;
+  CGScal* fin_scal;
   const void* coef;     // [2][NCOEF][Ns], compute precision
   double kappa[MAXRHS]; // per right-hand side: -mu_r
   // fifth-dimension programs on the hopping result (h), the x term (x) and the

@@ -116,6 +116,10 @@ struct HopOpt {
   HV* cg_r = nullptr;
   const HV* cg_p = nullptr;  // f of the residual f - N p (mode 3)
   const CGScal* scal = nullptr;
+  // alpha of the iteration from an earlier launch's partial sums, formed by an
+  // extra block of this one (fin_scal: the records, copies behind them)
+  const double* fin_partial = nullptr;
+  CGScal* fin_scal = nullptr;
   // gating (GateMode): only right-hand sides selected by gate do any work
   const CGScal* gate = nullptr;
   int gate_mode = GATE_NONE;

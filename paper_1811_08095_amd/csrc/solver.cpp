@@ -85,11 +85,12 @@ hipError_t apply_normal(const OpCtx& c, const HV& p, const HV& t, const HV& v, c
   k2.gate = gate;
   k2.gate_mode = gate_mode;
   HIPRET(hop(c, 0, 0, t, &v, k2));
-  if (partial_u && k4opt && k4opt->scal && k4opt->cg_r)
-    HIPRET(launch_fin(FIN_ALPHA, partial_u, hop_nblocks(c.S->lat->g, c.nrhs, c.Ns()), c.nrhs,
-                      const_cast<CGScal*>(k4opt->scal), nullptr, c.st));
   HopOpt k3;
   k3.ph = prog_ainv_t();
+  if (partial_u && k4opt && k4opt->scal && k4opt->cg_r) {  // alpha is ready when K4 needs it
+    k3.fin_partial = partial_u;
+    k3.fin_scal = const_cast<CGScal*>(k4opt->scal);
+  }
   k3.gate = gate;
   k3.gate_mode = gate_mode;
   HIPRET(hop(c, 1, 1, v, &t, k3));
@@ -100,6 +101,7 @@ hipError_t apply_normal(const OpCtx& c, const HV& p, const HV& t, const HV& v, c
   k4.cx = 1.0;
   k4.gate = gate;
   k4.gate_mode = gate_mode;
+  if (k3.fin_scal) k4.scal += SCAL_COPY;  // the records as alpha left them
   const HV* o = (k4opt && k4opt->cg_r) ? nullptr : &out;
   return hop(c, 0, 1, t, o, k4);
 }
@@ -121,12 +123,14 @@ struct Poller {
       if (ev[i]) (void)hipEventDestroy(ev[i]);
     if (host) (void)hipHostFree(host);
   }
-  hipError_t push(const CGScal* d, int nrhs, hipStream_t st) {
+  // the mirror the next step writes; its previous contents must have been read
+  CGScal* next() {
     const int slot = (int)(k % 4);
-    // the slot's previous copy must have landed before it is overwritten
-    if (k >= 4) HIPRET(hipEventSynchronize(ev[slot]));
-    HIPRET(hipMemcpyAsync(host + slot * MAXRHS, d, nrhs * sizeof(CGScal), hipMemcpyDeviceToHost, st));
-    HIPRET(hipEventRecord(ev[slot], st));
+    if (k >= 4 && hipEventSynchronize(ev[slot]) != hipSuccess) return nullptr;
+    return host + slot * MAXRHS;
+  }
+  hipError_t push(hipStream_t st) {  // behind that step
+    HIPRET(hipEventRecord(ev[k % 4], st));
     k++;
     return hipSuccess;
   }
@@ -165,7 +169,7 @@ bool solve_buffers(Workspace& W, const Geom& g, int nrhs, int Ns, int inner, Sol
   B.o0 = W.half("s.o0", h, nrhs, Ns, PREC64);  // FP64 odd scratch
   const int nbmax = std::max(hop_nblocks(g, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
   B.partial = (double*)W.get("s.partial", partial_bytes(nbmax, nrhs));
-  B.scal = (CGScal*)W.get("s.scal", 2 * MAXRHS * sizeof(CGScal));
+  B.scal = (CGScal*)W.get("s.scal", 3 * MAXRHS * sizeof(CGScal));
   B.res = (double*)W.get("s.res", 4 * MAXRHS * sizeof(double));
   bool ok = B.e0.d && (B.e1.d || !own_y) && B.e2.d && B.o0.d && B.partial && B.scal && B.res;
   if (inner == PREC64) {
@@ -232,7 +236,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   HV e0 = B.e0, e1 = B.e1, e2 = B.e2, o0 = B.o0;
   double* partial = B.partial;
   CGScal* dscal = B.scal;
-  CGScal* dscal_out = dscal + MAXRHS;
+  CGScal* dscal_out = dscal + 2 * MAXRHS;  // behind the records and their copies
   double* dres = B.res;
   int nb_vec = 0;
 
@@ -273,15 +277,15 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   }
 
   // ---- device scalars --------------------------------------------------------
-  CGScal hs[2 * MAXRHS];
+  CGScal hs[3 * MAXRHS];
   std::memset(hs, 0, sizeof(hs));
   for (int r = 0; r < nrhs; r++) {
     hs[r].tol2 = tol[r] * tol[r];
     hs[r].maxiter = maxiter;
     hs[r].active = 1;
     hs[r].delta2 = inner == PREC32 ? RELIABLE_DELTA2 : 0.0;
-    hs[MAXRHS + r] = hs[r];
-    hs[MAXRHS + r].delta2 = 0.0;
+    hs[2 * MAXRHS + r] = hs[r];
+    hs[2 * MAXRHS + r].delta2 = 0.0;
   }
   CHK(hipMemcpyAsync(dscal, hs, sizeof(hs), hipMemcpyHostToDevice, st));
   CHK(launch_vec_norm2(PREC64, e0.d, nullptr, partial, h, nrhs, Ns, &nb_vec, st));
@@ -331,9 +335,9 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(c64, p, o0, e2, e2, partial, &k4));
-        CHK(launch_fin(FIN_BETA, partial, nbh, nrhs, dscal, nullptr, st));
-        CHK(launch_vec_cg_step(PREC64, r.d, nullptr, p.d, nullptr, e1.d, nullptr, dscal, h, nrhs, Ns, st));
-        CHK(poll.push(dscal, nrhs, st));
+        CHK(launch_cg_step(PREC64, r.d, nullptr, p.d, nullptr, e1.d, nullptr, nullptr, partial, nbh, dscal, poll.next(),
+                           h, nrhs, Ns, st));
+        CHK(poll.push(st));
         const CGScal* v = poll.view(2);
         if (v && !any(v, 0)) break;
       }
@@ -359,9 +363,9 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(cin, p, t, v, v, partial, &k4));
-        CHK(launch_fin(FIN_BETA, partial, nbh, nrhs, dscal, nullptr, st));
-        CHK(launch_vec_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, dscal, h, nrhs, Ns, st));
-        CHK(poll.push(dscal, nrhs, st));
+        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, poll.next(), h, nrhs,
+                           Ns, st));
+        CHK(poll.push(st));
         const CGScal* vw = poll.view(2);
         if (vw && (!any(vw, 0) || any(vw, 1))) break;
       }
@@ -406,9 +410,9 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(cin, p, t, v, v, partial, &k4));
-        CHK(launch_fin(FIN_BETA, partial, nbh, nrhs, dscal, nullptr, st));
-        CHK(launch_vec_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, dscal, h, nrhs, Ns, st));
-        CHK(poll.push(dscal, nrhs, st));
+        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, poll.next(), h, nrhs,
+                           Ns, st));
+        CHK(poll.push(st));
         const CGScal* vw = poll.view(2);
         if (vw && !any(vw, 0)) break;
       }
