@@ -85,7 +85,7 @@ static size_t batch_footprint_bytes(const Geom& g, int Ns, int k, int inner) {
   const int ninner = inner == PREC64 ? 4 : 5;       // p, r, t, v (+ x)
   t += ninner * buf(half_bytes(h, k, Ns, inner));
   if (k > 1) t += 5 * buf(half_bytes(h, 1, Ns, PREC64));  // admission / retirement scratch
-  const int nb = std::max(hop_nblocks(g, k, Ns), vec_nblocks(h, k, Ns));
+  const int nb = std::max(max_nblocks(g, k, Ns, inner), max_nblocks(g, 1, Ns, PREC64));
   t += partial_bytes(nb, k) + 2 * MAXRHS * sizeof(CGScal) + 4 * MAXRHS * sizeof(double);
   return t;
 }
@@ -148,7 +148,7 @@ extern "C" odwf_status odwf_batch_create(odwf_solver S, int max_slots, odwf_prec
     B->s_o0 = W.half("s_o0", h, 1, Ns, PREC64);
     B->s_bo = W.half("s_bo", h, 1, Ns, PREC64);
   }
-  const int nb = std::max(hop_nblocks(S->lat->g, k, Ns), vec_nblocks(h, k, Ns));
+  const int nb = std::max(max_nblocks(S->lat->g, k, Ns, inner), max_nblocks(S->lat->g, 1, Ns, PREC64));
   B->partial = (double*)W.get("partial", partial_bytes(nb, k));
   B->dscal = (CGScal*)W.get("scal", 2 * MAXRHS * sizeof(CGScal));
   B->dres = (double*)W.get("res", 4 * MAXRHS * sizeof(double));
@@ -268,7 +268,7 @@ static hipError_t batch_iteration(odwf_batch B, hipStream_t st) {
   kappas(B, kap);
   OpCtx cin = ctx_of(B, st, B->inner, k, kap);
   OpCtx c64 = ctx_of(B, st, PREC64, k, kap);
-  const int nbh = hop_nblocks(S->lat->g, k, Ns);
+  const int nbh = hop_nblocks(S->lat->g, k, Ns, B->inner), nbh64 = hop_nblocks(S->lat->g, k, Ns, PREC64);
   HV* xacc = B->inner == PREC64 ? &B->y : &B->x;
   HopOpt k4;
   k4.cg_r = &B->r;
@@ -284,7 +284,7 @@ static hipError_t batch_iteration(odwf_batch B, hipStream_t st) {
   HIPRET(apply_normal(c64, B->y, B->o0, B->e2, B->e2, nullptr, &kr, B->dscal, GATE_UPDATE));
   HIPRET(launch_vec_convert(PREC64, B->e2.d, nullptr, B->inner, B->r.d, B->r.sc, 0, h, k, Ns, st,
                             B->dscal, GATE_UPDATE));
-  return launch_fin(FIN_INIT, B->partial, nbh, k, B->dscal, nullptr, st, 1);
+  return launch_fin(FIN_INIT, B->partial, nbh64, k, B->dscal, nullptr, st, 1);
 }
 
 extern "C" odwf_status odwf_batch_step(odwf_batch B, int iters, void* stream) {

@@ -527,7 +527,15 @@ constexpr int DENSE_SCRATCH = 4 * Mfma<R>::SET;
 // right-hand side of a launch.
 template <class R>
 __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab) {
-  for (int i = threadIdx.x; i < DENSE_LEN; i += blockDim.x) m[i] = (R)tab[i];
+  constexpr int K = (DENSE_LEN + 255) / 256;  // a thread's elements in flight together (256 threads)
+  for (int i0 = threadIdx.x; i0 < DENSE_LEN; i0 += K * blockDim.x) {
+    double v[K];
+#pragma unroll
+    for (int k = 0; k < K; k++) v[k] = tab[min(i0 + k * (int)blockDim.x, DENSE_LEN - 1)];
+#pragma unroll
+    for (int k = 0; k < K; k++)
+      if (i0 + k * (int)blockDim.x < DENSE_LEN) m[i0 + k * blockDim.x] = (R)v[k];
+  }
 }
 
 // y <- M y for the 12 components of every lane's 5D site; m: LDS image; scr:

@@ -27,14 +27,28 @@ int hop_spb(int hx, int nrhs, int Ns) {
   return most;
 }
 
-int hop_nblocks(const Geom& g, int nrhs, int Ns) {
-  const int spb = hop_spb(g.L[0] / 2, nrhs, Ns);
+// Small launches take the four-wave kernel: 64 lanes of columns a block, up to
+// 512 blocks in FP64 and 1024 in the reduced precisions.  Measured per CG
+// iteration, four-wave kernel against the other, N_s = 16, one right-hand side:
+// 4^4 47.8 / 71.9 us (FP64), 49 / 64 (FP32); 8^4 (512 blocks) 71 / 91 and
+// 62 / 73; 8^3 x 16 (1024) 103 / 96 and 62 / 75; 16^2 x 8^2 (2048) 177 / 154 and
+// 110 / 104.
+bool hop_small(const Geom& g, int nrhs, int Ns, int prec) {
+  if (!dense_ns(Ns) || nrhs * Ns > 64) return false;
+  const int spb = 64 / (nrhs * Ns);
+  return (g.h + spb - 1) / spb <= (prec == PREC64 ? 512 : 1024);
+}
+
+int hop_nblocks(const Geom& g, int nrhs, int Ns, int prec) {
+  const int spb = hop_launch_spb(g, nrhs, Ns, prec, false);
   return (int)((g.h + spb - 1) / spb);
 }
 
 // sites per block of a launch (plain launches, which carry no partial sums, may
 // use smaller blocks: shorter x-row segments, so more of them per XCD share its L2)
-int hop_launch_spb(int hx, int nrhs, int Ns, int prec, bool plain) {
+int hop_launch_spb(const Geom& g, int nrhs, int Ns, int prec, bool plain) {
+  if (hop_small(g, nrhs, Ns, prec) && !(plain && prec != PREC64)) return 64 / (nrhs * Ns);
+  const int hx = g.L[0] / 2;
   const int threads = !plain ? 256 : (prec == PREC64 ? ODWF_HOP_THREADS64 : ODWF_HOP_THREADS32);
   if (threads == 256) return hop_spb(hx, nrhs, Ns);
   const int spb = std::max(1, threads / (nrhs * Ns));

@@ -291,24 +291,49 @@ struct ProgLds {
 // loaded (and transformed) here
 enum XMode { X_LDS = 1, X_LOAD = 2 };
 
+// what the epilogue reads, loaded ahead of the hop where registers allow
+// (small launches): x term, CG residual or f, rho per program and chirality
+template <class P, int NS>
+__device__ __forceinline__ void tail_preload(const HopArgs& a, bool valid, long j, int r, int s,
+                                             cpx<typename P::real> (&xv)[12], cpx<typename P::real> (&rv)[12],
+                                             typename P::real (&rho)[6], typename P::real& alpha, bool& cg_update) {
+  using R = typename P::real;
+#pragma unroll
+  for (int chi = 0; chi < 2; chi++) {  // zeros where there is no program
+    rho[chi] = (R)a.dn_h.rho[chi * MAXRHS + r];
+    rho[2 + chi] = (R)a.dn_x.rho[chi * MAXRHS + r];
+    rho[4 + chi] = (R)a.dn_o.rho[chi * MAXRHS + r];
+  }
+  cg_update = a.partial && a.cg_r && valid && a.scal[r].active;
+  alpha = cg_update ? (R)a.scal[r].alpha : R(0);
+  if (a.xin && valid) load_site<P, ODWF_NT_FUSED>(a.xin, a.xin_sc, j, r, s, a.nrhs, NS, xv);
+  if (cg_update || (a.partial && !a.cg_r && a.cg_p && valid)) {
+    const bool upd = a.cg_r != nullptr;
+    load_site<P, ODWF_NT_FUSED>(upd ? a.cg_r : a.cg_p, upd ? a.cg_r_sc : a.cg_p_sc, j, r, s, a.nrhs, NS, rv);
+  }
+}
+
 // Fused epilogue of one output site after the hop: the fifth-dimension
 // programs, the x term, the norm for the partial sums, and the residual, the CG
 // update or the store.  Every thread of the block calls it (whole waves enter
 // the matrix instructions; the column passes of N_s = 32 synchronise the
 // block); returns this lane's share of the partial sum.
-template <class P, int NS>
+template <class P, int NS, bool PRE>
 __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::real> (&acc)[12], bool valid,
                                              long j, int sl, int r, int s, int nsb,
                                              const ProgLds<typename P::real>& pl, const typename P::real* kap,
-                                             int xmode) {
+                                             int xmode, cpx<typename P::real> (&xv)[12],
+                                             cpx<typename P::real> (&rv)[12], const typename P::real (&rho)[6],
+                                             typename P::real alpha, bool cg_pre) {
   using R = typename P::real;
   constexpr int NSP = NS + 1;
   const int nrhs = a.nrhs;
   auto column = [&](cpx<R>* b, int c) -> cpx<R>& { return b[((size_t)(sl * nrhs + r) * 12 + c) * NSP + s]; };
-  auto program = [&](const DenseArg& dn, const M5Prog& prog, R* lds, cpx<R>(&v)[12]) {
+  auto program = [&](int p, const DenseArg& dn, const M5Prog& prog, R* lds, cpx<R>(&v)[12]) {
     if constexpr (NS <= DENSE_N) {
       if (!dn.tab) return;
-      dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
+      if constexpr (PRE) dense_apply<NS>(v, lds, pl.scr, rho[2 * p], rho[2 * p + 1]);
+      else dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
     } else {
       if (prog.n == 0) return;
       cpx<R>* buf = reinterpret_cast<cpx<R>*>(lds);
@@ -327,11 +352,10 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
     }
   };
 
-  program(a.dn_h, a.prog_h, pl.h, acc);  // N_s = 32: never together with X_LDS
+  program(0, a.dn_h, a.prog_h, pl.h, acc);  // N_s = 32: never together with X_LDS
   const int cgmode = a.partial ? (a.cg_r ? 2 : (a.cg_p ? 3 : 1)) : 0;
-  const bool cg_update = cgmode == 2 && valid && a.scal[r].active;
-  cpx<R> xv[12], rv[12];
-  bool r_loaded = false;
+  const bool cg_update = PRE ? cg_pre : cgmode == 2 && valid && a.scal[r].active;
+  bool r_loaded = PRE;
   const bool has_x = a.xin != nullptr;
   if (has_x) {
     if (xmode == X_LDS) {  // transformed before the hop, still in the column buffer
@@ -340,19 +364,19 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
         for (int c = 0; c < 12; c++) xv[c] = column(reinterpret_cast<cpx<R>*>(pl.h), c);
       }
     } else {
-      if constexpr (NS <= DENSE_N) {
+      if constexpr (NS <= DENSE_N && !PRE) {
 #pragma unroll
         for (int c = 0; c < 12; c++) xv[c] = {R(0), R(0)};
       }
-      if (valid) load_site<P, ODWF_NT_FUSED>(a.xin, a.xin_sc, j, r, s, nrhs, NS, xv);
-      if constexpr (sizeof(R) == 4 && NS <= DENSE_N && !P::SCALED) {
+      if (!PRE && valid) load_site<P, ODWF_NT_FUSED>(a.xin, a.xin_sc, j, r, s, nrhs, NS, xv);
+      if constexpr (!PRE && sizeof(R) == 4 && NS <= DENSE_N && !P::SCALED) {
         // the CG residual travels with the x term: one memory round trip fewer
         if (cg_update) {
           load_site<P, ODWF_NT_FUSED>(a.cg_r, a.cg_r_sc, j, r, s, nrhs, NS, rv);
           r_loaded = true;
         }
       }
-      program(a.dn_x, a.prog_x, pl.x, xv);
+      program(1, a.dn_x, a.prog_x, pl.x, xv);
     }
   }
   if (has_x) {
@@ -370,7 +394,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
 #pragma unroll
     for (int c = 0; c < 12; c++) nval += (double)cnorm2(acc[c]);
   }
-  program(a.dn_o, a.prog_o, pl.o, acc);
+  program(2, a.dn_o, a.prog_o, pl.o, acc);
   if constexpr (NS <= DENSE_N) {
     if (a.diag_o) {
       const R p = (R)a.diag_o[s], m = (R)a.diag_o[NCOEF * NS + NS - 1 - s];
@@ -381,31 +405,38 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
 
   if (cgmode == 3 && valid) {  // residual: out = f - y
     cpx<R> f[12];
-    load_site<P>(a.cg_p, a.cg_p_sc, j, r, s, nrhs, NS, f);
+    if constexpr (PRE) {
+#pragma unroll
+      for (int c = 0; c < 12; c++) f[c] = rv[c];
+    } else {
+      load_site<P>(a.cg_p, a.cg_p_sc, j, r, s, nrhs, NS, f);
+    }
 #pragma unroll
     for (int c = 0; c < 12; c++) {
       acc[c] = csub(f[c], acc[c]);
       nval += (double)cnorm2(acc[c]);
     }
   }
+  void* dst = a.out;
+  float* dst_sc = a.out_sc;
+  bool store = valid && a.out;
   if (cgmode == 2) {
-    if (cg_update) {
-      const R al = (R)a.scal[r].alpha;
-      {  // r -= alpha N p, |r|^2
-        if (!r_loaded) load_site<P, ODWF_NT_FUSED>(a.cg_r, a.cg_r_sc, j, r, s, nrhs, NS, rv);
+    // x += alpha p runs in the vector step after beta (launch_cg_step),
+    // which reads p there anyway
+    dst = a.cg_r;
+    dst_sc = a.cg_r_sc;
+    store = cg_update;
+    if (cg_update) {  // r -= alpha N p, |r|^2
+      const R al = PRE ? alpha : (R)a.scal[r].alpha;
+      if (!r_loaded) load_site<P, ODWF_NT_FUSED>(a.cg_r, a.cg_r_sc, j, r, s, nrhs, NS, rv);
 #pragma unroll
-        for (int c = 0; c < 12; c++) {
-          rv[c] = csub(rv[c], cscale(al, acc[c]));
-          nval += (double)cnorm2(rv[c]);
-        }
-        store_site<P, ODWF_NT_FUSED>(a.cg_r, a.cg_r_sc, j, r, s, nrhs, NS, rv);
+      for (int c = 0; c < 12; c++) {
+        acc[c] = csub(rv[c], cscale(al, acc[c]));
+        nval += (double)cnorm2(acc[c]);
       }
-      // x += alpha p runs in the vector step after beta (launch_cg_step),
-      // which reads p there anyway
     }
-  } else if (valid && a.out) {
-    store_site<P, ODWF_NT_FUSED>(a.out, a.out_sc, j, r, s, nrhs, NS, acc);
   }
+  if (store) store_site<P, ODWF_NT_FUSED>(dst, dst_sc, j, r, s, nrhs, NS, acc);
 
   return nval;
 }
@@ -815,9 +846,225 @@ __global__ void __launch_bounds__(256, (HopWaves<P, NS, PLAIN>::W)) hop_kernel(c
   // the empty asm stops the compiler from reusing the value computed earlier
   int slr = sl;
   asm volatile("" : "+v"(slr));
-  const double nval =
-      fused_tail<P, NS>(a, acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap, x_first ? X_LDS : X_LOAD);
+  cpx<R> xv[12], rv[12];
+  const R rho[6] = {};
+  const double nval = fused_tail<P, NS, false>(a, acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap,
+                                               x_first ? X_LDS : X_LOAD, xv, rv, rho, R(0), false);
   if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, lb);
+}
+
+// ---------------------------------------------------------------------------
+// Small launches: a lattice whose columns do not fill the chip is bound by the
+// chain of latencies of one block, not by traffic.  Here four waves share 64
+// 5D sites: wave mu takes the forward and the backward hop of direction mu (its
+// two neighbours, and its links through LDS of its own, all in flight
+// together), the four partial sums meet in LDS at the only barrier, and wave 0,
+// which has meanwhile requested what the epilogue reads, runs it.  Against the
+// kernel above: a quarter of the hop's arithmetic per wave, one round trip to memory
+// instead of six, four times the waves.
+// ---------------------------------------------------------------------------
+// complex numbers of one wave's links: two of each of the block's sites
+template <int NS>
+constexpr int SMALL_LINKS = 2 * (64 / NS) * 9;
+
+template <class P, bool DAG, int MU, bool FWD>
+__device__ __forceinline__ void small_term(typename Neighbour<P>::V& v, typename P::real sc, bool flip, float one,
+                                           const cpx<typename P::real>* U, cpx<typename P::real> (&acc)[12]) {
+  constexpr int SIG = FWD != DAG ? +1 : -1;
+  if (flip) {
+    if constexpr (P::SCALED) {
+      sc = -sc;
+    } else {
+#pragma unroll
+      for (int c = 0; c < 12; c++) v[c] = {-v[c].re, -v[c].im};
+    }
+  }
+  if constexpr (Neighbour<P>::RAW16) hop_one_h16<MU, SIG>(v, sc, one, U, acc);
+  else if constexpr (P::SCALED) hop_one_scaled<MU, SIG>(v, sc, U, acc);
+  else hop_one<MU, SIG>(v, U, acc);
+}
+template <class P, bool DAG, int MU>
+__device__ __forceinline__ void small_terms(typename Neighbour<P>::V (&v)[2], const typename P::real (&sc)[2], bool flip_f,
+                                            bool flip_b, float one, const cpx<typename P::real>* U,
+                                            cpx<typename P::real> (&acc)[12]) {
+  small_term<P, DAG, MU, true>(v[0], sc[0], flip_f, one, U, acc);
+  small_term<P, DAG, MU, false>(v[1], sc[1], flip_b, one, U + 9, acc);
+}
+
+// The two links (forward, backward) of direction mu of the block's sites into
+// LDS of the calling wave, times -1/2 as in stage_links: matrix 2 site + b.
+// load() requests them, store() writes them.
+template <class P, int NS>
+struct SmallLinks {
+  static constexpr bool FULL = LinkFmt<P>::REALS == 18;
+  static constexpr int K = FULL ? (2 * (64 / NS) * 9 + 63) / 64 : 3;
+  uint4 q[K];
+  __device__ static __forceinline__ int clamp_mat(int m, int nsb) { return min(m, 2 * nsb - 1); }
+  __device__ __forceinline__ void load(const HopArgs& a, uint32_t j0, int nsb, int mu, int l) {
+    const uint4* src = reinterpret_cast<const uint4*>(a.links);
+#pragma unroll
+    for (int k = 0; k < K; k++) {
+      const int m = clamp_mat(FULL ? (l + 64 * k) / 9 : l, nsb), e = FULL ? (l + 64 * k) % 9 : k;
+      q[k] = src[(((long)j0 + (m >> 1)) * 8 + mu + 4 * (m & 1)) * (FULL ? 9 : 3) + e];
+    }
+  }
+  __device__ __forceinline__ void store(cpx<typename P::real>* lw, int nsb, int l) const {
+    if constexpr (FULL) {
+#pragma unroll
+      for (int k = 0; k < K; k++) {
+        cpx<double> z;
+        unpack_chunk<SP64>(q[k], &z);
+        if (l + 64 * k < 2 * nsb * 9) lw[l + 64 * k] = cscale(-0.5, z);
+      }
+    } else if (l < 2 * nsb) {
+      cpx<float> u[6];
+#pragma unroll
+      for (int k = 0; k < 3; k++) unpack_chunk<SP32>(q[k], &u[2 * k]);
+      cpx<float>* d = lw + l * 9;
+#pragma unroll
+      for (int k = 0; k < 6; k++) d[k] = cscale(-0.5f, u[k]);
+#pragma unroll
+      for (int a0 = 0; a0 < 3; a0++) {
+        const int b0 = (a0 + 1) % 3, c0 = (a0 + 2) % 3;
+        const cpx<float> t = csub(cmul(u[b0], u[3 + c0]), cmul(u[c0], u[3 + b0]));
+        d[6 + a0] = {-0.5f * t.re, 0.5f * t.im};
+      }
+    }
+  }
+};
+
+// (two waves per SIMD keep the register budget at 256: above it the compiler
+// puts the matrix results of the dense programs into accumulation registers,
+// and such builds of this kernel gave wrong results)
+template <class P, int NS, bool DAG>
+__global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
+  using R = typename P::real;
+  using N = Neighbour<P>;
+  constexpr int NCG = 12 / P::CPB;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int nrhs = a.nrhs;
+  const int tid = threadIdx.x;
+  uint32_t lb = blockIdx.x;
+  if (a.fin_partial) {  // the first block forms the step lengths
+    if (lb == 0) {
+      fin_block(a, reinterpret_cast<double*>(smem));
+      return;
+    }
+    lb -= 1;
+  }
+  if (!gate_any(a.gate, a.gate_mode, nrhs)) return;  // whole block idle
+  const int mu = uniform_int(tid >> 6), l = tid & 63;
+  const int col = l / NS, s = l - col * NS;
+  const int sl = nrhs == 1 ? col : col / nrhs;
+  const int r = col - sl * nrhs;
+  const uint32_t j0 = lb * a.spb;
+  const int nsb = min(a.spb, a.h - (int)j0);
+  const bool valid = sl < nsb && gate_on(a.gate, a.gate_mode, r);
+  const uint32_t j = j0 + min(sl, nsb - 1);
+
+  // LDS: partial sums of waves 1-3, wave 0's scratch, programs.  Each wave's
+  // links lie where it writes later (its sums, or the scratch)
+  R* sum = reinterpret_cast<R*>(smem);
+  R* scr = sum + 3 * 24 * 64;
+  cpx<R>* lw = reinterpret_cast<cpx<R>*>(mu > 0 ? sum + (mu - 1) * 24 * 64 : scr);
+  static_assert(2 * SMALL_LINKS<NS> <= DENSE_SCRATCH<R> && 2 * SMALL_LINKS<NS> <= 24 * 64, "");
+  R* prog = scr + DENSE_SCRATCH<R>;
+
+  // the two neighbours and links of this wave's direction
+  const int L1 = a.L[1], L2 = a.L[2], L3 = a.L[3];
+  const int hx = a.L[0] >> 1;
+  const int row = a.d_hx.div(j), xh = j - row * hx;
+  const int zt = a.d_y.div(row), y = row - zt * L1;
+  const int t = a.d_z.div(zt), z = zt - t * L2;
+  const int p = (y + z + t + a.out_par) & 1;
+  typename N::V v[2];
+  R sc[2] = {R(1), R(1)};
+  SmallLinks<P, NS> lk;
+  lk.load(a, j0, nsb, mu, l);
+  if (valid) {
+#pragma unroll
+    for (int b = 0; b < 2; b++) {  // forward, backward
+      const bool fwd = b == 0;
+      int xx = xh, yy = y, zz = z, tt = t;
+      // x + 1 lies in column xh (p = 0) or xh + 1 (p = 1), x - 1 in xh - 1 or xh
+      if (mu == 0 && fwd && p) xx = xh + 1 == hx ? 0 : xh + 1;
+      if (mu == 0 && !fwd && !p) xx = xh == 0 ? hx - 1 : xh - 1;
+      if (mu == 1) yy = fwd ? (y + 1 == L1 ? 0 : y + 1) : (y == 0 ? L1 - 1 : y - 1);
+      if (mu == 2) zz = fwd ? (z + 1 == L2 ? 0 : z + 1) : (z == 0 ? L2 - 1 : z - 1);
+      if (mu == 3) tt = fwd ? (t + 1 == L3 ? 0 : t + 1) : (t == 0 ? L3 - 1 : t - 1);
+      const long nj = (long)((tt * L2 + zz) * L1 + yy) * hx + xx;
+      const uint4* src = reinterpret_cast<const uint4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
+      uint4 q[NCG];
+#pragma unroll
+      for (int cg = 0; cg < NCG; cg++) q[cg] = src[cg * NS];
+      N::set(v[b], q);
+      if constexpr (P::SCALED) sc[b] = a.in_sc[(nj * nrhs + r) * NS + s];
+    }
+  }
+  ProgLds<R> pl = {prog, nullptr, nullptr, nullptr};
+  if (a.dn_h.tab) dense_stage<R>(prog, a.dn_h.tab), prog += DENSE_LEN;
+  pl.x = prog;
+  if (a.dn_x.tab) dense_stage<R>(prog, a.dn_x.tab), prog += DENSE_LEN;
+  pl.o = prog;
+  if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab), prog += DENSE_LEN;
+  pl.scr = scr;
+  lk.store(lw, nsb, l);
+  __builtin_amdgcn_wave_barrier();  // the wave's own LDS, in order
+
+  cpx<R> acc[12];
+#pragma unroll
+  for (int c = 0; c < 12; c++) acc[c] = {R(0), R(0)};
+  if (valid) {
+    const float one = N::opaque_one();
+    const cpx<R>* U = lw + sl * 18;
+    const bool flip_f = mu == 3 && a.bc_t < 0 && t + 1 == L3, flip_b = mu == 3 && a.bc_t < 0 && t == 0;
+    switch (mu) {
+      case 0: small_terms<P, DAG, 0>(v, sc, false, false, one, U, acc); break;
+      case 1: small_terms<P, DAG, 1>(v, sc, false, false, one, U, acc); break;
+      case 2: small_terms<P, DAG, 2>(v, sc, false, false, one, U, acc); break;
+      default: small_terms<P, DAG, 3>(v, sc, flip_f, flip_b, one, U, acc); break;
+    }
+  }
+  cpx<R> xv[12], rv[12];
+  R rho[6], alpha = R(0);
+  bool cg_update = false;
+#pragma unroll
+  for (int c = 0; c < 12; c++) xv[c] = rv[c] = {R(0), R(0)};
+#pragma unroll
+  for (int c = 0; c < 6; c++) rho[c] = R(0);
+  // (after the hop: its neighbours, links and these together exceed the registers in FP64)
+  if (mu == 0) tail_preload<P, NS>(a, valid, j, r, s, xv, rv, rho, alpha, cg_update);
+  if (mu > 0) {
+    R* d = sum + (mu - 1) * 24 * 64 + l;
+#pragma unroll
+    for (int c = 0; c < 12; c++) {
+      d[(2 * c) * 64] = acc[c].re;
+      d[(2 * c + 1) * 64] = acc[c].im;
+    }
+  }
+  __syncthreads();
+  if (mu > 0) return;
+#pragma unroll
+  for (int w = 0; w < 3; w++) {
+    const R* d = sum + w * 24 * 64 + l;
+#pragma unroll
+    for (int c = 0; c < 12; c++) acc[c] = cadd(acc[c], cpx<R>{d[(2 * c) * 64], d[(2 * c + 1) * 64]});
+  }
+  double nval = fused_tail<P, NS, true>(a, acc, valid, j, sl, r, s, nsb, pl, nullptr, X_LOAD, xv, rv, rho, alpha,
+                                        cg_update);
+  if (a.partial) {  // one wave: LDS of its own, in order
+    if (!valid) nval = 0.0;
+    for (int m = NS >> 1; m >= 1; m >>= 1) nval += __shfl_xor(nval, m, NS);
+    double* tmp = reinterpret_cast<double*>(smem);
+    __builtin_amdgcn_wave_barrier();
+    if (s == 0) tmp[col] = nval;
+    __builtin_amdgcn_wave_barrier();
+    if (l < nrhs) {
+      double tot = 0.0;
+      for (int k = 0; k < a.spb; k++) tot += tmp[k * nrhs + l];
+      a.partial[(long)lb * nrhs + l] = tot;
+    }
+  }
 }
 
 // extra LDS per block (plain / fused kernels): caps the blocks resident per CU
@@ -846,6 +1093,17 @@ template <class P, int NS>
 static hipError_t launch_hop_t(HopArgs a, int dag, hipStream_t st) {
   const int inner = a.nrhs * NS;
   if (inner > 256 || a.nrhs > MAXRHS) return hipErrorInvalidValue;
+  if constexpr (NS <= DENSE_N) {
+    if (a.small) {
+      using R = typename P::real;
+      const int np = (a.dn_h.tab != nullptr) + (a.dn_x.tab != nullptr) + (a.dn_o.tab != nullptr);
+      const size_t sm = (3 * 24 * 64 + (size_t)np * DENSE_LEN + DENSE_SCRATCH<R>) * sizeof(R);
+      const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0));
+      if (dag) hipLaunchKernelGGL((hop_small_kernel<P, NS, true>), grid, dim3(256), sm, st, a);
+      else hipLaunchKernelGGL((hop_small_kernel<P, NS, false>), grid, dim3(256), sm, st, a);
+      return hipGetLastError();
+    }
+  }
   const int block = (a.spb * inner + 63) & ~63;  // whole waves, <= 256
   const size_t sm = hop_smem<P, NS>(a, a.plain);
   const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0));

@@ -24,8 +24,10 @@ inline Geom geom_of(const int dims[4]) {
 hipError_t launch_hop(const HopArgs& a, int prec, int Ns, hipStream_t st);
 // blocks of a fused launch (one partial sum per block and right-hand side), and
 // sites per block of a launch
-int hop_nblocks(const Geom& g, int nrhs, int Ns);
-int hop_launch_spb(int hx, int nrhs, int Ns, int prec, bool plain);
+int hop_nblocks(const Geom& g, int nrhs, int Ns, int prec);
+int hop_launch_spb(const Geom& g, int nrhs, int Ns, int prec, bool plain);
+// the launch takes the four-wave kernel (plain reduced-precision hops never do)
+bool hop_small(const Geom& g, int nrhs, int Ns, int prec);
 
 // layouts (pack.hip)
 // canonical complex128 [rhs][s][t][z][y][x][4][3] (rhs offset r0, nrhs of them)

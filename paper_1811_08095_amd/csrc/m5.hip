@@ -56,7 +56,7 @@ __global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in
 // store per 5D site, no LDS for the data).  The columns (site, right-hand side)
 // of a half field are consecutive, so a wave takes 64 / N_s of them.
 template <class P, int NS>
-__global__ void __launch_bounds__(256) m5_dense_kernel(const void* in, const float* in_sc, void* out, float* out_sc,
+__global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const float* in_sc, void* out, float* out_sc,
                                                        const void* other, const float* other_sc, double c0,
                                                        double c1, const DenseArg dn, const double* diag, long ncol,
                                                        int nrhs) {

@@ -170,6 +170,7 @@ struct HopArgs {
   int h, nrhs, spb, out_par, bc_t, dag;
   int plain;  // the hop alone: no program, x term, factor or partial sums
   int rows;   // every block is a segment of one x-row
+  int small;  // four waves to 64 lanes of sites
   int L[4];
   int nblocks;
   // block traversal: xcd != 0 gives each of the 8 XCDs a contiguous range of

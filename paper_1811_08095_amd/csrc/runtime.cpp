@@ -284,7 +284,7 @@ hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out
   a.scal = o.scal;
   a.partial = o.partial;
   a.fin_partial = o.fin_partial;
-  a.fin_nblocks = hop_nblocks(L->g, c.nrhs, c.Ns());
+  a.fin_nblocks = hop_nblocks(L->g, c.nrhs, c.Ns(), c.prec);
   a.fin_scal = o.fin_scal;
   a.gate = o.gate;
   a.gate_mode = o.gate ? o.gate_mode : GATE_NONE;
@@ -311,7 +311,8 @@ hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out
     return hipErrorInvalidValue;
   const int hx = a.L[0] / 2;
   a.plain = o.ph.n == 0 && o.po.n == 0 && !o.x && !o.partial && !o.fin_partial && o.ch == 1.0;
-  a.spb = hop_launch_spb(hx, c.nrhs, c.Ns(), c.prec, a.plain);
+  a.spb = hop_launch_spb(L->g, c.nrhs, c.Ns(), c.prec, a.plain);
+  a.small = hop_small(L->g, c.nrhs, c.Ns(), c.prec) && !(a.plain && c.prec != PREC64);
   a.nblocks = (a.h + a.spb - 1) / a.spb;
   a.rows = hx % a.spb == 0 && a.L[0] <= 256;
   traversal(a);

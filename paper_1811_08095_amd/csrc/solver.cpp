@@ -148,6 +148,11 @@ static hipError_t read_scal(const CGScal* d, CGScal* h, int nrhs, hipStream_t st
   return hipStreamSynchronize(st);
 }
 
+// blocks that write partial sums, over the launches of a solve or an engine
+int max_nblocks(const Geom& g, int nrhs, int Ns, int inner) {
+  return std::max({hop_nblocks(g, nrhs, Ns, PREC64), hop_nblocks(g, nrhs, Ns, inner), vec_nblocks(g.h, nrhs, Ns)});
+}
+
 size_t solve_workspace_bytes(const Geom& g, int Ns, int nrhs, int inner) {
   const long h = g.h;
   size_t b = 4 * half_bytes(h, nrhs, Ns, PREC64);  // f, y, two FP64 temporaries
@@ -156,7 +161,7 @@ size_t solve_workspace_bytes(const Geom& g, int Ns, int nrhs, int inner) {
   } else {
     b += 5 * (half_bytes(h, nrhs, Ns, inner) + scale_bytes(h, nrhs, Ns, inner));
   }
-  const int nb = std::max(hop_nblocks(g, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
+  const int nb = max_nblocks(g, nrhs, Ns, inner);
   b += partial_bytes(nb, nrhs) + 64 * 1024;
   return b;
 }
@@ -167,7 +172,7 @@ bool solve_buffers(Workspace& W, const Geom& g, int nrhs, int Ns, int inner, Sol
   if (own_y) B.e1 = W.half("s.e1", h, nrhs, Ns, PREC64);  // y (else the caller's packed field)
   B.e2 = W.half("s.e2", h, nrhs, Ns, PREC64);  // FP64 even scratch / residual
   B.o0 = W.half("s.o0", h, nrhs, Ns, PREC64);  // FP64 odd scratch
-  const int nbmax = std::max(hop_nblocks(g, nrhs, Ns), vec_nblocks(h, nrhs, Ns));
+  const int nbmax = max_nblocks(g, nrhs, Ns, inner);
   B.partial = (double*)W.get("s.partial", partial_bytes(nbmax, nrhs));
   B.scal = (CGScal*)W.get("s.scal", 3 * MAXRHS * sizeof(CGScal));
   B.res = (double*)W.get("s.res", 4 * MAXRHS * sizeof(double));
@@ -193,7 +198,7 @@ static hipError_t true_residual(const OpCtx& c64, const HV& f, const HV& y, cons
   k4.partial = partial;
   k4.cg_p = &f;
   HIPRET(apply_normal(c64, y, t, v, v, nullptr, &k4));
-  return launch_fin(FIN_INIT, partial, hop_nblocks(c64.S->lat->g, c64.nrhs, c64.Ns()), c64.nrhs,
+  return launch_fin(FIN_INIT, partial, hop_nblocks(c64.S->lat->g, c64.nrhs, c64.Ns(), PREC64), c64.nrhs,
                     scal, out, c64.st);
 }
 
@@ -313,7 +318,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
     return launch_fin(FIN_INIT, partial, nb_vec, nrhs, sc, dres, st);
   };
 
-  const int nbh = hop_nblocks(g, nrhs, Ns);
+  const int nbh = hop_nblocks(g, nrhs, Ns, inner), nbh64 = hop_nblocks(g, nrhs, Ns, PREC64);
   auto any = [&](const CGScal* s, int which) {
     for (int r = 0; r < nrhs; r++) {
       if (which == 0 && s[r].active) return true;
@@ -458,7 +463,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
       kd.cg_p = &bp;
       kd.partial = partial;
       CHK(hop(c64, par, 0, par == 0 ? o0 : e1, nullptr, kd));
-      CHK(launch_fin(FIN_SUM, partial, nbh, nrhs, nullptr, dres + par * MAXRHS, st));
+      CHK(launch_fin(FIN_SUM, partial, nbh64, nrhs, nullptr, dres + par * MAXRHS, st));
     }
     // x = (1 + L)^{-1} y
     CHK(unpack(c64, &e1, &o0, x, r0, prog_1pl_inv()));

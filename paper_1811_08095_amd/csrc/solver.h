@@ -36,6 +36,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
                         int nrhs, int inner, int maxiter, const void* b, void* x, int use_x0,
                         odwf_stats* stats, hipStream_t st, const SolveIO& io = SolveIO());
 
+int max_nblocks(const Geom& g, int nrhs, int Ns, int inner);
 size_t solve_workspace_bytes(const Geom& g, int Ns, int nrhs, int inner);
 
 // device buffers of a solve chunk of nrhs right-hand sides (named workspace
