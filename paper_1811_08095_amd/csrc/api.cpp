@@ -554,25 +554,8 @@ extern "C" odwf_status odwf_force(odwf_solver S, const void* chi, const void* ps
   HIPCHK(hipSetDevice(S->lat->device));
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   std::lock_guard<std::mutex> lk(S->mtx);
-  Workspace& W = S->workspace(st);
-  const Geom& g = S->lat->g;
-  const int Ns = S->Ns;
-  HV ce = W.half("f.ce", g.h, 1, Ns, PREC64), co = W.half("f.co", g.h, 1, Ns, PREC64);
-  HV pe = W.half("f.pe", g.h, 1, Ns, PREC64), po = W.half("f.po", g.h, 1, Ns, PREC64);
-  if (!ce.d || !co.d || !pe.d || !po.d) {
-    set_error("odwf_force: out of device memory for workspaces");
-    return ODWF_ENOMEM;
-  }
-  OpCtx c;
-  c.S = S;
-  c.st = st;
-  c.prec = PREC64;
-  c.nrhs = 1;
-  for (int r = 0; r < MAXRHS; r++) c.kappa[r] = 0.0;
-  HIPCHK(pack(c, chi, 0, &ce, &co));
-  HIPCHK(pack(c, psi, 0, &pe, &po));
-  HIPCHK(launch_force(ce.d, pe.d, co.d, po.d, S->lat->U64[0], F, 0, Ns, S->lat->bc_t, accumulate, g, st));
-  HIPCHK(launch_force(co.d, po.d, ce.d, pe.d, S->lat->U64[1], F, 1, Ns, S->lat->bc_t, accumulate, g, st));
+  const void* const links[2] = {S->lat->U64[0], S->lat->U64[1]};
+  HIPCHK(launch_force(chi, psi, links, F, S->Ns, S->lat->bc_t, accumulate, S->lat->g, st));
   return ODWF_OK;
 }
 

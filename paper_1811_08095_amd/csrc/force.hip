@@ -15,177 +15,302 @@
 //
 // In the chiral basis sum_spin [(1 - s gamma) p] (x) c^dag = h_p (x) h_c^dag
 // with h the same half-spinor projection of p and of c, so a lane forms each
-// outer product from two 2 x 3 half spinors.  Thread layout as in the hopping
-// kernel: a block holds 256 / Ns sites of one parity with Ns lanes each (s
-// fastest); the lanes of a site add their 3 x 3 products over s through LDS in
-// a fixed order (deterministic), then the site's lanes form the nine entries
-// of TA(U M) and write (or add to) the canonical force field.  FP64 throughout.
+// outer product from two 2 x 3 half spinors.
+//
+// chi and psi are read in the canonical layout (a slice's 12 components of
+// consecutive sites are contiguous), without a packed copy.  A block takes 16
+// consecutive sites, lane = (site, mu); each of its two waves walks every
+// second slice, so M stays in the lane's registers and nothing is reduced
+// across lanes.  Per slice a wave brings the 16 sites, their forward neighbours
+// in y, z and t and the at most two x neighbours outside the block (25 KB of
+// both fields) through LDS of its own: whole runs of the canonical layout on
+// the way in, one 16-byte chunk a lane on the way out, slots padded so that the
+// lanes meet different banks.  The next slice's chunks travel while a slice is
+// used (25 loads of 16 bytes in flight a lane; three blocks a CU by LDS).  The
+// waves' sums meet at the end and the lane writes (or adds to) its link's nine
+// entries.  FP64 throughout.
+// Bound: L2 fills (1.6 GB for 0.95 GB of fields, links and forces at 16^3 x 32 x
+// 16, 4.7 TB/s) and, one after the other, the LDS passes of six waves a CU.
+// 16^3 x 32 x 16: 353 us, against 2 x 418 us of one launch per parity with the
+// sum over s through LDS and 278 us for the packed copies; 445 us with every x
+// neighbour brought as well, two blocks a CU and rotated slots (twice the bank
+// conflicts), 376 us with 2 x 2 (z, t) planes for the tiles of the walk.
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace odwf {
 
+constexpr int FS = 16;               // sites of a block
+constexpr int FSLOTS = 4 * FS + 2;   // own sites, y, z, t neighbours, two x neighbours
+constexpr int FLOADS = (FSLOTS * 12 + 63) / 64;  // chunks a lane brings, per field and slice
+// first chunk of slot q in LDS: 16 lanes (four sites by four directions) that
+// read the same component of their slots meet 16 different 16-byte banks
+__host__ __device__ constexpr int slot_at(int q) { return 12 * q + 2 * (q >> 2) + (q >> 4); }
+constexpr int FCH = slot_at(FSLOTS - 1) + 12;    // chunks of a field
+
 struct ForceArgs {
-  const void* chi_own;   // chi on the sites of the output parity
-  const void* psi_own;
-  const void* chi_nb;    // chi on the opposite parity
-  const void* psi_nb;
-  const void* links;     // FP64 links of the output parity [h][8][18]
+  const uint4* chi;      // canonical [s][site][12] complex128
+  const uint4* psi;
+  const void* links[2];  // FP64 links by parity, [h][8][18]
   cpx<double>* F;        // canonical [t][z][y][x][mu][3][3]
   int L[4];
-  int h, Ns, par, bc_t, accumulate;
+  FastDiv dx, dy, dz;    // Lx, Ly, Lz
+  long V;
+  uint32_t unit, units;  // blocks of a unit of the walk (0: linear), units of an (x, y) plane
+  uint32_t tile[3];      // units, z and t of a tile
+  int Ns, bc_t, accumulate;
 };
 
-// partial[b][a] += sum_sigma hp[sigma][b] conj(hc[sigma][a])
+// m[b][a] += sum_sigma hp[sigma][b] conj(hc[sigma][a]), or its adjoint
+template <bool ADJ>
 __device__ __forceinline__ void outer_acc(const cpx<double> (&hp)[6], const cpx<double> (&hc)[6],
                                           cpx<double> (&m)[9]) {
 #pragma unroll
   for (int b = 0; b < 3; b++)
 #pragma unroll
     for (int a = 0; a < 3; a++) {
-      cpx<double> v = m[b * 3 + a];
+      cpx<double> v = m[ADJ ? a * 3 + b : b * 3 + a];
 #pragma unroll
       for (int sg = 0; sg < 2; sg++) {
         const cpx<double> p = hp[sg * 3 + b], c = hc[sg * 3 + a];
-        v.re += p.re * c.re + p.im * c.im;
-        v.im += p.im * c.re - p.re * c.im;
+        v.re = fma(p.re, c.re, v.re);
+        v.re = fma(p.im, c.im, v.re);
+        v.im = fma(ADJ ? -p.im : p.im, c.re, v.im);
+        v.im = fma(ADJ ? p.re : -p.re, c.im, v.im);
       }
-      m[b * 3 + a] = v;
+      m[ADJ ? a * 3 + b : b * 3 + a] = v;
     }
 }
 
-template <int MU>
-__device__ __forceinline__ void link_products(const cpx<double> (&pn)[12], const cpx<double> (&cn)[12],
-                                              const cpx<double> (&po)[12], const cpx<double> (&co)[12],
-                                              cpx<double> (&A)[9], cpx<double> (&B)[9]) {
-  cpx<double> hp[6], hc[6];
-  project<MU, +1>(pn, hp);  // (1 - gamma_mu) psi(x + mu)
-  project<MU, +1>(co, hc);  // with chi(x)
-  outer_acc(hp, hc, A);
-  project<MU, -1>(po, hp);  // (1 + gamma_mu) psi(x)
-  project<MU, -1>(cn, hc);  // with chi(x + mu)
-  outer_acc(hp, hc, B);
+// The lane's direction as data: gamma_mu = [[0, B], [B^dag, 0]], row r of B has
+// one entry f_r at column p_r.  f z for f in {+-1, +-i} is z or (im, re) with a
+// sign for each part, so the lanes of all four directions run the same code:
+// the parts are picked by LDS address, the signs enter as factors +-1.
+struct Dir {
+  int p[2];        // column p_r
+  int im[2];       // f_r imaginary
+  double s[2][2];  // signs of the real and imaginary part of f_r z
+};
+__device__ __forceinline__ Dir dir_of(int mu) {
+  Dir d;
+  d.p[0] = mu < 2 ? 1 : 0;  // x, y: p = (1, 0); z, t: p = (0, 1)
+  d.p[1] = 1 - d.p[0];
+  // f: x (-i, -i), y (-1, +1), z (-i, +i), t (+1, +1);  -i z = (im, -re), +i z = (-im, re)
+  d.im[0] = d.im[1] = mu == 0 || mu == 2;
+  d.s[0][0] = mu == 1 ? -1.0 : 1.0;
+  d.s[0][1] = mu == 3 ? 1.0 : -1.0;
+  d.s[1][0] = mu == 2 ? -1.0 : 1.0;
+  d.s[1][1] = mu == 0 ? -1.0 : 1.0;
+  return d;
 }
 
-__global__ void __launch_bounds__(256) force_kernel(const ForceArgs a) {
-  __shared__ double red[256 * 18];
-  __shared__ double msum[64 * 18];
-  const int Ns = a.Ns;
-  const int spb = 256 / Ns;
-  const int tid = threadIdx.x;
-  const int sl = tid / Ns, s = tid - sl * Ns;
-  const long j = (long)blockIdx.x * spb + sl;
-  const bool valid = j < a.h;
-  const int L0 = a.L[0], L1 = a.L[1], L2 = a.L[2], L3 = a.L[3];
-  const int hx = L0 >> 1;
-  int x = 0, y = 0, z = 0, t = 0;
-  cpx<double> po[12], co[12];
-  if (valid) {
-    const int xh = (int)(j % hx);
-    long rest = j / hx;
-    y = (int)(rest % L1);
-    rest /= L1;
-    z = (int)(rest % L2);
-    t = (int)(rest / L2);
-    x = 2 * xh + ((y + z + t + a.par) & 1);
-    load_site<SP64>(a.psi_own, nullptr, j, 0, s, 1, Ns, po);
-    load_site<SP64>(a.chi_own, nullptr, j, 0, s, 1, Ns, co);
+// half spinor psi_up - SIG B psi_dn of (1 - SIG gamma_mu) of the spinor in slot q
+template <int SIG>
+__device__ __forceinline__ void slot_half(const double* slot, const Dir& d, cpx<double> (&h)[6]) {
+  constexpr double S = SIG > 0 ? -1.0 : 1.0;
+#pragma unroll
+  for (int r = 0; r < 2; r++)
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      const double* up = slot + (r * 3 + c) * 2;
+      const double* dn = slot + ((2 + d.p[r]) * 3 + c) * 2;
+      h[r * 3 + c] = {fma(S * d.s[r][0], dn[d.im[r]], up[0]), fma(S * d.s[r][1], dn[1 - d.im[r]], up[1])};
+    }
+}
+
+// M += A + B^dag of one slice for the lane's link (site at q, neighbour at n)
+__device__ __forceinline__ void link_slice(const double* chi, const double* psi, int q, int n, const Dir& d,
+                                           cpx<double> (&m)[9]) {
+  cpx<double> hp[6], hc[6];
+  slot_half<+1>(psi + n, d, hp);  // (1 - gamma_mu) psi(x + mu)
+  slot_half<+1>(chi + q, d, hc);  // with chi(x)
+  outer_acc<false>(hp, hc, m);
+  slot_half<-1>(psi + q, d, hp);  // (1 + gamma_mu) psi(x)
+  slot_half<-1>(chi + n, d, hc);  // with chi(x + mu)
+  outer_acc<true>(hp, hc, m);
+}
+
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// first site of this block: XCD b % 8 takes a contiguous range of the walk, and
+// the walk takes the smallest runs of rows that are whole blocks (units) in
+// tiles of (y, z, t), so that forward neighbours meet in its L2
+__device__ __forceinline__ uint32_t force_first_site(const ForceArgs& a) {
+  const uint32_t nb8 = gridDim.x >> 3, rem8 = gridDim.x & 7, xcd = blockIdx.x & 7;
+  uint32_t lb = xcd * nb8 + min(xcd, rem8) + (blockIdx.x >> 3);
+  if (a.unit > 0) {
+    auto split = [](uint32_t& n, uint32_t d) {  // n mod d, n <- n / d
+      const uint32_t q = n / d, r = n - q * d;
+      n = q;
+      return r;
+    };
+    const uint32_t in = split(lb, a.unit);
+    uint32_t y = split(lb, a.tile[0]), z = split(lb, a.tile[1]), t = split(lb, a.tile[2]);
+    y += split(lb, a.units / a.tile[0]) * a.tile[0];
+    z += split(lb, a.L[2] / a.tile[1]) * a.tile[1];
+    t += lb * a.tile[2];
+    lb = ((t * a.L[2] + z) * a.units + y) * a.unit + in;
+  }
+  return lb * FS;
+}
+
+__global__ void __launch_bounds__(128, 2) force_kernel(const ForceArgs a) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  __shared__ int slot_site[FSLOTS];
+  __shared__ int x_slot[FS];  // LDS position of x + 1 per site
+  const int tid = threadIdx.x, w = tid >> 6, l = tid & 63;
+  const uint32_t i0 = force_first_site(a);
+  const int n = (int)min((long)FS, a.V - (long)i0);
+  // sites of the slots
+  if (tid < 4 * FS) {
+    const uint32_t k = min(tid % FS, n - 1), i = i0 + k;
+    const uint32_t row = a.dx.div(i), x = i - row * a.dx.d;
+    const uint32_t zt = a.dy.div(row), y = row - zt * a.dy.d;
+    const uint32_t t = a.dz.div(zt), z = zt - t * a.dz.d;
+    const int dir = tid / FS;  // 0: the site itself
+    const int yy = dir == 1 ? (y + 1 == a.L[1] ? 0 : y + 1) : y;
+    const int zz = dir == 2 ? (z + 1 == a.L[2] ? 0 : z + 1) : z;
+    const int tt = dir == 3 ? (t + 1 == a.L[3] ? 0 : t + 1) : t;
+    slot_site[tid] = ((tt * a.L[2] + zz) * a.L[1] + yy) * a.L[0] + x;
+    if (dir == 0) {
+      // x + 1 lies in the block, but for the last site (its neighbour is the next
+      // block's first) and for the end of a row that began before the block
+      const bool wrap = (int)x + 1 == a.L[0];
+      const uint32_t ix = wrap ? i - x : i + 1;
+      const bool in = ix >= i0 && ix < i0 + n;
+      const int extra = 4 * FS + (wrap ? 0 : 1);
+      x_slot[tid] = slot_at(in ? (int)(ix - i0) : extra);
+    }
+    if (tid == 0) {
+      // the row the block begins in, and the site behind the block (clamped:
+      // where there is none, no lane uses the slot)
+      slot_site[4 * FS] = i - x;
+      slot_site[4 * FS + 1] = (int)min((long)i0 + n, a.V - 1);
+    }
+  }
+  __syncthreads();
+  u32x4* buf = reinterpret_cast<u32x4*>(smem) + w * 2 * FCH;
+  // this lane's chunks of a slice: index within a field, and LDS position
+  uint32_t off[FLOADS];
+  uint16_t put[FLOADS];
+#pragma unroll
+  for (int k = 0; k < FLOADS; k++) {
+    const int e = min(l + 64 * k, FSLOTS * 12 - 1), q = e / 12, c = e % 12;
+    off[k] = (uint32_t)slot_site[q] * 12 + c;
+    put[k] = (uint16_t)(slot_at(q) + c);
+  }
+  const int site = l >> 2, mu = l & 3;
+  const int own = 2 * slot_at(site), nb = 2 * (mu == 0 ? x_slot[site] : slot_at(FS * mu + site));
+  cpx<double> m[9];
+#pragma unroll
+  for (int k = 0; k < 9; k++) m[k] = {0.0, 0.0};
+  const Dir d = dir_of(mu);
+  const u32x4* chi0 = reinterpret_cast<const u32x4*>(a.chi);
+  const u32x4* psi0 = reinterpret_cast<const u32x4*>(a.psi);
+  u32x4 v[2][FLOADS];
+  const long first = (long)min(w, a.Ns - 1) * a.V * 12;
+#pragma unroll
+  for (int k = 0; k < FLOADS; k++) {
+    v[0][k] = chi0[first + off[k]];
+    v[1][k] = psi0[first + off[k]];
   }
 #pragma unroll 1
-  for (int mu = 0; mu < 4; mu++) {
-    cpx<double> A[9], B[9];
+  for (int s = w; s < a.Ns; s += 2) {
+    __builtin_amdgcn_wave_barrier();  // LDS of this wave, in order
 #pragma unroll
-    for (int k = 0; k < 9; k++) A[k] = B[k] = {0.0, 0.0};
-    double bs = 1.0;
-    if (valid) {
-      int xx = x, yy = y, zz = z, tt = t;
-      if (mu == 0) xx = x + 1 == L0 ? 0 : x + 1;
-      if (mu == 1) yy = y + 1 == L1 ? 0 : y + 1;
-      if (mu == 2) zz = z + 1 == L2 ? 0 : z + 1;
-      if (mu == 3) {
-        tt = t + 1 == L3 ? 0 : t + 1;
-        if (t + 1 == L3 && a.bc_t < 0) bs = -1.0;
-      }
-      const long nj = (((long)tt * L2 + zz) * L1 + yy) * hx + (xx >> 1);
-      cpx<double> pn[12], cn[12];
-      load_site<SP64>(a.psi_nb, nullptr, nj, 0, s, 1, Ns, pn);
-      load_site<SP64>(a.chi_nb, nullptr, nj, 0, s, 1, Ns, cn);
-      switch (mu) {
-        case 0: link_products<0>(pn, cn, po, co, A, B); break;
-        case 1: link_products<1>(pn, cn, po, co, A, B); break;
-        case 2: link_products<2>(pn, cn, po, co, A, B); break;
-        default: link_products<3>(pn, cn, po, co, A, B); break;
-      }
+    for (int k = 0; k < FLOADS; k++) {  // (the clamped lanes write one value to one place)
+      buf[put[k]] = v[0][k];
+      buf[FCH + put[k]] = v[1][k];
     }
-    // this lane's share of M = -1/2 b (A + B^dag), then the sum over s
-    __syncthreads();  // red and msum of the previous direction are consumed
+    __builtin_amdgcn_wave_barrier();
+    const long next = (long)min(s + 2, a.Ns - 1) * a.V * 12;  // (the last slice again behind the end)
 #pragma unroll
-    for (int b = 0; b < 3; b++)
-#pragma unroll
-      for (int c = 0; c < 3; c++) {
-        const cpx<double> v = {-0.5 * bs * (A[b * 3 + c].re + B[c * 3 + b].re),
-                               -0.5 * bs * (A[b * 3 + c].im - B[c * 3 + b].im)};
-        red[tid * 18 + (b * 3 + c) * 2] = v.re;
-        red[tid * 18 + (b * 3 + c) * 2 + 1] = v.im;
-      }
-    __syncthreads();
-    for (int q = tid; q < spb * 18; q += blockDim.x) {
-      const int site = q / 18, k = q - site * 18;
-      double acc = 0.0;
-      for (int u = 0; u < Ns; u++) acc += red[(site * Ns + u) * 18 + k];
-      msum[q] = acc;
+    for (int k = 0; k < FLOADS; k++) {
+      v[0][k] = chi0[next + off[k]];
+      v[1][k] = psi0[next + off[k]];
     }
-    __syncthreads();
-    // F = TA(U M): the Ns lanes of a site write entries e = s, s + Ns, ... < 9
-    for (int e = s; valid && e < 9; e += Ns) {
-      const int ra = e / 3, cb = e - ra * 3;
-      const double* m = msum + sl * 18;
-      const cpx<double>* U = reinterpret_cast<const cpx<double>*>(a.links) + (j * 8 + mu) * 9;
-      auto X = [&](int r, int c) {  // (U M)[r][c]
-        cpx<double> v = {0.0, 0.0};
+    const double* lds = reinterpret_cast<const double*>(buf);
+    link_slice(lds, lds + 2 * FCH, own, nb, d, m);
+  }
+  // the waves' sums
+  __syncthreads();
+  double* red = reinterpret_cast<double*>(smem);
+  if (w == 1) {
 #pragma unroll
-        for (int k = 0; k < 3; k++) {
-          const cpx<double> u = U[r * 3 + k], w = {m[(k * 3 + c) * 2], m[(k * 3 + c) * 2 + 1]};
-          v = cfma(u, w, v);
-        }
-        return v;
-      };
-      const cpx<double> xab = X(ra, cb), xba = X(cb, ra);
-      cpx<double> f = {0.5 * (xab.re - xba.re), 0.5 * (xab.im + xba.im)};
-      if (ra == cb) {  // minus tr(X - X^dag) / 6 = i Im tr(X) / 3
-        double imtr = 0.0;
-#pragma unroll
-        for (int k = 0; k < 3; k++) imtr += X(k, k).im;
-        f.im -= imtr / 3.0;
-      }
-      const long site = (((long)t * L2 + z) * L1 + y) * L0 + x;
-      cpx<double>* dst = a.F + (site * 4 + mu) * 9 + e;
-      if (a.accumulate) f = cadd(*dst, f);
-      *dst = f;
+    for (int k = 0; k < 9; k++) {
+      red[(2 * k) * 64 + l] = m[k].re;
+      red[(2 * k + 1) * 64 + l] = m[k].im;
     }
   }
+  __syncthreads();
+  if (w == 1 || site >= n) return;
+  const uint32_t i = i0 + site;
+  const uint32_t row = a.dx.div(i), x = i - row * a.dx.d;
+  const uint32_t zt = a.dy.div(row), y = row - zt * a.dy.d;
+  const uint32_t t = a.dz.div(zt), z = zt - t * a.dz.d;
+  const double f = mu == 3 && a.bc_t < 0 && t + 1 == (uint32_t)a.L[3] ? 0.5 : -0.5;  // M = -1/2 b (A + B^dag)
+#pragma unroll
+  for (int k = 0; k < 9; k++) {
+    m[k].re = f * (m[k].re + red[(2 * k) * 64 + l]);
+    m[k].im = f * (m[k].im + red[(2 * k + 1) * 64 + l]);
+  }
+  // F = TA(U M)
+  const uint32_t j = row * (a.dx.d >> 1) + (x >> 1);
+  const uint4* up = reinterpret_cast<const uint4*>((x + y + z + t) & 1 ? a.links[1] : a.links[0]) + ((long)j * 8 + mu) * 9;
+  cpx<double> U[9], X[9];
+#pragma unroll
+  for (int k = 0; k < 9; k++) unpack_chunk<SP64>(up[k], &U[k]);
+#pragma unroll
+  for (int r = 0; r < 3; r++)
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      cpx<double> q = cmul(U[r * 3], m[c]);
+      q = cfma(U[r * 3 + 1], m[3 + c], q);
+      X[r * 3 + c] = cfma(U[r * 3 + 2], m[6 + c], q);
+    }
+  const double imtr = (X[0].im + X[4].im + X[8].im) / 3.0;  // - tr(X - X^dag) / 6
+  cpx<double>* dst = a.F + ((long)i * 4 + mu) * 9;
+#pragma unroll
+  for (int r = 0; r < 3; r++)
+#pragma unroll
+    for (int c = 0; c < 3; c++) {
+      cpx<double> q = {0.5 * (X[r * 3 + c].re - X[c * 3 + r].re), 0.5 * (X[r * 3 + c].im + X[c * 3 + r].im)};
+      if (r == c) q.im -= imtr;
+      if (a.accumulate) q = cadd(dst[r * 3 + c], q);
+      dst[r * 3 + c] = q;
+    }
 }
 
-hipError_t launch_force(const void* chi_own, const void* psi_own, const void* chi_nb, const void* psi_nb,
-                        const void* links, void* F, int par, int Ns, int bc_t, int accumulate, const Geom& g,
-                        hipStream_t st) {
+hipError_t launch_force(const void* chi, const void* psi, const void* const links[2], void* F, int Ns, int bc_t,
+                        int accumulate, const Geom& g, hipStream_t st) {
+  if (Ns < 1 || g.V * 12 > 0xffffffffL) return hipErrorInvalidValue;  // 32-bit chunk offsets within a slice
   ForceArgs a;
-  a.chi_own = chi_own;
-  a.psi_own = psi_own;
-  a.chi_nb = chi_nb;
-  a.psi_nb = psi_nb;
-  a.links = links;
+  a.chi = reinterpret_cast<const uint4*>(chi);
+  a.psi = reinterpret_cast<const uint4*>(psi);
+  a.links[0] = links[0];
+  a.links[1] = links[1];
   a.F = reinterpret_cast<cpx<double>*>(F);
   for (int d = 0; d < 4; d++) a.L[d] = g.L[d];
-  a.h = (int)g.h;
+  a.dx = FastDiv(g.L[0]);
+  a.dy = FastDiv(g.L[1]);
+  a.dz = FastDiv(g.L[2]);
+  a.V = g.V;
+  int rows = 1;  // of a unit
+  while (g.L[0] * rows % FS) rows *= 2;
+  a.unit = a.units = 0;
+  if (g.L[1] % rows == 0) {
+    a.unit = g.L[0] * rows / FS;
+    a.units = g.L[1] / rows;
+    auto tile = [](int n) { return n % 4 == 0 ? 4u : (n % 2 == 0 ? 2u : 1u); };
+    a.tile[0] = rows >= 4 ? 1 : tile(a.units);
+    a.tile[1] = tile(g.L[2]);
+    a.tile[2] = tile(g.L[3]);
+  }
   a.Ns = Ns;
-  a.par = par;
   a.bc_t = bc_t;
   a.accumulate = accumulate;
-  if (Ns < 4 || Ns > 32 || (Ns & (Ns - 1))) return hipErrorInvalidValue;
-  const int spb = 256 / Ns;
-  const dim3 grid((unsigned)((g.h + spb - 1) / spb));
-  hipLaunchKernelGGL(force_kernel, grid, dim3(256), 0, st, a);
+  const dim3 grid((unsigned)((g.V + FS - 1) / FS));
+  hipLaunchKernelGGL(force_kernel, grid, dim3(128), 4 * FCH * sizeof(uint4), st, a);
   return hipGetLastError();
 }
 
