@@ -111,9 +111,8 @@ extern "C" odwf_status odwf_lattice_load_gauge(odwf_lattice L, const void* U, in
       set_error("odwf_lattice_load_gauge: out of device memory");
       return ODWF_ENOMEM;
     }
-    HIPCHK(launch_pack_gauge(src, L->U64[p], p, PREC64, L->g, st));
-    HIPCHK(launch_pack_gauge(src, L->U32[p], p, PREC32, L->g, st));
   }
+  HIPCHK(launch_pack_gauge(src, L->U64, L->U32, L->g, st));
   if (tmp) {
     HIPCHK(hipStreamSynchronize(st));
     HIPCHK(hipFree(tmp));

@@ -50,9 +50,9 @@ hipError_t launch_unpack(int prec, const HalfIO& e, const HalfIO& o, void* canon
 // slice 0, plus into slice Ns - 1, zeros elsewhere); project back
 hipError_t launch_boundary_embed(const void* q, void* f, int nrhs, int Ns, const Geom& g, hipStream_t st);
 hipError_t launch_boundary_project(const void* f, void* q, int nrhs, int Ns, const Geom& g, hipStream_t st);
-// gauge: canonical complex128 [t][z][y][x][mu][3][3] -> per-parity link
-// arrays [h][8][18 doubles] (prec64) or [h][8][12 floats] (reduced)
-hipError_t launch_pack_gauge(const void* canon, void* out, int par, int prec, const Geom& g,
+// gauge: canonical complex128 [t][z][y][x][mu][3][3] -> link arrays of both
+// parities, [h][8][18 doubles] and [h][8][12 floats]
+hipError_t launch_pack_gauge(const void* canon, void* const out64[2], void* const out32[2], const Geom& g,
                              hipStream_t st);
 
 // fifth-dimension programs on a half field (m5.hip):
