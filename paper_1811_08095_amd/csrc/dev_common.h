@@ -97,6 +97,18 @@ __device__ __forceinline__ uint16_t f_to_bf16(float f) {
 }
 
 // unpack one 16-byte chunk into CPB complex values
+// A 16-byte load that stays one: where only the two doubles of a chunk are used,
+// the compiler takes two loads of 8 bytes, each of which passes the same cache
+// lines through L1 again.  The empty asm uses the chunk as a whole, at the point
+// where its value is needed.  FP64 hops (230 -> 129 vector memory instructions a
+// wave): 32^3 x 16 x 16 755 / 784 -> about 640 us, normal operator of
+// 16^4 x 16 495 -> 448 us a call.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ uint4 whole_chunk(u32x4 w) {
+  asm("" : "+v"(w));
+  return make_uint4(w.x, w.y, w.z, w.w);
+}
+
 template <class P>
 __device__ __forceinline__ void unpack_chunk(const uint4 q, cpx<typename P::real>* v);
 
@@ -180,26 +192,25 @@ struct HalfView {
 };
 
 // load the 12 components of 5D site (j, r, s); NT = 1: nontemporal loads
-// (a stream read once, which should not displace re-used rows from L2)
-template <class P, int NT = 0>
+// (a stream read once, which should not displace re-used rows from L2); NOW:
+// the values are needed at once (else they may travel on behind this call)
+template <class P, int NT = 0, bool NOW = true>
 __device__ __forceinline__ void load_site(const void* base, const float* scale, long j, int r, int s,
                                           int nrhs, int Ns, cpx<typename P::real> (&v)[12]) {
   constexpr int NCG = 12 / P::CPB;
-  const uint4* b = reinterpret_cast<const uint4*>(base);
+  const u32x4* b = reinterpret_cast<const u32x4*>(base);
   const long off = ((j * nrhs + r) * NCG) * Ns + s;
-  uint4 q[NCG];
+  u32x4 q[NCG];
 #pragma unroll
   for (int cg = 0; cg < NCG; cg++) {
-    if constexpr (NT) {
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(b + off + cg * Ns));
-      q[cg] = make_uint4(w.x, w.y, w.z, w.w);
-    } else {
-      q[cg] = b[off + cg * Ns];
-    }
+    if constexpr (NT) q[cg] = __builtin_nontemporal_load(b + off + cg * Ns);
+    else q[cg] = b[off + cg * Ns];
   }
 #pragma unroll
-  for (int cg = 0; cg < NCG; cg++) unpack_chunk<P>(q[cg], &v[cg * P::CPB]);
+  for (int cg = 0; cg < NCG; cg++) {
+    if constexpr (NOW && P::CPB == 1) unpack_chunk<P>(whole_chunk(q[cg]), &v[cg * P::CPB]);
+    else unpack_chunk<P>(make_uint4(q[cg].x, q[cg].y, q[cg].z, q[cg].w), &v[cg * P::CPB]);
+  }
   if constexpr (P::SCALED) {
     float sc = scale[(j * nrhs + r) * Ns + s];
 #pragma unroll
@@ -234,7 +245,6 @@ __device__ __forceinline__ void store_site(void* base, float* scale, long j, int
   for (int cg = 0; cg < NCG; cg++) {
     const uint4 q = pack_chunk<P>(&v[cg * P::CPB], inv);
     if constexpr (NT) {
-      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
       const u32x4 w = {q.x, q.y, q.z, q.w};
       __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(b + off + cg * Ns));
     } else {
@@ -499,6 +509,7 @@ struct Mfma<float> {
   using V = mfma_f32x4;
   static constexpr int ROW = 20;           // scratch: reals between two rows of 16 slots
   static constexpr int SET = 12 * ROW;     // reals between two sets
+  __device__ static __forceinline__ int swap(int) { return 0; }
   // register v of lane group g is result row 4 g + v: row = 4 set + real
   __device__ static __forceinline__ int set_of(int row) { return row >> 2; }
   __device__ static __forceinline__ int real_of(int row) { return row & 3; }
@@ -511,6 +522,9 @@ struct Mfma<double> {
   using V = mfma_f64x4;
   static constexpr int ROW = 18;
   static constexpr int SET = 12 * ROW + 24;
+  // sets 2 and 3 keep the halves of a row swapped: sets 0 / 2 and 1 / 3, which lie
+  // on the same banks, are read together
+  __device__ static __forceinline__ int swap(int set) { return (set & 2) << 2; }
   // register v of lane group g is result row 4 v + g: row = 4 real + set
   __device__ static __forceinline__ int set_of(int row) { return row & 3; }
   __device__ static __forceinline__ int real_of(int row) { return row >> 2; }
@@ -553,9 +567,9 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
   using V = typename M::V;
   constexpr int NN = DENSE_N * DENSE_N;
   const int lane = threadIdx.x & 63, slot = lane & 15, k = lane >> 4;
-  R* put = scr + k * M::SET + slot;
+  R* put = scr + k * M::SET + (slot ^ M::swap(k));
   const int set_i = M::set_of(slot);
-  const R* get = scr + set_i * M::SET + M::real_of(slot) * M::ROW + 4 * k;
+  const R* get = scr + set_i * M::SET + M::real_of(slot) * M::ROW + ((4 * k) ^ M::swap(set_i));
   const int src = 16 * set_i + 4 * k;  // a lane of the operand element's column
   const R rho[2] = {__shfl(rho_p, src, 64), __shfl(rho_m, src, 64)};
   const bool same = slot / NS == 4 * k / NS;  // result slot and operand slots belong to one column

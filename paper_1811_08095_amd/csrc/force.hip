@@ -130,7 +130,6 @@ __device__ __forceinline__ void link_slice(const double* chi, const double* psi,
   outer_acc<true>(hp, hc, m);
 }
 
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // first site of this block: XCD b % 8 takes a contiguous range of the walk, and
 // the walk takes the smallest runs of rows that are whole blocks (units) in

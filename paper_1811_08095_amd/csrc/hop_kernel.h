@@ -306,10 +306,10 @@ __device__ __forceinline__ void tail_preload(const HopArgs& a, bool valid, long 
   }
   cg_update = a.partial && a.cg_r && valid && a.scal[r].active;
   alpha = cg_update ? (R)a.scal[r].alpha : R(0);
-  if (a.xin && valid) load_site<P, ODWF_NT_FUSED>(a.xin, a.xin_sc, j, r, s, a.nrhs, NS, xv);
+  if (a.xin && valid) load_site<P, ODWF_NT_FUSED, false>(a.xin, a.xin_sc, j, r, s, a.nrhs, NS, xv);
   if (cg_update || (a.partial && !a.cg_r && a.cg_p && valid)) {
     const bool upd = a.cg_r != nullptr;
-    load_site<P, ODWF_NT_FUSED>(upd ? a.cg_r : a.cg_p, upd ? a.cg_r_sc : a.cg_p_sc, j, r, s, a.nrhs, NS, rv);
+    load_site<P, ODWF_NT_FUSED, false>(upd ? a.cg_r : a.cg_p, upd ? a.cg_r_sc : a.cg_p_sc, j, r, s, a.nrhs, NS, rv);
   }
 }
 
@@ -520,35 +520,49 @@ __device__ __forceinline__ void hop_dir(int dir, const cpx<typename P::real> (&p
 template <class P>
 struct Neighbour {
   static constexpr bool RAW16 = std::is_same<P, SP16>::value;
-  using V = typename std::conditional<RAW16, uint32_t[12], cpx<typename P::real>[12]>::type;
-  // unpack the chunks of the site
-  __device__ static __forceinline__ void set(V& v, const uint4 (&q)[12 / P::CPB]) {
+  static constexpr bool RAW64 = std::is_same<P, SP64>::value;
+  using Site = cpx<typename P::real>[12];
+  using V = typename std::conditional<RAW16, uint32_t[12], typename std::conditional<RAW64, u32x4[12], Site>::type>::type;
+  // keep the chunks of the site (FP64, FP16), or unpack them
+  __device__ static __forceinline__ void set(V& v, const u32x4 (&q)[12 / P::CPB]) {
 #pragma unroll
     for (int cg = 0; cg < 12 / P::CPB; cg++) {
-      if constexpr (RAW16) {
+      if constexpr (RAW64) {
+        v[cg] = q[cg];
+      } else if constexpr (RAW16) {
         v[cg * 4 + 0] = q[cg].x;
         v[cg * 4 + 1] = q[cg].y;
         v[cg * 4 + 2] = q[cg].z;
         v[cg * 4 + 3] = q[cg].w;
       } else {
-        unpack_chunk<P>(q[cg], &v[cg * P::CPB]);
+        unpack_chunk<P>(make_uint4(q[cg].x, q[cg].y, q[cg].z, q[cg].w), &v[cg * P::CPB]);
       }
     }
+  }
+  __device__ static __forceinline__ void get(const V& v, Site& z) {  // FP64
+#pragma unroll
+    for (int c = 0; c < 12; c++) unpack_chunk<SP64>(whole_chunk(v[c]), &z[c]);
+  }
+  __device__ static __forceinline__ void negate(Site& z) {
+#pragma unroll
+    for (int c = 0; c < 12; c++) z[c] = {-z[c].re, -z[c].im};
   }
   // its hopping term, with the boundary sign of a wrapping t hop
   template <bool DAG>
   __device__ static __forceinline__ void apply(int dir, V& v, typename P::real sc, bool flip, float one,
                                                const cpx<typename P::real>* U, cpx<typename P::real> (&acc)[12]) {
-    if (flip) {
-      if constexpr (P::SCALED) {
-        sc = -sc;
-      } else {
-#pragma unroll
-        for (int c = 0; c < 12; c++) v[c] = {-v[c].re, -v[c].im};
-      }
+    if (P::SCALED && flip) sc = -sc;
+    if constexpr (RAW16) {
+      hop_dir_h16<DAG>(dir, v, sc, one, U, acc);
+    } else if constexpr (RAW64) {
+      Site z;
+      get(v, z);
+      if (flip) negate(z);
+      hop_dir<P, DAG>(dir, z, sc, U, acc);
+    } else {
+      if (!P::SCALED && flip) negate(v);
+      hop_dir<P, DAG>(dir, v, sc, U, acc);
     }
-    if constexpr (RAW16) hop_dir_h16<DAG>(dir, v, sc, one, U, acc);
-    else hop_dir<P, DAG>(dir, v, sc, U, acc);
   }
   // 1.0 where the compiler cannot fold it (see proj_h16)
   __device__ static __forceinline__ float opaque_one() {
@@ -615,9 +629,9 @@ __device__ __forceinline__ void hop_sum_row(const HopArgs& a, int j0, int sl, in
     const int nrow = (tt * L2 + zz) * L1 + yy;  // block-uniform
     const unsigned off = mu == 0 ? (fwd ? off_xp : off_xm) : off_own;
     const unsigned char* base = in + (size_t)nrow * row_bytes;
-    uint4 q[NCG];
+    u32x4 q[NCG];
 #pragma unroll
-    for (int cg = 0; cg < NCG; cg++) q[cg] = *reinterpret_cast<const uint4*>(base + off + cg * NS * 16);
+    for (int cg = 0; cg < NCG; cg++) q[cg] = *reinterpret_cast<const u32x4*>(base + off + cg * NS * 16);
     N::set(v, q);
     if constexpr (P::SCALED) {
       const unsigned so = mu == 0 ? (fwd ? soff_xp : soff_xm) : soff_own;
@@ -694,8 +708,8 @@ __device__ __forceinline__ void hop_sum(const HopArgs& a, uint32_t j, int r, int
     if (mu == 3) tt = fwd ? (t + 1 == L3 ? 0 : t + 1) : (t == 0 ? L3 - 1 : t - 1);
     const long nj = (long)((tt * L2 + zz) * L1 + yy) * hx + xx;
     constexpr int NCG = 12 / P::CPB;
-    const uint4* b = reinterpret_cast<const uint4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
-    uint4 q[NCG];
+    const u32x4* b = reinterpret_cast<const u32x4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
+    u32x4 q[NCG];
 #pragma unroll
     for (int cg = 0; cg < NCG; cg++) q[cg] = b[cg * NS];
     N::set(v, q);
@@ -871,17 +885,21 @@ template <class P, bool DAG, int MU, bool FWD>
 __device__ __forceinline__ void small_term(typename Neighbour<P>::V& v, typename P::real sc, bool flip, float one,
                                            const cpx<typename P::real>* U, cpx<typename P::real> (&acc)[12]) {
   constexpr int SIG = FWD != DAG ? +1 : -1;
-  if (flip) {
-    if constexpr (P::SCALED) {
-      sc = -sc;
-    } else {
-#pragma unroll
-      for (int c = 0; c < 12; c++) v[c] = {-v[c].re, -v[c].im};
-    }
+  using N = Neighbour<P>;
+  if (P::SCALED && flip) sc = -sc;
+  if constexpr (N::RAW16) {
+    hop_one_h16<MU, SIG>(v, sc, one, U, acc);
+  } else if constexpr (N::RAW64) {
+    typename N::Site z;
+    N::get(v, z);
+    if (flip) N::negate(z);
+    hop_one<MU, SIG>(z, U, acc);
+  } else if constexpr (P::SCALED) {
+    hop_one_scaled<MU, SIG>(v, sc, U, acc);
+  } else {
+    if (flip) N::negate(v);
+    hop_one<MU, SIG>(v, U, acc);
   }
-  if constexpr (Neighbour<P>::RAW16) hop_one_h16<MU, SIG>(v, sc, one, U, acc);
-  else if constexpr (P::SCALED) hop_one_scaled<MU, SIG>(v, sc, U, acc);
-  else hop_one<MU, SIG>(v, U, acc);
 }
 template <class P, bool DAG, int MU>
 __device__ __forceinline__ void small_terms(typename Neighbour<P>::V (&v)[2], const typename P::real (&sc)[2], bool flip_f,
@@ -993,8 +1011,8 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
       if (mu == 2) zz = fwd ? (z + 1 == L2 ? 0 : z + 1) : (z == 0 ? L2 - 1 : z - 1);
       if (mu == 3) tt = fwd ? (t + 1 == L3 ? 0 : t + 1) : (t == 0 ? L3 - 1 : t - 1);
       const long nj = (long)((tt * L2 + zz) * L1 + yy) * hx + xx;
-      const uint4* src = reinterpret_cast<const uint4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
-      uint4 q[NCG];
+      const u32x4* src = reinterpret_cast<const u32x4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
+      u32x4 q[NCG];
 #pragma unroll
       for (int cg = 0; cg < NCG; cg++) q[cg] = src[cg * NS];
       N::set(v[b], q);
