@@ -17,12 +17,16 @@ namespace odwf {
 
 // Sites per block of a fused launch: as many as 256 threads hold, or fewer where
 // that makes every block a segment of one x-row (scalar row addressing, tiled
-// traversal) and leaves at most a tenth of its lanes idle.
-int hop_spb(int hx, int nrhs, int Ns) {
+// traversal) and leaves at most a tenth of its lanes idle.  Half of them (128
+// threads) pay in FP64 and FP32 (16^4 x 16, one right-hand side, us per CG
+// iteration: 432 against 459 and 238 against 254), not in 16-bit storage (210
+// against 205).
+int hop_spb(int hx, int nrhs, int Ns, int prec) {
   const int inner = nrhs * Ns;
   const int most = inner >= 256 ? 1 : 256 / inner;
   if (hx % most == 0) return most;
-  for (int spb = most - 1; 2 * spb > most; spb--)
+  const bool half = prec == PREC64 || prec == PREC32;
+  for (int spb = most - 1; half ? 2 * spb >= most : 2 * spb > most; spb--)
     if (hx % spb == 0 && 10 * spb * inner >= 9 * ((spb * inner + 63) & ~63)) return spb;
   return most;
 }
@@ -50,9 +54,9 @@ int hop_launch_spb(const Geom& g, int nrhs, int Ns, int prec, bool plain) {
   if (hop_small(g, nrhs, Ns, prec) && !(plain && prec != PREC64)) return 64 / (nrhs * Ns);
   const int hx = g.L[0] / 2;
   const int threads = !plain ? 256 : (prec == PREC64 ? ODWF_HOP_THREADS64 : ODWF_HOP_THREADS32);
-  if (threads == 256) return hop_spb(hx, nrhs, Ns);
+  if (threads == 256) return hop_spb(hx, nrhs, Ns, prec);
   const int spb = std::max(1, threads / (nrhs * Ns));
-  return hx % spb == 0 ? spb : hop_spb(hx, nrhs, Ns);
+  return hx % spb == 0 ? spb : hop_spb(hx, nrhs, Ns, prec);
 }
 
 hipError_t launch_hop_fp64(const HopArgs& a, int Ns, hipStream_t st);
