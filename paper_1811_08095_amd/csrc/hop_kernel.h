@@ -572,6 +572,18 @@ struct Neighbour {
   }
 };
 
+// Direction of the k-th term (4-7 are the backward hops).  FP64 takes -t first
+// and +t last, -t +x -x +y -y +z -z +t: the slice behind was read longest ago,
+// the slice ahead is what the next blocks read (17 % fewer L2 misses at
+// 32^3 x 16 x 16, CG iteration 3340 -> 3285 us; 16^4 x 16, two right-hand sides,
+// 831 -> 811 us).  FP32 spills in this order, FP16 gains nothing from it
+// (32^3 x 16 1.6 % slower, 24^4 0.7 % faster): +x -x +y -y +z -z +t -t.
+template <class P>
+__device__ __forceinline__ int term_dir(int k) {
+  if constexpr (sizeof(typename P::real) == 8) return k & 1 ? k >> 1 : 4 + (((k >> 1) + 3) & 3);
+  else return (k >> 1) | ((k & 1) << 2);
+}
+
 // a block-uniform integer in a scalar register (the compiler does not always
 // prove uniformity through the traversal arithmetic)
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -643,8 +655,7 @@ __device__ __forceinline__ void hop_sum_row(const HopArgs& a, int j0, int sl, in
   auto apply_nb = [&](int dir, Nb& v, R sc) {
     N::template apply<DAG>(dir, v, sc, (dir == 3 && flip_f) || (dir == 7 && flip_b), one, U, acc);
   };
-  // direction of the k-th term: 0, 4, 1, 5, 2, 6, 3, 7
-  auto dir_of = [](int k) { return (k >> 1) | ((k & 1) << 2); };
+  auto dir_of = [](int k) { return term_dir<P>(k); };
   Nb psi[G];
   R scl[G];
   if (PRE && valid) {
@@ -694,8 +705,7 @@ __device__ __forceinline__ void hop_sum(const HopArgs& a, uint32_t j, int r, int
   const float one = N::opaque_one();
   Nb psi[G];
   R scl[G];  // per-site scales of the neighbours (scaled formats)
-  // direction order: +x, -x, +y, -y, ... (4-7 are the backward hops)
-  auto dir_of = [](int k) { return (k >> 1) | ((k & 1) << 2); };
+  auto dir_of = [](int k) { return term_dir<P>(k); };
   auto load_nb = [&](int dir, Nb& v, R& sc) {
     const int mu = dir & 3;
     const bool fwd = dir < 4;
