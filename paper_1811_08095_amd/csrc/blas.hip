@@ -366,7 +366,8 @@ hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, 
 
 // beta is formed inside the vector step while a block of it reads at most this
 // many partial sums (two loads a thread, the scalar launch and its gap saved:
-// 4-6 us of a 4^4 x 8 iteration); above, by a launch of its own
+// 4-6 us of a 4^4 x 8 iteration); above, by a launch of its own (up to 2048:
+// 8^4 x 16, twelve right-hand sides, 330 -> 358 us an FP64 iteration)
 constexpr int STEP_BLOCKS = 512;
 
 hipError_t launch_cg_step(int prec, const void* r, const float* r_sc, void* p, float* p_sc, void* x, float* x_sc,
@@ -465,6 +466,7 @@ hipError_t launch_vec_copy_rhs(int prec_src, const void* src, const float* src_s
 __global__ void __launch_bounds__(1024) fin_kernel(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
                                                    double* out, int gated, CGScal* host) {
   __shared__ double tmp[1024];
+  if (gated && !gate_any(scal, GATE_UPDATE, nrhs)) return;
   const double v = partial_sum(partial, nblocks, nrhs, tmp);
   if ((int)threadIdx.x >= nrhs) return;
   const int r = threadIdx.x;
@@ -523,8 +525,9 @@ size_t partial_bytes(int nblocks, int nrhs) {
 
 hipError_t launch_fin(int kind, const double* partial, int nblocks, int nrhs, CGScal* scal,
                       double* out, hipStream_t st, int gated, CGScal* host) {
-  // one block reads up to 16384 values at 16 a thread; longer arrays take two stages
-  if ((long)nblocks * nrhs > 16384) {
+  // one block reads up to 32768 values at 32 a thread (24576: 4.5 us, as much as
+  // the first of two stages and its gap save); longer arrays take two stages
+  if ((long)nblocks * nrhs > 32768) {
     // the second-stage inputs live behind the first-stage partials
     double* dst = const_cast<double*>(partial) + (size_t)nblocks * nrhs;
     const int nb2 = (nblocks + 1023) / 1024;
