@@ -507,7 +507,7 @@ struct Mfma;
 template <>
 struct Mfma<float> {
   using V = mfma_f32x4;
-  static constexpr int ROW = 20;           // scratch: reals between two rows of 16 slots
+  static constexpr int ROW = 20;           // reals between two rows of 16 slots, scratch and matrix
   static constexpr int SET = 12 * ROW;     // reals between two sets
   __device__ static __forceinline__ int swap(int) { return 0; }
   // register v of lane group g is result row 4 g + v: row = 4 set + real
@@ -540,15 +540,23 @@ constexpr int DENSE_SCRATCH = 4 * Mfma<R>::SET;
 // type.  Nothing in it depends on the mass, so one image serves every
 // right-hand side of a launch.
 template <class R>
+constexpr int DENSE_IMAGE_CHI = DENSE_N * Mfma<R>::ROW + 2 * DENSE_N;  // rows padded against bank conflicts (0.5 - 1.2 % of a solve)
+template <class R>
+constexpr int DENSE_IMAGE = 2 * DENSE_IMAGE_CHI<R>;
+template <class R>
 __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab) {
   constexpr int K = (DENSE_LEN + 255) / 256;  // a thread's elements in flight together (256 threads)
+  constexpr int NN = DENSE_N * DENSE_N;
   for (int i0 = threadIdx.x; i0 < DENSE_LEN; i0 += K * blockDim.x) {
     double v[K];
 #pragma unroll
     for (int k = 0; k < K; k++) v[k] = tab[min(i0 + k * (int)blockDim.x, DENSE_LEN - 1)];
 #pragma unroll
-    for (int k = 0; k < K; k++)
-      if (i0 + k * (int)blockDim.x < DENSE_LEN) m[i0 + k * blockDim.x] = (R)v[k];
+    for (int k = 0; k < K; k++) {
+      const int i = i0 + k * blockDim.x, chi = i / DENSE_CHI, e = i - chi * DENSE_CHI;
+      const int at = e < NN ? (e / DENSE_N) * Mfma<R>::ROW + e % DENSE_N : DENSE_N * Mfma<R>::ROW + e - NN;
+      if (i < DENSE_LEN) m[chi * DENSE_IMAGE_CHI<R> + at] = (R)v[k];
+    }
   }
 }
 
@@ -565,7 +573,7 @@ template <int NS, class R>
 __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m) {
   using M = Mfma<R>;
   using V = typename M::V;
-  constexpr int NN = DENSE_N * DENSE_N;
+  constexpr int NN = DENSE_N * M::ROW;
   const int lane = threadIdx.x & 63, slot = lane & 15, k = lane >> 4;
   R* put = scr + k * M::SET + (slot ^ M::swap(k));
   const int set_i = M::set_of(slot);
@@ -575,7 +583,7 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
   const bool same = slot / NS == 4 * k / NS;  // result slot and operand slots belong to one column
 #pragma unroll
   for (int chi = 0; chi < 2; chi++) {
-    const R* mc = m + chi * DENSE_CHI;
+    const R* mc = m + chi * DENSE_IMAGE_CHI<R>;
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int c = 0; c < 6; c++) {
@@ -585,7 +593,7 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
     __builtin_amdgcn_wave_barrier();
     R b[4], w[4];
 #pragma unroll
-    for (int e = 0; e < 4; e++) b[e] = mc[slot * DENSE_N + 4 * k + e];
+    for (int e = 0; e < 4; e++) b[e] = mc[slot * M::ROW + 4 * k + e];
 #pragma unroll
     for (int e = 0; e < 4; e++) w[e] = mc[NN + DENSE_N + 4 * k + e];
     const R u = same ? mc[NN + slot] : R(0);

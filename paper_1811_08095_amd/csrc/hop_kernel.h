@@ -803,17 +803,17 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
   if constexpr (DENSE) {
     if (a.dn_h.tab) {
       dense_stage<R>(pl.h, a.dn_h.tab);
-      prog += DENSE_LEN;
+      prog += DENSE_IMAGE<R>;
     }
     pl.x = prog;
     if (a.dn_x.tab) {
       dense_stage<R>(pl.x, a.dn_x.tab);
-      prog += DENSE_LEN;
+      prog += DENSE_IMAGE<R>;
     }
     pl.o = prog;
     if (a.dn_o.tab) {
       dense_stage<R>(pl.o, a.dn_o.tab);
-      prog += DENSE_LEN;
+      prog += DENSE_IMAGE<R>;
     }
     pl.scr = prog + (tid >> 6) * DENSE_SCRATCH<R>;
     prog += (blockDim.x >> 6) * DENSE_SCRATCH<R>;
@@ -1051,11 +1051,11 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
     }
   }
   ProgLds<R> pl = {prog, nullptr, nullptr, nullptr};
-  if (a.dn_h.tab) dense_stage<R>(prog, a.dn_h.tab), prog += DENSE_LEN;
+  if (a.dn_h.tab) dense_stage<R>(prog, a.dn_h.tab), prog += DENSE_IMAGE<R>;
   pl.x = prog;
-  if (a.dn_x.tab) dense_stage<R>(prog, a.dn_x.tab), prog += DENSE_LEN;
+  if (a.dn_x.tab) dense_stage<R>(prog, a.dn_x.tab), prog += DENSE_IMAGE<R>;
   pl.o = prog;
-  if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab), prog += DENSE_LEN;
+  if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab), prog += DENSE_IMAGE<R>;
   pl.scr = scr;
   lk.store(lw, nsb, l);
   __builtin_amdgcn_wave_barrier();  // the wave's own LDS, in order
@@ -1128,7 +1128,7 @@ static size_t hop_smem(const HopArgs& a, bool plain) {
   using R = typename P::real;
   size_t n = (size_t)a.spb * 8 * 9 * 2;  // reals
   if (!plain && NS <= DENSE_N)
-    n += (size_t)DENSE_LEN * ((a.dn_h.tab != nullptr) + (a.dn_x.tab != nullptr) + (a.dn_o.tab != nullptr)) +
+    n += (size_t)DENSE_IMAGE<R> * ((a.dn_h.tab != nullptr) + (a.dn_x.tab != nullptr) + (a.dn_o.tab != nullptr)) +
          (size_t)((a.spb * a.nrhs * NS + 63) / 64) * DENSE_SCRATCH<R>;
   else if (!plain)
     n += (size_t)a.spb * a.nrhs * 12 * (NS + 1) * 2 + MAXRHS;
@@ -1146,7 +1146,7 @@ static hipError_t launch_hop_t(HopArgs a, int dag, hipStream_t st) {
     if (a.small) {
       using R = typename P::real;
       const int np = (a.dn_h.tab != nullptr) + (a.dn_x.tab != nullptr) + (a.dn_o.tab != nullptr);
-      const size_t sm = (3 * 24 * 64 + (size_t)np * DENSE_LEN + DENSE_SCRATCH<R>) * sizeof(R);
+      const size_t sm = (3 * 24 * 64 + (size_t)np * DENSE_IMAGE<R> + DENSE_SCRATCH<R>) * sizeof(R);
       const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0));
       if (dag) hipLaunchKernelGGL((hop_small_kernel<P, NS, true>), grid, dim3(256), sm, st, a);
       else hipLaunchKernelGGL((hop_small_kernel<P, NS, false>), grid, dim3(256), sm, st, a);

@@ -61,7 +61,7 @@ __global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const 
                                                        double c1, const DenseArg dn, const double* diag, long ncol,
                                                        int nrhs) {
   using R = typename P::real;
-  __shared__ __align__(16) R mat[DENSE_LEN];
+  __shared__ __align__(16) R mat[DENSE_IMAGE<R>];
   __shared__ __align__(16) R scr[4 * DENSE_SCRATCH<R>];
   const int s = threadIdx.x % NS;
   const long j = (long)blockIdx.x * (256 / NS) + threadIdx.x / NS;

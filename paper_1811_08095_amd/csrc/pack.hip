@@ -278,7 +278,7 @@ static hipError_t launch_tile(bool pack, void* canon, const TileArgs& a, hipStre
   using R = typename P::real;
   constexpr int TS = Tile<NS>::TS;
   if (a.dn.tab && NS > DENSE_N) return hipErrorInvalidValue;
-  const size_t sm = TileLds<NS>::N * sizeof(cpx<R>) + (a.dn.tab ? DENSE_LEN * sizeof(R) : 0);
+  const size_t sm = TileLds<NS>::N * sizeof(cpx<R>) + (a.dn.tab ? DENSE_IMAGE<R> * sizeof(R) : 0);
   const dim3 grid((unsigned)((a.n + TS - 1) / TS), a.nrhs);
   double2* c = reinterpret_cast<double2*>(canon);
   if (pack) hipLaunchKernelGGL((pack_tile_kernel<P, NS>), grid, dim3(Tile<NS>::T), sm, st, c, a);
