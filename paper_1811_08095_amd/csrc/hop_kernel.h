@@ -17,11 +17,12 @@
 // neighbour.  The 8 links of the block's sites are staged once in LDS and
 // shared by all nrhs * Ns lanes of a site (links are stored per output parity
 // as [site][8][...] with directions 0-3 forward U_mu(x) and 4-7 backward
-// U_mu(x - mu)^dag).  Fifth-dimension programs run across the 16 lanes of a
-// DPP row for FP32 arithmetic at Ns = 16 (one slice per lane), otherwise on LDS
-// columns (site, r, colour-spin component) of Ns values.  No MFMA: the stencil
-// is a string of 3x3 complex mat-vecs; its time is set by the traffic between
-// the L2 caches and memory (FP32, FP64) or by VALU issue (FP16, BF16 storage).
+// U_mu(x - mu)^dag).  Fifth-dimension programs are dense N_s x N_s matrices per
+// chirality on the matrix cores for N_s <= 16 (dense_apply), and run on LDS
+// columns (site, r, colour-spin component) for N_s = 32.  The stencil itself is a
+// string of 3x3 complex mat-vecs on the vector units.  Its time is set by the L2
+// misses (FP64, FP32: 5.3 - 6.6 TB/s), with L1 passes and vector instructions
+// close behind, or by vector instructions (FP16, BF16 storage).
 #pragma once
 #include <algorithm>
 #include <type_traits>
@@ -291,10 +292,14 @@ struct ProgLds {
 // loaded (and transformed) here
 enum XMode { X_LDS = 1, X_LOAD = 2 };
 
+__device__ __forceinline__ HopIo first_io(const HopArgs& a) {
+  return {a.in, a.in_sc, a.links, a.xin, a.xin_sc, a.out, a.out_sc, a.out_par};
+}
+
 // what the epilogue reads, loaded ahead of the hop where registers allow
 // (small launches): x term, CG residual or f, rho per program and chirality
 template <class P, int NS>
-__device__ __forceinline__ void tail_preload(const HopArgs& a, bool valid, long j, int r, int s,
+__device__ __forceinline__ void tail_preload(const HopArgs& a, const HopIo& io, bool valid, long j, int r, int s,
                                              cpx<typename P::real> (&xv)[12], cpx<typename P::real> (&rv)[12],
                                              typename P::real (&rho)[6], typename P::real& alpha, bool& cg_update) {
   using R = typename P::real;
@@ -306,7 +311,7 @@ __device__ __forceinline__ void tail_preload(const HopArgs& a, bool valid, long 
   }
   cg_update = a.partial && a.cg_r && valid && a.scal[r].active;
   alpha = cg_update ? (R)a.scal[r].alpha : R(0);
-  if (a.xin && valid) load_site<P, ODWF_NT_FUSED, false>(a.xin, a.xin_sc, j, r, s, a.nrhs, NS, xv);
+  if (io.xin && valid) load_site<P, ODWF_NT_FUSED, false>(io.xin, io.xin_sc, j, r, s, a.nrhs, NS, xv);
   if (cg_update || (a.partial && !a.cg_r && a.cg_p && valid)) {
     const bool upd = a.cg_r != nullptr;
     load_site<P, ODWF_NT_FUSED, false>(upd ? a.cg_r : a.cg_p, upd ? a.cg_r_sc : a.cg_p_sc, j, r, s, a.nrhs, NS, rv);
@@ -319,7 +324,7 @@ __device__ __forceinline__ void tail_preload(const HopArgs& a, bool valid, long 
 // the matrix instructions; the column passes of N_s = 32 synchronise the
 // block); returns this lane's share of the partial sum.
 template <class P, int NS, bool PRE>
-__device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::real> (&acc)[12], bool valid,
+__device__ __forceinline__ double fused_tail(const HopArgs& a, const HopIo& io, cpx<typename P::real> (&acc)[12], bool valid,
                                              long j, int sl, int r, int s, int nsb,
                                              const ProgLds<typename P::real>& pl, const typename P::real* kap,
                                              int xmode, cpx<typename P::real> (&xv)[12],
@@ -356,7 +361,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
   const int cgmode = a.partial ? (a.cg_r ? 2 : (a.cg_p ? 3 : 1)) : 0;
   const bool cg_update = PRE ? cg_pre : cgmode == 2 && valid && a.scal[r].active;
   bool r_loaded = PRE;
-  const bool has_x = a.xin != nullptr;
+  const bool has_x = io.xin != nullptr;
   if (has_x) {
     if (xmode == X_LDS) {  // transformed before the hop, still in the column buffer
       if (valid) {
@@ -368,7 +373,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
 #pragma unroll
         for (int c = 0; c < 12; c++) xv[c] = {R(0), R(0)};
       }
-      if (!PRE && valid) load_site<P, ODWF_NT_FUSED>(a.xin, a.xin_sc, j, r, s, nrhs, NS, xv);
+      if (!PRE && valid) load_site<P, ODWF_NT_FUSED>(io.xin, io.xin_sc, j, r, s, nrhs, NS, xv);
       if constexpr (!PRE && sizeof(R) == 4 && NS <= DENSE_N && !P::SCALED) {
         // the CG residual travels with the x term: one memory round trip fewer
         if (cg_update) {
@@ -417,9 +422,9 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, cpx<typename P::r
       nval += (double)cnorm2(acc[c]);
     }
   }
-  void* dst = a.out;
-  float* dst_sc = a.out_sc;
-  bool store = valid && a.out;
+  void* dst = io.out;
+  float* dst_sc = io.out_sc;
+  bool store = valid && io.out;
   if (cgmode == 2) {
     // x += alpha p runs in the vector step after beta (launch_cg_step),
     // which reads p there anyway
@@ -862,7 +867,7 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
   asm volatile("" : "+v"(slr));
   cpx<R> xv[12], rv[12];
   const R rho[6] = {};
-  const double nval = fused_tail<P, NS, false>(a, acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap,
+  const double nval = fused_tail<P, NS, false>(a, first_io(a), acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap,
                                                x_first ? X_LDS : X_LOAD, xv, rv, rho, R(0), false);
   if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, lb);
 }
@@ -949,8 +954,8 @@ struct SmallLinks {
   static constexpr int K = FULL ? (2 * (64 / NS) * 9 + 63) / 64 : 3;
   uint4 q[K];
   __device__ static __forceinline__ int clamp_mat(int m, int nsb) { return min(m, 2 * nsb - 1); }
-  __device__ __forceinline__ void load(const HopArgs& a, uint32_t j0, int nsb, int mu, int l) {
-    const uint4* src = reinterpret_cast<const uint4*>(a.links);
+  __device__ __forceinline__ void load(const void* links, uint32_t j0, int nsb, int mu, int l) {
+    const uint4* src = reinterpret_cast<const uint4*>(links);
 #pragma unroll
     for (int k = 0; k < K; k++) {
       const int m = clamp_mat(FULL ? (l + 64 * k) / 9 : l, nsb), e = FULL ? (l + 64 * k) % 9 : k;
@@ -1002,6 +1007,17 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
     lb -= 1;
   }
   if (!gate_any(a.gate, a.gate_mode, nrhs)) return;  // whole block idle
+  HopIo io = first_io(a);
+  if (blockIdx.y) {  // (field by field: an indexed copy of arguments would go through scratch)
+    io.in = a.other.in;
+    io.in_sc = a.other.in_sc;
+    io.links = a.other.links;
+    io.xin = a.other.xin;
+    io.xin_sc = a.other.xin_sc;
+    io.out = a.other.out;
+    io.out_sc = a.other.out_sc;
+    io.out_par = a.other.out_par;
+  }
   const int mu = uniform_int(tid >> 6), l = tid & 63;
   const int col = l / NS, s = l - col * NS;
   const int sl = nrhs == 1 ? col : col / nrhs;
@@ -1025,11 +1041,11 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
   const int row = a.d_hx.div(j), xh = j - row * hx;
   const int zt = a.d_y.div(row), y = row - zt * L1;
   const int t = a.d_z.div(zt), z = zt - t * L2;
-  const int p = (y + z + t + a.out_par) & 1;
+  const int p = (y + z + t + io.out_par) & 1;
   typename N::V v[2];
   R sc[2] = {R(1), R(1)};
   SmallLinks<P, NS> lk;
-  lk.load(a, j0, nsb, mu, l);
+  lk.load(io.links, j0, nsb, mu, l);
   if (valid) {
 #pragma unroll
     for (int b = 0; b < 2; b++) {  // forward, backward
@@ -1042,12 +1058,12 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
       if (mu == 2) zz = fwd ? (z + 1 == L2 ? 0 : z + 1) : (z == 0 ? L2 - 1 : z - 1);
       if (mu == 3) tt = fwd ? (t + 1 == L3 ? 0 : t + 1) : (t == 0 ? L3 - 1 : t - 1);
       const long nj = (long)((tt * L2 + zz) * L1 + yy) * hx + xx;
-      const u32x4* src = reinterpret_cast<const u32x4*>(a.in) + (nj * nrhs + r) * NCG * NS + s;
+      const u32x4* src = reinterpret_cast<const u32x4*>(io.in) + (nj * nrhs + r) * NCG * NS + s;
       u32x4 q[NCG];
 #pragma unroll
       for (int cg = 0; cg < NCG; cg++) q[cg] = src[cg * NS];
       N::set(v[b], q);
-      if constexpr (P::SCALED) sc[b] = a.in_sc[(nj * nrhs + r) * NS + s];
+      if constexpr (P::SCALED) sc[b] = io.in_sc[(nj * nrhs + r) * NS + s];
     }
   }
   ProgLds<R> pl = {prog, nullptr, nullptr, nullptr};
@@ -1082,7 +1098,7 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
 #pragma unroll
   for (int c = 0; c < 6; c++) rho[c] = R(0);
   // (after the hop: its neighbours, links and these together exceed the registers in FP64)
-  if (mu == 0) tail_preload<P, NS>(a, valid, j, r, s, xv, rv, rho, alpha, cg_update);
+  if (mu == 0) tail_preload<P, NS>(a, io, valid, j, r, s, xv, rv, rho, alpha, cg_update);
   if (mu > 0) {
     R* d = sum + (mu - 1) * 24 * 64 + l;
 #pragma unroll
@@ -1099,7 +1115,7 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
 #pragma unroll
     for (int c = 0; c < 12; c++) acc[c] = cadd(acc[c], cpx<R>{d[(2 * c) * 64], d[(2 * c + 1) * 64]});
   }
-  double nval = fused_tail<P, NS, true>(a, acc, valid, j, sl, r, s, nsb, pl, nullptr, X_LOAD, xv, rv, rho, alpha,
+  double nval = fused_tail<P, NS, true>(a, io, acc, valid, j, sl, r, s, nsb, pl, nullptr, X_LOAD, xv, rv, rho, alpha,
                                         cg_update);
   if (a.partial) {  // one wave: LDS of its own, in order
     if (!valid) nval = 0.0;
@@ -1147,7 +1163,7 @@ static hipError_t launch_hop_t(HopArgs a, int dag, hipStream_t st) {
       using R = typename P::real;
       const int np = (a.dn_h.tab != nullptr) + (a.dn_x.tab != nullptr) + (a.dn_o.tab != nullptr);
       const size_t sm = (3 * 24 * 64 + (size_t)np * DENSE_IMAGE<R> + DENSE_SCRATCH<R>) * sizeof(R);
-      const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0));
+      const dim3 grid(a.nblocks + (a.fin_partial ? 1 : 0), a.pair ? 2 : 1);
       if (dag) hipLaunchKernelGGL((hop_small_kernel<P, NS, true>), grid, dim3(256), sm, st, a);
       else hipLaunchKernelGGL((hop_small_kernel<P, NS, false>), grid, dim3(256), sm, st, a);
       return hipGetLastError();

@@ -137,6 +137,17 @@ struct FastDiv {
 };
 
 // ---- arguments of the fused hopping kernel ----------------------------------
+// fields of one output parity
+struct HopIo {
+  const void* in;
+  const float* in_sc;
+  const void* links;
+  const void* xin;
+  const float* xin_sc;
+  void* out;
+  float* out_sc;
+  int out_par;
+};
 struct HopArgs {
   const void* in;       // opposite-parity input half
   const float* in_sc;
@@ -171,6 +182,8 @@ struct HopArgs {
   int plain;  // the hop alone: no program, x term, factor or partial sums
   int rows;   // every block is a segment of one x-row
   int small;  // four waves to 64 lanes of sites
+  int pair;   // (small) blockIdx.y = 1 works on `other`, the other output parity of the same operator
+  HopIo other;
   int L[4];
   int nblocks;
   // block traversal: xcd != 0 gives each of the 8 XCDs a contiguous range of

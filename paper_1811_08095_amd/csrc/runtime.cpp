@@ -266,8 +266,8 @@ static void traversal(HopArgs& a) {
   }
 }
 
-hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out, const HopOpt& o) {
-  HopArgs a;
+static hipError_t hop_args(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out, const HopOpt& o,
+                           HopArgs& a) {
   std::memset(&a, 0, sizeof(a));
   const odwf_lattice L = c.S->lat;
   a.in = in.d;
@@ -331,6 +331,13 @@ hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out
     a.d_nz = FastDiv(a.L[2] / a.tile_z / gz);
     a.d_nx = FastDiv(nseg / tx);
   }
+  return hipSuccess;
+}
+
+hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out, const HopOpt& o) {
+  HopArgs a;
+  HIPRET(hop_args(c, out_par, dag, in, out, o, a));
+  const odwf_lattice L = c.S->lat;
   // launches gated to the active right-hand sides of a batch are counted with
   // the bytes of all nrhs (exact while every slot is active); launches gated to
   // pending reliable updates mostly exit at once and are not counted
@@ -346,6 +353,26 @@ hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out
     prof_end(c.st, n5 * site_bytes(c.prec) * streams + link_b);
   }
   return e;
+}
+
+// Both output parities of an operator, out_p = hop(in_{1-p}) with x term in_p: one
+// launch where the four-wave kernel takes them (4^4 x 8 in FP64 PAIRFIG), else two.
+hipError_t hop_pair(const OpCtx& c, int dag, const HV& in_e, const HV& in_o, const HV& out_e, const HV& out_o,
+                    HopOpt o) {
+  const bool apart = out_e.d != in_e.d && out_e.d != in_o.d && out_o.d != in_e.d && out_o.d != in_o.d;
+  o.x = &in_e;
+  if (!hop_small(c.S->lat->g, c.nrhs, c.Ns(), c.prec) || !apart || o.partial || prof_on()) {
+    HIPRET(hop(c, 0, dag, in_o, &out_e, o));
+    o.x = &in_o;
+    return hop(c, 1, dag, in_e, &out_o, o);
+  }
+  HopArgs a, b;
+  HIPRET(hop_args(c, 0, dag, in_o, &out_e, o, a));
+  o.x = &in_o;
+  HIPRET(hop_args(c, 1, dag, in_e, &out_o, o, b));
+  a.pair = 1;
+  a.other = {b.in, b.in_sc, b.links, b.xin, b.xin_sc, b.out, b.out_sc, b.out_par};
+  return launch_hop(a, c.prec, c.S->Ns, c.st);
 }
 
 hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p, double c0,

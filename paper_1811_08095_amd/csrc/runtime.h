@@ -127,6 +127,9 @@ struct HopOpt {
 };
 
 hipError_t hop(const OpCtx& c, int out_par, int dag, const HV& in, const HV* out, const HopOpt& o);
+// both output parities of an operator, each with the own parity's field as its x term (o.x is set here)
+hipError_t hop_pair(const OpCtx& c, int dag, const HV& in_e, const HV& in_o, const HV& out_e, const HV& out_o,
+                    HopOpt o);
 // a program as the kernels take it: its dense form (table null: none) and its
 // coefficients when it is a pure scaling (null: not one)
 DenseArg dense_arg(const OpCtx& c, const M5Prog& p);

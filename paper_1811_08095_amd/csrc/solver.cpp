@@ -27,20 +27,14 @@ hipError_t apply_D(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, con
   HopOpt o;
   o.px = prog_a();
   o.po = po;
-  o.x = &ye;
-  HIPRET(hop(c, 0, 0, yo, &oe, o));
-  o.x = &yo;
-  return hop(c, 1, 0, ye, &oo, o);
+  return hop_pair(c, 0, ye, yo, oe, oo, o);
 }
 
 hipError_t apply_Ddag(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo) {
   HopOpt o;
   o.px = prog_a_t();
   o.po = prog_1pl_t();
-  o.x = &ye;
-  HIPRET(hop(c, 0, 1, yo, &oe, o));
-  o.x = &yo;
-  return hop(c, 1, 1, ye, &oo, o);
+  return hop_pair(c, 1, ye, yo, oe, oo, o);
 }
 
 hipError_t apply_schur(const OpCtx& c, const HV& in, const HV& to, const HV& out) {
