@@ -54,6 +54,7 @@ int hop_launch_spb(const Geom& g, int nrhs, int Ns, int prec, bool plain) {
   if (hop_small(g, nrhs, Ns, prec) && !(plain && prec != PREC64)) return 64 / (nrhs * Ns);
   const int hx = g.L[0] / 2;
   const int threads = !plain ? 256 : (prec == PREC64 ? ODWF_HOP_THREADS64 : ODWF_HOP_THREADS32);
+  if (plain && prec == PREC16) return std::max(1, 256 / (nrhs * Ns));  // (its two paths differ in rounding)
   if (threads == 256) return hop_spb(hx, nrhs, Ns, prec);
   const int spb = std::max(1, threads / (nrhs * Ns));
   return hx % spb == 0 ? spb : hop_spb(hx, nrhs, Ns, prec);

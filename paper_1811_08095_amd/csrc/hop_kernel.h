@@ -520,11 +520,14 @@ __device__ __forceinline__ void hop_dir(int dir, const cpx<typename P::real> (&p
   }
 }
 
-// a neighbour in registers: FP16 stays packed until the projection (see
-// proj_h16), in every path, so that a site's sum is the same bits in all of them
-template <class P>
+// a neighbour in registers.  FP16 stays packed until the projection (see
+// proj_h16), in the row and the general path alike, so that a site's sum is the
+// same bits in both; the plain hop of the general path unpacks first (PACKED =
+// false): the compiler contracts the link products of the two forms differently,
+// and a plain hop's bits in 16-bit storage do not change from one version to the next.
+template <class P, bool PACKED = true>
 struct Neighbour {
-  static constexpr bool RAW16 = std::is_same<P, SP16>::value;
+  static constexpr bool RAW16 = PACKED && std::is_same<P, SP16>::value;
   static constexpr bool RAW64 = std::is_same<P, SP64>::value;
   using Site = cpx<typename P::real>[12];
   using V = typename std::conditional<RAW16, uint32_t[12], typename std::conditional<RAW64, u32x4[12], Site>::type>::type;
@@ -692,7 +695,7 @@ __device__ __forceinline__ void hop_sum_row(const HopArgs& a, int j0, int sl, in
 // The eight hopping terms of output site j, summed into acc (the factor -1/2
 // rides on the staged links), for any block shape: the coordinates and the
 // neighbour index are formed per lane.
-template <class P, int NS, bool DAG, int G, bool PRE>
+template <class P, int NS, bool DAG, int G, bool PRE, bool PACKED>
 __device__ __forceinline__ void hop_sum(const HopArgs& a, uint32_t j, int r, int s, bool valid,
                                         const cpx<typename P::real>* U, cpx<typename P::real> (&acc)[12]) {
   using R = typename P::real;
@@ -705,7 +708,7 @@ __device__ __forceinline__ void hop_sum(const HopArgs& a, uint32_t j, int r, int
   const int p = (y + z + t + a.out_par) & 1;
   const bool flip_f = a.bc_t < 0 && t + 1 == L3;  // forward t hop wraps
   const bool flip_b = a.bc_t < 0 && t == 0;       // backward t hop wraps
-  using N = Neighbour<P>;
+  using N = Neighbour<P, PACKED>;
   using Nb = typename N::V;
   const float one = N::opaque_one();
   Nb psi[G];
@@ -853,7 +856,7 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
     constexpr bool PRE = sizeof(R) == 8;
     // (row offsets are 32-bit: a row of a half field is at most 3 MB here)
     if (a.rows) hop_sum_row<P, NS, DAG, G, PRE>(a, (int)j0, sl, r, s, valid, U, acc);
-    else hop_sum<P, NS, DAG, G, PRE>(a, j0 + sl, r, s, valid, U, acc);
+    else hop_sum<P, NS, DAG, G, PRE, !PLAIN>(a, j0 + sl, r, s, valid, U, acc);
   }
   if constexpr (PLAIN) {
     if (valid) store_site<P, ODWF_NT_STORE>(a.out, a.out_sc, j0 + sl, r, s, nrhs, NS, acc);
