@@ -32,15 +32,17 @@ int hop_spb(int hx, int nrhs, int Ns, int prec) {
 }
 
 // Small launches take the four-wave kernel: 64 lanes of columns a block, up to
-// 512 blocks in FP64 and 1024 in the reduced precisions.  Measured per CG
-// iteration, four-wave kernel against the other, N_s = 16, one right-hand side:
-// 4^4 47.8 / 71.9 us (FP64), 49 / 64 (FP32); 8^4 (512 blocks) 71 / 91 and
-// 62 / 73; 8^3 x 16 (1024) 103 / 96 and 62 / 75; 16^2 x 8^2 (2048) 177 / 154 and
-// 110 / 104.
+// 768 blocks in FP64 (512 fit the chip by LDS) and 1024 in the reduced
+// precisions.  Measured in us per CG iteration, four-wave kernel against the
+// other, one right-hand side: N_s = 16, 4^4 46 / 65 (FP64) and 50 / 62 (FP32);
+// 8^4 (512 blocks) 68 / 85 and 63 / 73; 8^3 x 16 (1024) 100 / 90 and 65 / 75;
+// 16^2 x 8^2 (2048) 173 / 129 and 108 / 92; N_s = 8, 10^4 (625) 82 / 90 and 58 / 75.
+// Three right-hand sides: N_s = 8, 6x10x6x8 (720) 81 / 87 and 58 / 72; N_s = 16,
+// 8^3 x 4 (1024) 94 / 89 and 75 / 84.
 bool hop_small(const Geom& g, int nrhs, int Ns, int prec) {
   if (!dense_ns(Ns) || nrhs * Ns > 64) return false;
   const int spb = 64 / (nrhs * Ns);
-  return (g.h + spb - 1) / spb <= (prec == PREC64 ? 512 : 1024);
+  return (g.h + spb - 1) / spb <= (prec == PREC64 ? 768 : 1024);
 }
 
 int hop_nblocks(const Geom& g, int nrhs, int Ns, int prec) {

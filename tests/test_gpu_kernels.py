@@ -56,10 +56,11 @@ def test_operators_at_tile_edges(case, prec):
     lat.close()
 
 
-# (lattice, right-hand sides): the last launch of the four-wave kernel in FP64 (512
-# blocks) and the first above, the same in FP32 (1024); three right-hand sides
-# leave 16 lanes of a wave idle, five are too many for it
-SMALL = [((8, 8, 8, 8), 1), ((8, 8, 8, 10), 1), ((8, 8, 8, 18), 1), ((4, 4, 4, 16), 3), ((8, 4, 8, 4), 4), ((4, 4, 4, 4), 5)]
+# (lattice, right-hand sides): 512 partial sums and the first launch above, the last
+# launch of the four-wave kernel in FP64 (768 blocks) and the first above, the same
+# in FP32 (1024); three right-hand sides leave 16 lanes of a wave idle, five are
+# too many for it
+SMALL = [((8, 8, 8, 8), 1), ((8, 8, 8, 10), 1), ((8, 8, 8, 12), 1), ((8, 8, 8, 14), 1), ((8, 8, 8, 16), 1), ((8, 8, 8, 18), 1), ((4, 4, 4, 16), 3), ((8, 4, 8, 4), 4), ((4, 4, 4, 4), 5)]
 
 
 @pytest.mark.parametrize("prec", [odwf.FP64, odwf.FP32])
