@@ -104,7 +104,7 @@ def cycle_lines(d, regex, n, skip):
 
 
 def _copy_factor(vals, nbytes):
-    cands = [max(v) for k, v in vals.items() if COPY_RE.search(k) and v]
+    cands = [max(v) for k, v in vals.items() if COPY_RE.search(k) and "odwf::" not in k and v]
     if not cands:
         raise RuntimeError("no copy kernel dispatch in the counter output")
     kib = max(cands)
