@@ -113,6 +113,7 @@ struct Poller {
     return hipSuccess;
   }
   ~Poller() {
+    if (k > 0) (void)hipEventSynchronize(ev[(k - 1) % 4]);  // the last step writes its mirror until then
     for (int i = 0; i < 4; i++)
       if (ev[i]) (void)hipEventDestroy(ev[i]);
     if (host) (void)hipHostFree(host);
