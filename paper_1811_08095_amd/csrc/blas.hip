@@ -155,6 +155,19 @@ __device__ __forceinline__ CGScal step_scal(const StepScal& a, int r, int nrhs, 
   return c;
 }
 
+// The solution is touched by the step alone: nontemporal, so that it displaces
+// less of what the hops read next (16^4 x 16 FP32, two right-hand sides, 104.7 ->
+// 101.5 ms a solve, 32^3 x 16 x 16 520 -> 510 ms; r as well: 8^4 x 16, twelve slots,
+// 0.7 % slower, the others up to 0.8 % faster; FP16S 24^4 x 16 384 -> 380 ms).
+__device__ __forceinline__ uint4 stream_load(const uint4* p) {
+  const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(w.x, w.y, w.z, w.w);
+}
+__device__ __forceinline__ void stream_store(uint4* p, const uint4 q) {
+  const u32x4 w = {q.x, q.y, q.z, q.w};
+  __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+}
+
 // CG vector step:
 //   x += alpha p   (for every right-hand side that iterated: alpha != 0, which
 //                   includes one that converged at this iteration's beta)
@@ -177,7 +190,7 @@ __global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uin
       if (k >= g.n) continue;
       const long at = g.at(k, r);
       unpack_chunk<P>(p_[at], p[u]);
-      unpack_chunk<P>(x_[at], x[u]);
+      unpack_chunk<P>(stream_load(x_ + at), x[u]);
       unpack_chunk<P>(r_[at], rv[u]);
     }
   }
@@ -207,7 +220,7 @@ __global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uin
         x[u][q] = {R(0), R(0)};
       }
     }
-    if (c.alpha != 0.0) x_[at] = pack_chunk<P>(x[u], R(1));
+    if (c.alpha != 0.0) stream_store(x_ + at, pack_chunk<P>(x[u], R(1)));
     if (act) p_[at] = pack_chunk<P>(p[u], R(1));
   }
 }
@@ -259,10 +272,10 @@ __global__ void __launch_bounds__(256) vec_cg_step_kernel(const void* r_, const 
     load_site<P>(p_, p_sc, j, r, s, nrhs, Ns, pv);
     if (alpha != 0.0) {
       cpx<R> xv[12];
-      load_site<P>(x_, x_sc, j, r, s, nrhs, Ns, xv);
+      load_site<P, 1>(x_, x_sc, j, r, s, nrhs, Ns, xv);
 #pragma unroll
       for (int c = 0; c < 12; c++) xv[c] = cadd(xv[c], cscale(al, pv[c]));
-      store_site<P>(x_, x_sc, j, r, s, nrhs, Ns, xv);
+      store_site<P, 1>(x_, x_sc, j, r, s, nrhs, Ns, xv);
     }
     if (act) {
       cpx<R> rv[12];
