@@ -569,6 +569,12 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
 // share the instruction, and each one's result is the same bits whatever the
 // others are.  Called by whole waves: the matrix instructions ignore the lane
 // mask.
+// Below 16 slices the zeros between the columns of a row do not stop a value that
+// is not finite (0 * Inf is NaN), nor a product rho * t that is not.  A wave that
+// holds either takes its columns one at a time as well, the others' slots zero in
+// the operand, and keeps those results.  (The test is of the inputs and of rho * t,
+// not of the results: it runs beside the LDS round trip.)  Within its own column, of
+// 16 slices too, such a value may reach every slice.
 template <int NS, class R>
 __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m) {
   using M = Mfma<R>;
@@ -581,6 +587,16 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
   const int src = 16 * set_i + 4 * k;  // a lane of the operand element's column
   const R rho[2] = {__shfl(rho_p, src, 64), __shfl(rho_m, src, 64)};
   const bool same = slot / NS == 4 * k / NS;  // result slot and operand slots belong to one column
+  bool nonfinite = false;
+  if constexpr (NS < DENSE_N) {
+    R z[2] = {R(0), R(0)};
+#pragma unroll
+    for (int c = 0; c < 12; c++) {
+      z[0] = fma(y[c].re, R(0), z[0]);
+      z[1] = fma(y[c].im, R(0), z[1]);
+    }
+    nonfinite = !(z[0] + z[1] == R(0));
+  }
 #pragma unroll
   for (int chi = 0; chi < 2; chi++) {
     const R* mc = m + chi * DENSE_IMAGE_CHI<R>;
@@ -597,20 +613,43 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
 #pragma unroll
     for (int e = 0; e < 4; e++) w[e] = mc[NN + DENSE_N + 4 * k + e];
     const R u = same ? mc[NN + slot] : R(0);
+    R z = R(0);
+    // three groups of four reals; `in`: the lane's operand slots take part, else zeros
+    auto product = [&](bool in, auto&& result) {
 #pragma unroll
-    for (int g = 0; g < 3; g++) {
-      R x[4];
+      for (int g = 0; g < 3; g++) {
+        R x[4];
 #pragma unroll
-      for (int e = 0; e < 4; e++) x[e] = get[4 * g * M::ROW + e];
-      V d = {R(0), R(0), R(0), R(0)};
+        for (int e = 0; e < 4; e++) x[e] = in ? get[4 * g * M::ROW + e] : R(0);
+        V d = {R(0), R(0), R(0), R(0)};
 #pragma unroll
-      for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
-      R t = w[0] * x[0];
+        for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
+        R t = w[0] * x[0];
 #pragma unroll
-      for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
-      d = M::mul(rho[chi] * t, u, d);
+        for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
+        t *= rho[chi];
+        if (NS < DENSE_N) z = fma(t, R(0), z);
+        d = M::mul(t, u, d);
+        result(g, d);
+      }
+    };
+    product(true, [&](int g, const V& d) {
       y[6 * chi + 2 * g] = {d[0], d[1]};
       y[6 * chi + 2 * g + 1] = {d[2], d[3]};
+    });
+    if constexpr (NS < DENSE_N) {
+      if (__any(nonfinite || !(z == R(0)))) {
+#pragma unroll 1
+        for (int q = 0; q < DENSE_N / NS; q++) {
+          const bool own = slot / NS == q;
+          product(4 * k / NS == q, [&](int g, const V& d) {
+            if (own) {
+              y[6 * chi + 2 * g] = {d[0], d[1]};
+              y[6 * chi + 2 * g + 1] = {d[2], d[3]};
+            }
+          });
+        }
+      }
     }
   }
 }
