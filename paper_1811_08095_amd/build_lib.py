@@ -6,6 +6,7 @@ instructions disabled, and linked into a shared library with a plain C ABI
 """
 import concurrent.futures as cf
 import os
+import re
 import subprocess
 import sys
 
@@ -20,7 +21,43 @@ SOURCES = ["hop_fp64.hip", "hop_fp32.hip", "hop_fp16.hip", "hop_bf16.hip", "hop.
 COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall",
           "-Wno-unused-function", "-Wno-unused-variable",
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-          "-I" + CSRC, "-I" + os.path.join(os.path.dirname(HERE), "include")]
+          "-I" + CSRC, "-I" + os.path.join(os.path.dirname(HERE), "include"),
+          "-Rpass-analysis=kernel-resource-usage"]
+
+
+def check_usage(messages: str) -> None:
+    """Refuse kernels that hold values in accumulation registers, from the
+    compiler's resource-usage remarks.  Every kernel here fits the 256 vector
+    registers that its launch bounds leave it.  Builds of the four-wave hopping
+    kernel with a larger budget, in which the matrix results went to accumulation
+    registers, gave wrong results for a reason that is not known (the generated
+    code shows none: LDS accesses in order, matrix results waited for as in the
+    right builds), so no such kernel is let into the library."""
+    name = None
+    for line in messages.splitlines():
+        m = re.search(r"remark: .*?(Function Name|AGPRs): (\S+)", line)
+        if not m:
+            continue
+        if m[1] == "Function Name":
+            name = m[2]
+        elif int(m[2]) > 0:
+            raise RuntimeError(f"{name} uses {m[2]} accumulation registers: give it a launch bound "
+                               "that keeps it within 256 vector registers")
+
+
+def _without_remarks(messages: str) -> str:
+    """The compiler's messages but for the resource-usage remarks, their source
+    lines and the include lines that lead to them."""
+    out, lead, remark = [], [], False
+    for line in messages.splitlines():
+        if line.startswith("In file included from"):
+            lead.append(line)
+        elif "[-Rpass-analysis=kernel-resource-usage]" in line:
+            lead, remark = [], True
+        elif not (remark and re.match(r"\s*\d* \|", line)):
+            out += lead + [line]
+            lead, remark = [], False
+    return "\n".join(out)
 
 
 def _compile(src: str, verbose: bool, build_dir: str, defines) -> str:
@@ -30,7 +67,12 @@ def _compile(src: str, verbose: bool, build_dir: str, defines) -> str:
         ["-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
-    subprocess.check_call(cmd)
+    r = subprocess.run(cmd, stderr=subprocess.PIPE, text=True)
+    messages = _without_remarks(r.stderr)
+    if messages:
+        print(messages, file=sys.stderr, flush=True)
+    r.check_returncode()
+    check_usage(r.stderr)
     return obj
 
 

@@ -312,6 +312,16 @@ __device__ __forceinline__ void project(const cpx<R> (&psi)[12], cpx<R> (&h)[6])
   }
 }
 
+// Orders what the lanes of one wave exchange through LDS: writes before, reads (and
+// later writes) behind.  The hardware takes a wave's LDS operations in order, so
+// this costs no instruction; the fences keep the compiler from moving accesses
+// across (wave_barrier alone orders the instructions it schedules, not the memory).
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // is right-hand side r selected by the gate?
 __device__ __forceinline__ bool gate_on(const CGScal* g, int mode, int r) {
   if (!g || mode == GATE_NONE) return true;
@@ -600,13 +610,13 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
 #pragma unroll
   for (int chi = 0; chi < 2; chi++) {
     const R* mc = m + chi * DENSE_IMAGE_CHI<R>;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
 #pragma unroll
     for (int c = 0; c < 6; c++) {
       put[(2 * c) * M::ROW] = y[6 * chi + c].re;
       put[(2 * c + 1) * M::ROW] = y[6 * chi + c].im;
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     R b[4], w[4];
 #pragma unroll
     for (int e = 0; e < 4; e++) b[e] = mc[slot * M::ROW + 4 * k + e];

@@ -215,13 +215,13 @@ __global__ void __launch_bounds__(128, 2) force_kernel(const ForceArgs a) {
   }
 #pragma unroll 1
   for (int s = w; s < a.Ns; s += 2) {
-    __builtin_amdgcn_wave_barrier();  // LDS of this wave, in order
+    wave_lds_order();
 #pragma unroll
     for (int k = 0; k < FLOADS; k++) {  // (the clamped lanes write one value to one place)
       buf[put[k]] = v[0][k];
       buf[FCH + put[k]] = v[1][k];
     }
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     const long next = (long)min(s + 2, a.Ns - 1) * a.V * 12;  // (the last slice again behind the end)
 #pragma unroll
     for (int k = 0; k < FLOADS; k++) {

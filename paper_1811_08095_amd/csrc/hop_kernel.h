@@ -769,6 +769,7 @@ template <class P, int NS, bool PLAIN>
 struct HopWaves {
   static constexpr int W =
       sizeof(typename P::real) == 8 ? ODWF_HOP_WAVES64 : ((PLAIN || NS <= DENSE_N) ? ODWF_HOP_WAVES32 : 2);
+  static_assert(W >= 2, "above 256 registers the compiler takes accumulation registers (hop_small_kernel)");
 };
 
 // alpha of the iteration from the partial sums of an earlier launch, into the
@@ -990,9 +991,9 @@ struct SmallLinks {
   }
 };
 
-// (two waves per SIMD keep the register budget at 256: above it the compiler
-// puts the matrix results of the dense programs into accumulation registers,
-// and such builds of this kernel gave wrong results)
+// (two waves per SIMD keep the register budget at 256: above it the compiler puts
+// the matrix results of the dense programs into accumulation registers.  Such
+// builds gave wrong results, by a cause that was not found; the build refuses them)
 template <class P, int NS, bool DAG>
 __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
   using R = typename P::real;
@@ -1077,7 +1078,7 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
   if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab), prog += DENSE_IMAGE<R>;
   pl.scr = scr;
   lk.store(lw, nsb, l);
-  __builtin_amdgcn_wave_barrier();  // the wave's own LDS, in order
+  wave_lds_order();
 
   cpx<R> acc[12];
 #pragma unroll
@@ -1124,9 +1125,9 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
     if (!valid) nval = 0.0;
     for (int m = NS >> 1; m >= 1; m >>= 1) nval += __shfl_xor(nval, m, NS);
     double* tmp = reinterpret_cast<double*>(smem);
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     if (s == 0) tmp[col] = nval;
-    __builtin_amdgcn_wave_barrier();
+    wave_lds_order();
     if (l < nrhs) {
       double tot = 0.0;
       for (int k = 0; k < a.spb; k++) tot += tmp[k * nrhs + l];
