@@ -258,7 +258,9 @@ odwf_status odwf_deff(odwf_solver s, int inverse, const double* mq, const double
  * U_mu(x) -> exp(i eps T) U_mu(x) with T Hermitian and traceless.
  * chi, psi: device canonical spinor fields of ONE right-hand side (Ns * V * 12
  * complex128); F: device complex128 [t][z][y][x][mu][3][3], overwritten, or
- * added to when accumulate != 0 (sums of several bilinears).  FP64. */
+ * added to when accumulate != 0 (sums of several bilinears).  F may reach into
+ * chi or psi (not start at either); the field it reaches into is then copied to a
+ * workspace of the solver first.  FP64. */
 odwf_status odwf_force(odwf_solver s, const void* chi, const void* psi, int accumulate, void* F,
                        void* stream);
 

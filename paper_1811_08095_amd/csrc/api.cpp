@@ -553,6 +553,21 @@ extern "C" odwf_status odwf_force(odwf_solver S, const void* chi, const void* ps
   HIPCHK(hipSetDevice(S->lat->device));
   hipStream_t st = reinterpret_cast<hipStream_t>(stream);
   std::lock_guard<std::mutex> lk(S->mtx);
+  // chi and psi are read while F is written: one that F reaches into is copied first
+  const size_t nfield = (size_t)S->Ns * S->lat->g.V * 12 * 16, nforce = (size_t)S->lat->g.V * 4 * 9 * 16;
+  const void** fields[2] = {&chi, &psi};
+  const char* names[2] = {"f.chi", "f.psi"};
+  for (int k = 0; k < 2; k++) {
+    const uintptr_t v = reinterpret_cast<uintptr_t>(*fields[k]), f = reinterpret_cast<uintptr_t>(F);
+    if (f + nforce <= v || v + nfield <= f) continue;
+    void* copy = S->workspace(st).get(names[k], nfield);
+    if (!copy) {
+      set_error("odwf_force: out of device memory for workspaces");
+      return ODWF_ENOMEM;
+    }
+    HIPCHK(hipMemcpyAsync(copy, *fields[k], nfield, hipMemcpyDeviceToDevice, st));
+    *fields[k] = copy;
+  }
   const void* const links[2] = {S->lat->U64[0], S->lat->U64[1]};
   HIPCHK(launch_force(chi, psi, links, F, S->Ns, S->lat->bc_t, accumulate, S->lat->g, st));
   return ODWF_OK;

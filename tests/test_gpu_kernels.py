@@ -144,3 +144,26 @@ def test_force_block_edges(dims, Ns, bc):
     assert per <= 1e-12
     sol.close()
     lat.close()
+
+
+@pytest.mark.parametrize("accumulate", [False, True])
+@pytest.mark.parametrize("where", ["chi end", "psi end", "psi start"])
+def test_force_into_its_inputs(where, accumulate):
+    """F that starts inside chi or psi, or ends inside psi: as if it lay apart.
+    Blocks enough that some still read when others have written."""
+    import torch
+    dims, Ns = (16, 8, 8, 8), 4
+    U, w, lat, sol = _mk(dims, Ns, 15)
+    V = int(np.prod(dims))
+    nf, nF = Ns * V * 12, V * 36
+    buf = torch.from_numpy(synth.make_source(dims, Ns, 3, 4500)).cuda().reshape(-1)
+    # [chi | psi | rest] with F over the end of chi and the start of psi, or the end of psi
+    at = {"chi end": nf - nF // 2, "psi end": 2 * nf - nF + 12, "psi start": nf - nF + 12}[where]
+    chi, psi, F = buf[:nf], buf[nf:2 * nf], buf[at:at + nF]
+    shape, fshape = sol.spinor_shape(1), lat.shape_tzyx + (4, 3, 3)
+    F0, chi0, psi0 = F.clone().view(fshape), chi.clone().view(shape), psi.clone().view(shape)
+    ref = sol.force(chi0, psi0, F=F0, accumulate=accumulate)
+    out = sol.force(chi.view(shape), psi.view(shape), F=F.view(fshape), accumulate=accumulate)
+    assert torch.equal(out, ref)
+    sol.close()
+    lat.close()
