@@ -21,6 +21,8 @@
 #include <cmath>
 #include <cstring>
 
+#include "poller.h"
+
 namespace odwf {
 
 hipError_t apply_D(const OpCtx& c, const HV& ye, const HV& yo, const HV& oe, const HV& oo, const M5Prog& po) {
@@ -99,44 +101,6 @@ hipError_t apply_normal(const OpCtx& c, const HV& p, const HV& t, const HV& v, c
   const HV* o = (k4opt && k4opt->cg_r) ? nullptr : &out;
   return hop(c, 0, 1, t, o, k4);
 }
-
-// ---------------------------------------------------------------------------
-// host polling of the device scalars, a few iterations behind the GPU
-// ---------------------------------------------------------------------------
-struct Poller {
-  CGScal* host = nullptr;  // pinned, 4 slots
-  hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
-  long k = 0;
-  hipError_t init() {
-    HIPRET(hipHostMalloc((void**)&host, 4 * MAXRHS * sizeof(CGScal), hipHostMallocDefault));
-    for (int i = 0; i < 4; i++) HIPRET(hipEventCreateWithFlags(&ev[i], hipEventDisableTiming));
-    return hipSuccess;
-  }
-  ~Poller() {
-    if (k > 0) (void)hipEventSynchronize(ev[(k - 1) % 4]);  // the last step writes its mirror until then
-    for (int i = 0; i < 4; i++)
-      if (ev[i]) (void)hipEventDestroy(ev[i]);
-    if (host) (void)hipHostFree(host);
-  }
-  // the mirror the next step writes; its previous contents must have been read
-  CGScal* next() {
-    const int slot = (int)(k % 4);
-    if (k >= 4 && hipEventSynchronize(ev[slot]) != hipSuccess) return nullptr;
-    return host + slot * MAXRHS;
-  }
-  hipError_t push(hipStream_t st) {  // behind that step
-    HIPRET(hipEventRecord(ev[k % 4], st));
-    k++;
-    return hipSuccess;
-  }
-  // scalars as of `lag` pushes ago (nullptr if none yet)
-  const CGScal* view(int lag) {
-    if (k <= lag) return nullptr;
-    const int slot = (int)((k - 1 - lag) % 4);
-    if (hipEventSynchronize(ev[slot]) != hipSuccess) return nullptr;
-    return host + slot * MAXRHS;
-  }
-};
 
 static hipError_t read_scal(const CGScal* d, CGScal* h, int nrhs, hipStream_t st) {
   HIPRET(hipMemcpyAsync(h, d, nrhs * sizeof(CGScal), hipMemcpyDeviceToHost, st));
@@ -293,7 +257,9 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
   CHK(launch_fin(FIN_F2, partial, nb_vec, nrhs, dscal_out, nullptr, st));
 
   Poller poll;
-  CHK(poll.init());
+  CHK(poll.init(st));
+  CGScal* mirror;         // of the step at hand
+  const CGScal* seen;     // records of an earlier step, or null
   CGScal cur[MAXRHS];
   int reliable = 0, outer = 0;
   std::vector<int> inner_iters(nrhs, 0), outer_q(nrhs, 0);
@@ -335,11 +301,12 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(c64, p, o0, e2, e2, partial, &k4));
-        CHK(launch_cg_step(PREC64, r.d, nullptr, p.d, nullptr, e1.d, nullptr, nullptr, partial, nbh, dscal, poll.next(),
+        CHK(poll.next(&mirror));
+        CHK(launch_cg_step(PREC64, r.d, nullptr, p.d, nullptr, e1.d, nullptr, nullptr, partial, nbh, dscal, mirror,
                            h, nrhs, Ns, st));
-        CHK(poll.push(st));
-        const CGScal* v = poll.view(2);
-        if (v && !any(v, 0)) break;
+        CHK(poll.push());
+        CHK(poll.view(2, &seen));
+        if (seen && !any(seen, 0)) break;
       }
       // confirm with the true residual; continue where it has drifted
       CHK(true_residual(c64, e0, e1, o0, e2, partial, dscal, dres));
@@ -363,11 +330,12 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(cin, p, t, v, v, partial, &k4));
-        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, poll.next(), h, nrhs,
+        CHK(poll.next(&mirror));
+        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, mirror, h, nrhs,
                            Ns, st));
-        CHK(poll.push(st));
-        const CGScal* vw = poll.view(2);
-        if (vw && (!any(vw, 0) || any(vw, 1))) break;
+        CHK(poll.push());
+        CHK(poll.view(2, &seen));
+        if (seen && (!any(seen, 0) || any(seen, 1))) break;
       }
       // reliable update: y += x_s, r = f - N y in FP64, restart the FP32 residual
       CHK(launch_vec_flush(inner, xs.d, xs.sc, e1.d, 1, h, nrhs, Ns, st));
@@ -410,11 +378,12 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         k4.scal = dscal;
         k4.partial = partial;
         CHK(apply_normal(cin, p, t, v, v, partial, &k4));
-        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, poll.next(), h, nrhs,
+        CHK(poll.next(&mirror));
+        CHK(launch_cg_step(inner, rr.d, rr.sc, p.d, p.sc, xs.d, xs.sc, nullptr, partial, nbh, dscal, mirror, h, nrhs,
                            Ns, st));
-        CHK(poll.push(st));
-        const CGScal* vw = poll.view(2);
-        if (vw && !any(vw, 0)) break;
+        CHK(poll.push());
+        CHK(poll.view(2, &seen));
+        if (seen && !any(seen, 0)) break;
       }
       CGScal fin[MAXRHS];
       CHK(read_scal(dscal, fin, nrhs, st));
