@@ -5,6 +5,7 @@ instructions disabled, and linked into a shared library with a plain C ABI
 (include/odwf.h).
 """
 import concurrent.futures as cf
+import json
 import os
 import re
 import subprocess
@@ -25,24 +26,27 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall",
           "-Rpass-analysis=kernel-resource-usage"]
 
 
-def check_usage(messages: str) -> None:
-    """Refuse kernels that hold values in accumulation registers, from the
-    compiler's resource-usage remarks.  Every kernel here fits the 256 vector
-    registers that its launch bounds leave it.  Builds of the four-wave hopping
+def check_usage(messages: str) -> dict:
+    """Scratch bytes a lane of every kernel, from the compiler's resource-usage
+    remarks, refusing kernels that hold values in accumulation registers.  Every kernel here fits the
+    256 vector registers that its launch bounds leave it.  Builds of the four-wave hopping
     kernel with a larger budget, in which the matrix results went to accumulation
     registers, gave wrong results for a reason that is not known (the generated
     code shows none: LDS accesses in order, matrix results waited for as in the
     right builds), so no such kernel is let into the library."""
-    name = None
+    name, scratch = None, {}
     for line in messages.splitlines():
-        m = re.search(r"remark: .*?(Function Name|AGPRs): (\S+)", line)
+        m = re.search(r"remark: .*?(Function Name|AGPRs|ScratchSize)(?: \[bytes/lane\])?: (\S+)", line)
         if not m:
             continue
         if m[1] == "Function Name":
             name = m[2]
+        elif m[1] == "ScratchSize":
+            scratch[name] = int(m[2])
         elif int(m[2]) > 0:
             raise RuntimeError(f"{name} uses {m[2]} accumulation registers: give it a launch bound "
                                "that keeps it within 256 vector registers")
+    return scratch
 
 
 def _without_remarks(messages: str) -> str:
@@ -72,7 +76,8 @@ def _compile(src: str, verbose: bool, build_dir: str, defines) -> str:
     if messages:
         print(messages, file=sys.stderr, flush=True)
     r.check_returncode()
-    check_usage(r.stderr)
+    with open(os.path.splitext(obj)[0] + ".scratch.json", "w") as f:
+        json.dump(check_usage(r.stderr), f)
     return obj
 
 

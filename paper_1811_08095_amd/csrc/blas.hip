@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(256) vec_norm2_kernel(const void* v, const flo
 #pragma unroll
       for (int c = 0; c < 12; c++) acc += (double)cnorm2(a[c]);
     }
-  block_reduce_rhs(sl < spb ? acc : 0.0, Ns, spb, nrhs, red, partial, blockIdx.x);
+  block_reduce_rhs(sl < spb ? acc : 0.0, Ns, spb, nrhs, red, partial, blockIdx.x, threadIdx.x);
 }
 
 #define ODWF_PREC_SWITCH(prec, KERNEL, ...)                                             \

@@ -554,10 +554,10 @@ constexpr int DENSE_IMAGE_CHI = DENSE_N * Mfma<R>::ROW + 2 * DENSE_N;  // rows p
 template <class R>
 constexpr int DENSE_IMAGE = 2 * DENSE_IMAGE_CHI<R>;
 template <class R>
-__device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab) {
+__device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab, int tid) {
   constexpr int K = (DENSE_LEN + 255) / 256;  // a thread's elements in flight together (256 threads)
   constexpr int NN = DENSE_N * DENSE_N;
-  for (int i0 = threadIdx.x; i0 < DENSE_LEN; i0 += K * blockDim.x) {
+  for (int i0 = tid; i0 < DENSE_LEN; i0 += K * blockDim.x) {
     double v[K];
 #pragma unroll
     for (int k = 0; k < K; k++) v[k] = tab[min(i0 + k * (int)blockDim.x, DENSE_LEN - 1)];
@@ -572,7 +572,7 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
 
 // y <- M y for the 12 components of every lane's 5D site; m: LDS image; scr:
 // DENSE_SCRATCH reals of this wave (16-byte aligned); rho_p / rho_m: rho of the
-// lane's right-hand side per chirality.  The rank-1 term rho u w^T rides on a
+// lane's right-hand side per chirality; tid: the thread's index in its block.  The rank-1 term rho u w^T rides on a
 // fifth matrix instruction: lane group k contributes rho times its part of
 // w . x (slots 4 k .. 4 k + 3) as element k of the operand row, and u in every
 // row of the second operand sums the parts.  Right-hand sides of any masses
@@ -586,11 +586,11 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
 // not of the results: it runs beside the LDS round trip.)  Within its own column, of
 // 16 slices too, such a value may reach every slice.
 template <int NS, class R>
-__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m) {
+__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m, int tid) {
   using M = Mfma<R>;
   using V = typename M::V;
   constexpr int NN = DENSE_N * M::ROW;
-  const int lane = threadIdx.x & 63, slot = lane & 15, k = lane >> 4;
+  const int lane = tid & 63, slot = lane & 15, k = lane >> 4;
   R* put = scr + k * M::SET + (slot ^ M::swap(k));
   const int set_i = M::set_of(slot);
   const R* get = scr + set_i * M::SET + M::real_of(slot) * M::ROW + ((4 * k) ^ M::swap(set_i));
@@ -673,12 +673,12 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
 // ---------------------------------------------------------------------------
 template <class R, int NS>
 __device__ __forceinline__ void column_pass_lds(cpx<R>* buf, int nsb, int nrhs, const M5Prog& prog,
-                                                const R* coef, const R* kap) {
+                                                const R* coef, const R* kap, int tid) {
   constexpr int NSP = NS + 1;
   const int per = nsb * nrhs * 6;
   const int ipc = (per + 63) & ~63;
-  const int lane = threadIdx.x & 63;
-  for (int base = threadIdx.x & ~63; base < 2 * ipc; base += blockDim.x) {
+  const int lane = tid & 63;
+  for (int base = tid & ~63; base < 2 * ipc; base += blockDim.x) {
     const int chi = __builtin_amdgcn_readfirstlane(base / ipc);
     const int q = base - chi * ipc + lane;
     if (q < per) {
@@ -717,9 +717,8 @@ __device__ __forceinline__ void column_pass_lds(cpx<R>* buf, int nsb, int nrhs, 
 // tmp: LDS of at least nsl * nrhs doubles.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void block_reduce_rhs(double v, int Ns, int nsl, int nrhs, double* tmp,
-                                                 double* partial, long slot) {
+                                                 double* partial, long slot, int tid) {
   for (int m = Ns >> 1; m >= 1; m >>= 1) v += __shfl_xor(v, m, Ns);
-  const int tid = threadIdx.x;
   const int g = tid / Ns;
   __syncthreads();  // tmp may alias LDS the block used before
   if ((tid & (Ns - 1)) == 0 && g < nsl * nrhs) tmp[g] = v;

@@ -60,7 +60,7 @@ struct LinkFmt<SPB16> : LinkF12 {};
 // hop sums round exactly as with the factor applied at the end)
 template <class P>
 __device__ __forceinline__ void stage_links(const void* links, long j0, int nsb,
-                                            cpx<typename P::real>* lnk) {
+                                            cpx<typename P::real>* lnk, int tid) {
   using R = typename P::real;
   const int nmat = nsb * 8;
   if constexpr (LinkFmt<P>::REALS == 18) {
@@ -69,7 +69,7 @@ __device__ __forceinline__ void stage_links(const void* links, long j0, int nsb,
     // five chunks of a thread in flight (all of them at Ns = 16: a round trip,
     // not one per chunk)
     constexpr int K = 5;
-    for (int q0 = threadIdx.x; q0 < nmat * 9; q0 += K * blockDim.x) {
+    for (int q0 = tid; q0 < nmat * 9; q0 += K * blockDim.x) {
       uint4 v[K];
 #pragma unroll
       for (int k = 0; k < K; k++) v[k] = src[min(q0 + k * (int)blockDim.x, nmat * 9 - 1)];
@@ -83,7 +83,7 @@ __device__ __forceinline__ void stage_links(const void* links, long j0, int nsb,
     }
   } else {
     const float4* src = reinterpret_cast<const float4*>(links) + j0 * 8 * 3;
-    for (int m = threadIdx.x; m < nmat; m += blockDim.x) {
+    for (int m = tid; m < nmat; m += blockDim.x) {
 #if ODWF_NT_LINKS
       // links are read once per launch: keep them from displacing spinor rows in L2
       typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -329,7 +329,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, const HopIo& io, 
                                              const ProgLds<typename P::real>& pl, const typename P::real* kap,
                                              int xmode, cpx<typename P::real> (&xv)[12],
                                              cpx<typename P::real> (&rv)[12], const typename P::real (&rho)[6],
-                                             typename P::real alpha, bool cg_pre) {
+                                             typename P::real alpha, bool cg_pre, int tid) {
   using R = typename P::real;
   constexpr int NSP = NS + 1;
   const int nrhs = a.nrhs;
@@ -337,8 +337,8 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, const HopIo& io, 
   auto program = [&](int p, const DenseArg& dn, const M5Prog& prog, R* lds, cpx<R>(&v)[12]) {
     if constexpr (NS <= DENSE_N) {
       if (!dn.tab) return;
-      if constexpr (PRE) dense_apply<NS>(v, lds, pl.scr, rho[2 * p], rho[2 * p + 1]);
-      else dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
+      if constexpr (PRE) dense_apply<NS>(v, lds, pl.scr, rho[2 * p], rho[2 * p + 1], tid);
+      else dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], tid);
     } else {
       if (prog.n == 0) return;
       cpx<R>* buf = reinterpret_cast<cpx<R>*>(lds);
@@ -348,7 +348,7 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, const HopIo& io, 
         for (int c = 0; c < 12; c++) column(buf, c) = v[c];
       }
       __syncthreads();
-      column_pass_lds<R, NS>(buf, nsb, nrhs, prog, reinterpret_cast<const R*>(a.coef), kap);
+      column_pass_lds<R, NS>(buf, nsb, nrhs, prog, reinterpret_cast<const R*>(a.coef), kap, tid);
       __syncthreads();
       if (valid) {
 #pragma unroll
@@ -784,14 +784,13 @@ __device__ __forceinline__ void fin_block(const HopArgs& a, double* tmp) {
   a.fin_scal[SCAL_COPY + r] = c;
 }
 
-// one block's sites
+// one block's sites; tid: the thread's index in the block
 template <class P, int NS, bool DAG, bool PLAIN>
-__device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
+__device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb, int tid) {
   using R = typename P::real;
   constexpr bool DENSE = !PLAIN && NS <= DENSE_N;
   extern __shared__ __align__(16) unsigned char smem[];
   const int nrhs = a.nrhs;
-  const int tid = threadIdx.x;
   const int col = tid / NS, s = tid - col * NS;  // column (site, right-hand side) of the block, and slice
   const int sl = nrhs == 1 ? col : col / nrhs;
   const int r = col - sl * nrhs;
@@ -807,21 +806,21 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
   R* prog = reinterpret_cast<R*>(lnk + (size_t)a.spb * 8 * 9);
   ProgLds<R> pl = {prog, prog, prog, nullptr};
   R* kap = nullptr;
-  stage_links<P>(a.links, j0, nsb, lnk);
+  stage_links<P>(a.links, j0, nsb, lnk, tid);
   bool x_first = false;
   if constexpr (DENSE) {
     if (a.dn_h.tab) {
-      dense_stage<R>(pl.h, a.dn_h.tab);
+      dense_stage<R>(pl.h, a.dn_h.tab, tid);
       prog += DENSE_IMAGE<R>;
     }
     pl.x = prog;
     if (a.dn_x.tab) {
-      dense_stage<R>(pl.x, a.dn_x.tab);
+      dense_stage<R>(pl.x, a.dn_x.tab, tid);
       prog += DENSE_IMAGE<R>;
     }
     pl.o = prog;
     if (a.dn_o.tab) {
-      dense_stage<R>(pl.o, a.dn_o.tab);
+      dense_stage<R>(pl.o, a.dn_o.tab, tid);
       prog += DENSE_IMAGE<R>;
     }
     pl.scr = prog + (tid >> 6) * DENSE_SCRATCH<R>;
@@ -843,7 +842,7 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
         for (int c = 0; c < 12; c++) buf[((size_t)(sl * nrhs + r) * 12 + c) * (NS + 1) + s] = xv[c];
       }
       __syncthreads();
-      column_pass_lds<R, NS>(buf, nsb, nrhs, a.prog_x, reinterpret_cast<const R*>(a.coef), kap);
+      column_pass_lds<R, NS>(buf, nsb, nrhs, a.prog_x, reinterpret_cast<const R*>(a.coef), kap, tid);
     }
   }
   double* red = reinterpret_cast<double*>(prog);
@@ -872,8 +871,8 @@ __device__ __forceinline__ void hop_block(const HopArgs& a, uint32_t lb) {
   cpx<R> xv[12], rv[12];
   const R rho[6] = {};
   const double nval = fused_tail<P, NS, false>(a, first_io(a), acc, valid, (long)j0 + slr, sl, r, s, nsb, pl, kap,
-                                               x_first ? X_LDS : X_LOAD, xv, rv, rho, R(0), false);
-  if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, lb);
+                                               x_first ? X_LDS : X_LOAD, xv, rv, rho, R(0), false, tid);
+  if (a.partial) block_reduce_rhs(valid ? nval : 0.0, NS, a.spb, nrhs, red, a.partial, lb, tid);
 }
 
 template <class P, int NS, bool DAG, bool PLAIN>
@@ -890,19 +889,34 @@ __global__ void __launch_bounds__(256, (HopWaves<P, NS, PLAIN>::W)) hop_kernel(c
     }
   }
   if (!gate_any(a.gate, a.gate_mode, a.nrhs)) return;  // whole block idle
-  hop_block<P, NS, DAG, PLAIN>(a, lb);
+  hop_block<P, NS, DAG, PLAIN>(a, lb, threadIdx.x);
 }
 
 // Launches gated to pending updates find nothing to do in most iterations, and
-// then cost the passing of their blocks, of which two a CU fit in LDS: above
-// that number LOOP_BLOCKS blocks walk the sites.  Twelve slots on 8^4 x 16 (2048
-// blocks, FP64): 10.0 -> 8.7 us a launch, one in twelve of them with work.
-constexpr int LOOP_BLOCKS = 512;
+// then cost the passing of their blocks.  Above the blocks that fit the chip at
+// once (a span) a block here walks several, a span apart: up to eight spans in a
+// single one, beyond them two to a block, since blocks that walk alone drift apart
+// and lose the rows they share in L2.  us a launch with work / without, against
+// hop_kernel: 16^4 x 16 (4 spans) 85 / 4.6 and 89 / 4.6; 16^3 x 32 x 16 (8) 168 / 4.6
+// and 174 / 4.7; 8^4 x 16 of twelve slots (4) 45 / 4.5 and 43 / 6.2; 32^3 x 16 x 16
+// (32) 654 / 4.9 and 623 / 10 (745 / 4.8 in one span, 717 / 4.7 with four to a
+// block); 64^3 x 32 x 16 (512) 10750 / 43 and 10460 / 119 (14430 / 4.5, 11750 / 23).
+constexpr int LOOP_SPANS = 8, LOOP_STEPS = 2;
+__host__ __device__ inline uint32_t loop_span(int threads) { return 256 * (512 / threads); }  // two waves per SIMD
 template <class P, int NS, bool DAG>
 __global__ void __launch_bounds__(256, (HopWaves<P, NS, false>::W)) hop_loop_kernel(const HopArgs a) {
   if (!gate_any(a.gate, a.gate_mode, a.nrhs)) return;  // whole block idle
-  for (uint32_t lb = blockIdx.x; lb < (uint32_t)a.nblocks; lb += gridDim.x) {
-    hop_block<P, NS, DAG, false>(a, lb);
+  const uint32_t span = loop_span(blockDim.x);
+  const uint32_t steps = gridDim.x == span ? LOOP_SPANS : LOOP_STEPS;
+  uint32_t lb = blockIdx.x / span * span * steps + blockIdx.x % span;
+  for (uint32_t k = 0; k < steps && lb < (uint32_t)a.nblocks; k++, lb += span) {
+    // the arguments and the thread's index again for every block: what follows from
+    // them would be formed outside the loop and kept through it, and does not fit
+    // the registers
+    auto* args = __builtin_amdgcn_kernarg_segment_ptr();
+    int tid = threadIdx.x;
+    asm volatile("" : "+s"(args), "+v"(tid));
+    hop_block<P, NS, DAG, false>(*(const HopArgs*)args, lb, tid);
     __syncthreads();  // LDS of these sites is done with
   }
 }
@@ -1071,11 +1085,11 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
     }
   }
   ProgLds<R> pl = {prog, nullptr, nullptr, nullptr};
-  if (a.dn_h.tab) dense_stage<R>(prog, a.dn_h.tab), prog += DENSE_IMAGE<R>;
+  if (a.dn_h.tab) dense_stage<R>(prog, a.dn_h.tab, tid), prog += DENSE_IMAGE<R>;
   pl.x = prog;
-  if (a.dn_x.tab) dense_stage<R>(prog, a.dn_x.tab), prog += DENSE_IMAGE<R>;
+  if (a.dn_x.tab) dense_stage<R>(prog, a.dn_x.tab, tid), prog += DENSE_IMAGE<R>;
   pl.o = prog;
-  if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab), prog += DENSE_IMAGE<R>;
+  if (a.dn_o.tab) dense_stage<R>(prog, a.dn_o.tab, tid), prog += DENSE_IMAGE<R>;
   pl.scr = scr;
   lk.store(lw, nsb, l);
   wave_lds_order();
@@ -1120,7 +1134,7 @@ __global__ void __launch_bounds__(256, 2) hop_small_kernel(const HopArgs a) {
     for (int c = 0; c < 12; c++) acc[c] = cadd(acc[c], cpx<R>{d[(2 * c) * 64], d[(2 * c + 1) * 64]});
   }
   double nval = fused_tail<P, NS, true>(a, io, acc, valid, j, sl, r, s, nsb, pl, nullptr, X_LOAD, xv, rv, rho, alpha,
-                                        cg_update);
+                                        cg_update, tid);
   if (a.partial) {  // one wave: LDS of its own, in order
     if (!valid) nval = 0.0;
     for (int m = NS >> 1; m >= 1; m >>= 1) nval += __shfl_xor(nval, m, NS);
@@ -1176,8 +1190,10 @@ static hipError_t launch_hop_t(HopArgs a, int dag, hipStream_t st) {
   const int block = (a.spb * inner + 63) & ~63;  // whole waves, <= 256
   const size_t sm = hop_smem<P, NS>(a, a.plain);
   if constexpr (sizeof(typename P::real) == 8) {
-    if (a.gate_mode == GATE_UPDATE && !a.plain && !a.fin_partial && a.nblocks > LOOP_BLOCKS) {
-      const dim3 grid(LOOP_BLOCKS);
+    const int span = loop_span(block);
+    if (a.gate_mode == GATE_UPDATE && !a.plain && !a.fin_partial && a.nblocks > span) {
+      const int walk = span * (a.nblocks <= span * LOOP_SPANS ? LOOP_SPANS : LOOP_STEPS);  // of a span of blocks
+      const dim3 grid((a.nblocks + walk - 1) / walk * span);
       if (dag) hipLaunchKernelGGL((hop_loop_kernel<P, NS, true>), grid, dim3(block), sm, st, a);
       else hipLaunchKernelGGL((hop_loop_kernel<P, NS, false>), grid, dim3(block), sm, st, a);
       return hipGetLastError();

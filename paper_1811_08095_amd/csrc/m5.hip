@@ -37,7 +37,7 @@ __global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in
     for (int c = 0; c < 12; c++) b[c * NSP] = v[c];
   }
   __syncthreads();
-  column_pass_lds<R, NS>(buf, nsb, nrhs, prog, reinterpret_cast<const R*>(coefp), kap);
+  column_pass_lds<R, NS>(buf, nsb, nrhs, prog, reinterpret_cast<const R*>(coefp), kap, tid);
   __syncthreads();
   if (!valid) return;
   const cpx<R>* b = buf + ((size_t)(sl * nrhs + r) * 12) * NSP + s;
@@ -72,9 +72,9 @@ __global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const 
   if (valid) load_site<P>(in, in_sc, j, 0, s, 1, NS, v);
   if (dn.tab) {
     const int r = nrhs > 1 ? (int)(j % nrhs) : 0;
-    dense_stage<R>(mat, dn.tab);
+    dense_stage<R>(mat, dn.tab, threadIdx.x);
     __syncthreads();
-    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r]);
+    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], threadIdx.x);
   }
   if (!valid) return;
   if (diag) {

@@ -125,6 +125,47 @@ def test_wide_batch_updates():
     assert torch.equal(run([0])[0], mixed[0])
 
 
+# (lattice, N_s, slots, inner): the gated updates in one span of blocks that walk on
+# their own (up to eight spans: 4096 blocks of 256 threads) and in pairs above, with
+# a last pair that is not whole; blocks of 128, 192 and 256 threads
+LOOPING = [((8, 8, 8, 8), 4, 16, odwf.FP32), ((6, 8, 8, 8), 8, 12, odwf.FP64), ((8, 8, 8, 12), 16, 12, odwf.FP64),
+           ((8, 8, 8, 18), 32, 6, odwf.FP32), ((10, 8, 10, 12), 16, 12, odwf.FP32), ((8, 12, 16, 16), 16, 1, odwf.FP64),
+           ((16, 16, 8, 10), 8, 16, odwf.FP32)]
+
+
+@pytest.mark.parametrize("dims,Ns,k,inner", LOOPING, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_looping_updates(dims, Ns, k, inner):
+    """A slot's solution meets its tolerance, and is the same bits beside others."""
+    import torch
+    U, w, lat, sol = _mk(dims, Ns, 16)
+    b = synth.make_source(dims, Ns, 1, 4600)[0]
+    dev = torch.from_numpy(b).cuda().contiguous()
+    other = torch.from_numpy(synth.make_source(dims, Ns, 1, 4601)[0]).cuda().contiguous()
+
+    def run(mixed):
+        bt = odwf.Batch(sol, k, inner=inner)
+        q = bt.admit(dev, 0.4, 1e-9)
+        if mixed:
+            bt.step(3)
+            bt.admit(other, 0.9, 1e-7)
+        for _ in range(200):
+            bt.step(8)
+            if bt.poll(q)[0]:
+                break
+        x = torch.zeros_like(dev)
+        st = bt.retire(q, x)
+        assert st["status"] == odwf.OK and st["true_rel_resid"] <= 1e-9
+        return x
+
+    print(f"looping {dims} Ns={Ns} k={k} inner={inner}", flush=True)
+    x = run(False)
+    Dx = oracle.apply(oracle.OP_D, U, x.cpu().numpy(), M0, w, 0.4 / (2 * M0))
+    assert _rel(Dx, b) <= 1e-6
+    assert k == 1 or torch.equal(run(True), x)
+    sol.close()
+    lat.close()
+
+
 # rows shorter and longer than a block's 16 sites, rows that end inside a block, a
 # ragged last block, planes that are no whole number of blocks
 FORCE = [((10, 2, 2, 4), 4, -1), ((18, 2, 4, 2), 8, 1), ((34, 2, 2, 2), 4, -1), ((6, 6, 2, 4), 4, -1),
