@@ -180,24 +180,27 @@ extern "C" odwf_status odwf_solver_create(odwf_lattice L, int Ns, double m0, con
       }
     }
   }
-  std::vector<double> dn;
-  if (dense_ns(Ns)) {
-    dn.resize((size_t)NDENSE * DENSE_LEN);
-    dense_tables(Ns, m0, omega, dn.data(), S->dense_q);
-  }
-  if (hipMalloc(&S->coef64, c64.size() * sizeof(double)) != hipSuccess ||
-      hipMalloc(&S->coef32, c32.size() * sizeof(float)) != hipSuccess ||
-      (!dn.empty() && hipMalloc(&S->dense, dn.size() * sizeof(double)) != hipSuccess)) {
+  // one device block: FP64 and FP32 coefficients, dense programs
+  const size_t n64 = c64.size() * sizeof(double), n32 = c32.size() * sizeof(float);
+  const size_t ndense = dense_ns(Ns) ? (size_t)NDENSE * DENSE_LEN : 0;
+  std::vector<double> host((n64 + n32) / sizeof(double) + ndense);
+  std::memcpy(host.data(), c64.data(), n64);
+  std::memcpy(reinterpret_cast<char*>(host.data()) + n64, c32.data(), n32);
+  if (ndense) dense_tables(Ns, m0, omega, host.data() + (n64 + n32) / sizeof(double), S->dense_q);
+  if (hipMalloc(&S->coef64, host.size() * sizeof(double)) != hipSuccess) {
     (void)hipGetLastError();
-    if (S->coef64) (void)hipFree(S->coef64);
-    if (S->coef32) (void)hipFree(S->coef32);
     delete S;
     set_error("odwf_solver_create: out of device memory");
     return ODWF_ENOMEM;
   }
-  HIPCHK(hipMemcpy(S->coef64, c64.data(), c64.size() * sizeof(double), hipMemcpyHostToDevice));
-  HIPCHK(hipMemcpy(S->coef32, c32.data(), c32.size() * sizeof(float), hipMemcpyHostToDevice));
-  if (!dn.empty()) HIPCHK(hipMemcpy(S->dense, dn.data(), dn.size() * sizeof(double), hipMemcpyHostToDevice));
+  S->coef32 = static_cast<char*>(S->coef64) + n64;
+  if (ndense) S->dense = reinterpret_cast<double*>(static_cast<char*>(S->coef64) + n64 + n32);
+  const hipError_t copied = hipMemcpy(S->coef64, host.data(), host.size() * sizeof(double), hipMemcpyHostToDevice);
+  if (copied != hipSuccess) {
+    (void)hipFree(S->coef64);
+    delete S;
+    HIPCHK(copied);
+  }
   *out = S;
   return ODWF_OK;
 }
@@ -208,8 +211,6 @@ extern "C" void odwf_solver_destroy(odwf_solver S) {
   (void)hipDeviceSynchronize();
   for (auto& kv : S->ws) delete kv.second;
   if (S->coef64) (void)hipFree(S->coef64);
-  if (S->coef32) (void)hipFree(S->coef32);
-  if (S->dense) (void)hipFree(S->dense);
   delete S;
 }
 

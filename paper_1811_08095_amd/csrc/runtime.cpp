@@ -114,54 +114,49 @@ M5Prog prog_omega2() { return mk({op(M5_SCALE, CF_OMEGA2)}); }
 // rank-1 term: A^{-1} = P B^{-1} omega has u = e_0 - c_0 P0 B0^{-1} e_0,
 // w^T = e_l^T B0^{-1} omega, q = c_0 (B0^{-1})_{l0}; A = omega^{-1} B P^{-1} has
 // u = omega^{-1} (c_0 e_0 - B0 P0^{-1} e_0), w^T = e_l^T P0^{-1}, q = (P0^{-1})_{l0}.
+// P0^{-1} has entries (-1)^{i-j}, B0^{-1} follows a column at a time, and a factor is
+// bidiagonal, so a product's entry is a sum of two: N^2 operations a matrix (16
+// slices: 18 us in all).
 void dense_tables(int Ns, double m0, const double* omega, double* tab, double q[][2]) {
   using ld = long double;
-  using Mat = std::vector<std::vector<ld>>;
+  using Mat = ld[DENSE_N][DENSE_N];
   const int N = Ns, l = Ns - 1;
-  auto zeros = [&]() { return Mat(N, std::vector<ld>(N, 0.0L)); };
-  auto mul = [&](const Mat& x, const Mat& y) {
-    Mat z = zeros();
-    for (int i = 0; i < N; i++)
-      for (int k = 0; k < N; k++)
-        for (int j = 0; j < N; j++) z[i][j] += x[i][k] * y[k][j];
-    return z;
-  };
-  auto inv_lo = [&](const Mat& x) {  // inverse of a lower bidiagonal matrix
-    Mat z = zeros();
-    for (int j = 0; j < N; j++) {
-      z[j][j] = 1.0L / x[j][j];
-      for (int i = j + 1; i < N; i++) z[i][j] = -x[i][i - 1] * z[i - 1][j] / x[i][i];
-    }
-    return z;
-  };
   std::memset(tab, 0, sizeof(double) * NDENSE * DENSE_LEN);
-  const int rep = DENSE_N / N;
   for (int chi = 0; chi < 2; chi++) {
-    std::vector<ld> w(N), c(N);
-    Mat P0 = zeros(), B0 = zeros();
+    ld w[DENSE_N], a[DENSE_N], c[DENSE_N], u[DENSE_N], v[DENSE_N];
+    Mat P0 = {}, Pi = {}, Bi = {}, m = {};
     for (int s = 0; s < N; s++) {
       w[s] = omega[chi ? N - 1 - s : s];
+      a[s] = (4.0L - m0) * w[s] + 1.0L;
       c[s] = (4.0L - m0) * w[s] - 1.0L;
-      P0[s][s] = 1.0L;
-      B0[s][s] = (4.0L - m0) * w[s] + 1.0L;
-      if (s > 0) P0[s][s - 1] = 1.0L, B0[s][s - 1] = c[s];
     }
-    const Mat Pi = inv_lo(P0), Bi = inv_lo(B0);
-    auto put = [&](int id, const Mat& m, const std::vector<ld>& u, const std::vector<ld>& v, ld qq, bool tr) {
+    for (int j = 0; j < N; j++) {
+      P0[j][j] = Pi[j][j] = 1.0L;
+      Bi[j][j] = 1.0L / a[j];
+      if (j > 0) P0[j][j - 1] = 1.0L;
+      for (int i = j + 1; i < N; i++) {
+        Pi[i][j] = -Pi[i - 1][j];
+        Bi[i][j] = -c[i] * Bi[i - 1][j] / a[i];
+      }
+    }
+    auto put = [&](int id, const Mat& m, const ld* u, const ld* v, ld qq, bool tr) {
       double* t = tab + (size_t)id * DENSE_LEN + chi * DENSE_CHI;
-      auto sl = [&](int s) { return chi ? N - 1 - s : s; };  // local index of slice s
-      for (int b = 0; b < rep; b++)
-        for (int i = 0; i < N; i++) {
-          for (int j = 0; j < N; j++)
-            t[(b * N + i) * DENSE_N + b * N + j] = (double)(tr ? m[sl(j)][sl(i)] : m[sl(i)][sl(j)]);
-          t[DENSE_N * DENSE_N + b * N + i] = (double)(tr ? v[sl(i)] : u[sl(i)]);
-          t[DENSE_N * DENSE_N + DENSE_N + b * N + i] = (double)(tr ? u[sl(i)] : v[sl(i)]);
+      for (int i = 0; i < N; i++) {
+        const int si = chi ? l - i : i;  // local index of slice i
+        for (int b = 0; b < DENSE_N; b += N) {
+          for (int j = 0; j < N; j++) {
+            const int sj = chi ? l - j : j;
+            t[(b + i) * DENSE_N + b + j] = (double)(tr ? m[sj][si] : m[si][sj]);
+          }
+          t[DENSE_N * DENSE_N + b + i] = (double)(tr ? v[si] : u[si]);
+          t[DENSE_N * DENSE_N + DENSE_N + b + i] = (double)(tr ? u[si] : v[si]);
         }
+      }
       q[id][chi] = (double)qq;
     };
-    std::vector<ld> u(N), v(N);
     // A^{-1}, A^{-T}, A^{-1} omega^{-1}
-    Mat m = mul(P0, Bi);
+    for (int i = 0; i < N; i++)
+      for (int j = 0; j <= i; j++) m[i][j] = (i > 0 ? Bi[i - 1][j] : 0.0L) + Bi[i][j];
     for (int s = 0; s < N; s++) {
       u[s] = (s == 0 ? 1.0L : 0.0L) - c[0] * m[s][0];
       v[s] = Bi[l][s];
@@ -173,7 +168,8 @@ void dense_tables(int Ns, double m0, const double* omega, double* tab, double q[
     put(DN_AINV, m, u, v, c[0] * Bi[l][0], false);
     put(DN_AINV_T, m, u, v, c[0] * Bi[l][0], true);
     // A, A^T
-    m = mul(B0, Pi);
+    for (int i = 0; i < N; i++)
+      for (int j = 0; j <= i; j++) m[i][j] = (i > 0 ? c[i] * Pi[i - 1][j] : 0.0L) + a[i] * Pi[i][j];
     for (int s = 0; s < N; s++) {
       u[s] = ((s == 0 ? c[0] : 0.0L) - m[s][0]) / w[s];
       v[s] = Pi[l][s];

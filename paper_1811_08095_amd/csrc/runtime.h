@@ -65,7 +65,7 @@ struct odwf_solver_s {
   int Ns;
   double m0;
   std::vector<double> omega;
-  void* coef64 = nullptr;  // [2][NCOEF][Ns] double
+  void* coef64 = nullptr;  // [2][NCOEF][Ns] double; the block that holds the next two as well
   void* coef32 = nullptr;  // [2][NCOEF][Ns] float
   double* dense = nullptr; // [NDENSE][DENSE_LEN] dense programs (Ns <= 16)
   double dense_q[odwf::NDENSE][2] = {};  // their q per chirality
