@@ -61,27 +61,6 @@ struct ForceArgs {
   int Ns, bc_t, accumulate;
 };
 
-// m[b][a] += sum_sigma hp[sigma][b] conj(hc[sigma][a]), or its adjoint
-template <bool ADJ>
-__device__ __forceinline__ void outer_acc(const cpx<double> (&hp)[6], const cpx<double> (&hc)[6],
-                                          cpx<double> (&m)[9]) {
-#pragma unroll
-  for (int b = 0; b < 3; b++)
-#pragma unroll
-    for (int a = 0; a < 3; a++) {
-      cpx<double> v = m[ADJ ? a * 3 + b : b * 3 + a];
-#pragma unroll
-      for (int sg = 0; sg < 2; sg++) {
-        const cpx<double> p = hp[sg * 3 + b], c = hc[sg * 3 + a];
-        v.re = fma(p.re, c.re, v.re);
-        v.re = fma(p.im, c.im, v.re);
-        v.im = fma(ADJ ? -p.im : p.im, c.re, v.im);
-        v.im = fma(ADJ ? p.re : -p.re, c.im, v.im);
-      }
-      m[ADJ ? a * 3 + b : b * 3 + a] = v;
-    }
-}
-
 // The lane's direction as data: gamma_mu = [[0, B], [B^dag, 0]], row r of B has
 // one entry f_r at column p_r.  f z for f in {+-1, +-i} is z or (im, re) with a
 // sign for each part, so the lanes of all four directions run the same code:
@@ -118,18 +97,37 @@ __device__ __forceinline__ void slot_half(const double* slot, const Dir& d, cpx<
     }
 }
 
-// M += A + B^dag of one slice for the lane's link (site at q, neighbour at n)
+// M += A + B^dag of one slice for the lane's link (site at q, neighbour at n).  A
+// slice's eight products an entry come first, so that the sum over slices rounds
+// once a slice.
 __device__ __forceinline__ void link_slice(const double* chi, const double* psi, int q, int n, const Dir& d,
                                            cpx<double> (&m)[9]) {
-  cpx<double> hp[6], hc[6];
-  slot_half<+1>(psi + n, d, hp);  // (1 - gamma_mu) psi(x + mu)
-  slot_half<+1>(chi + q, d, hc);  // with chi(x)
-  outer_acc<false>(hp, hc, m);
-  slot_half<-1>(psi + q, d, hp);  // (1 + gamma_mu) psi(x)
-  slot_half<-1>(chi + n, d, hc);  // with chi(x + mu)
-  outer_acc<true>(hp, hc, m);
+  cpx<double> pn[6], cq[6], pq[6], cn[6];
+  slot_half<+1>(psi + n, d, pn);  // (1 - gamma_mu) psi(x + mu)
+  slot_half<+1>(chi + q, d, cq);  // with chi(x)
+  slot_half<-1>(psi + q, d, pq);  // (1 + gamma_mu) psi(x)
+  slot_half<-1>(chi + n, d, cn);  // with chi(x + mu)
+#pragma unroll
+  for (int b = 0; b < 3; b++)
+#pragma unroll
+    for (int a = 0; a < 3; a++) {
+      // sum_sigma pn[b] conj(cq[a]) + conj(pq[a]) cn[b]
+      cpx<double> v = {0.0, 0.0};
+#pragma unroll
+      for (int sg = 0; sg < 2; sg++) {
+        const cpx<double> p = pn[sg * 3 + b], c = cq[sg * 3 + a], r = pq[sg * 3 + a], t = cn[sg * 3 + b];
+        v.re = sg ? fma(p.re, c.re, v.re) : p.re * c.re;
+        v.re = fma(p.im, c.im, v.re);
+        v.im = sg ? fma(p.im, c.re, v.im) : p.im * c.re;
+        v.im = fma(-p.re, c.im, v.im);
+        v.re = fma(r.re, t.re, v.re);
+        v.re = fma(r.im, t.im, v.re);
+        v.im = fma(-r.im, t.re, v.im);
+        v.im = fma(r.re, t.im, v.im);
+      }
+      m[b * 3 + a] = cadd(m[b * 3 + a], v);
+    }
 }
-
 
 // first site of this block: XCD b % 8 takes a contiguous range of the walk, and
 // the walk takes the smallest runs of rows that are whole blocks (units) in
