@@ -585,7 +585,12 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
 // the operand, and keeps those results.  (The test is of the inputs and of rho * t,
 // not of the results: it runs beside the LDS round trip.)  Within its own column, of
 // 16 slices too, such a value may reach every slice.
-template <int NS, class R>
+// FP64 with 16 slices takes two sums of eight terms (and the rank-1 term): the error
+// against extended precision is below that of the recurrences (D 1.40 -> 1.37,
+// normal operator 3.96 -> 3.32 units of 2^-53; one sum of sixteen 1.60 and 4.18), and
+// the shorter chains take 1 % off an iteration.  TIGHT: one after the other, for a
+// caller short of registers (hop_small_kernel, which spills 28 otherwise).
+template <int NS, bool TIGHT = false, class R>
 __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m, int tid) {
   using M = Mfma<R>;
   using V = typename M::V;
@@ -631,15 +636,25 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
         R x[4];
 #pragma unroll
         for (int e = 0; e < 4; e++) x[e] = in ? get[4 * g * M::ROW + e] : R(0);
-        V d = {R(0), R(0), R(0), R(0)};
-#pragma unroll
-        for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
         R t = w[0] * x[0];
 #pragma unroll
         for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
         t *= rho[chi];
         if (NS < DENSE_N) z = fma(t, R(0), z);
-        d = M::mul(t, u, d);
+        V d = {R(0), R(0), R(0), R(0)};
+        if constexpr (sizeof(R) == 8 && NS == DENSE_N) {
+          V d2 = M::mul(t, u, d);
+#pragma unroll
+          for (int e = 0; e < 2; e++) d = M::mul(x[e], b[e], d);
+          if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int e = 2; e < 4; e++) d2 = M::mul(x[e], b[e], d2);
+          d = d + d2;
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
+          d = M::mul(t, u, d);
+        }
         result(g, d);
       }
     };
