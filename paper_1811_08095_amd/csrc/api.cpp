@@ -186,7 +186,15 @@ extern "C" odwf_status odwf_solver_create(odwf_lattice L, int Ns, double m0, con
   std::vector<double> host((n64 + n32) / sizeof(double) + ndense);
   std::memcpy(host.data(), c64.data(), n64);
   std::memcpy(reinterpret_cast<char*>(host.data()) + n64, c32.data(), n32);
-  if (ndense) dense_tables(Ns, m0, omega, host.data() + (n64 + n32) / sizeof(double), S->dense_q);
+  if (ndense) {
+    const double* tab = host.data() + (n64 + n32) / sizeof(double);
+    dense_tables(Ns, m0, omega, host.data() + (n64 + n32) / sizeof(double), S->dense_q);
+    for (int k = 0; k < 2 * NDENSE; k++) {
+      double sum = 0.0;
+      for (int s = 0; s < Ns; s++) sum += std::fabs(tab[k * DENSE_CHI + DENSE_N * DENSE_N + DENSE_N + s]);
+      S->dense_w[k / 2] = std::max(S->dense_w[k / 2], sum);
+    }
+  }
   if (hipMalloc(&S->coef64, host.size() * sizeof(double)) != hipSuccess) {
     (void)hipGetLastError();
     delete S;

@@ -570,9 +570,54 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
   }
 }
 
+template <class R>
+__device__ __forceinline__ R dense_lim(const DenseArg& a) { return sizeof(R) == 8 ? (R)a.lim64 : (R)a.lim32; }
+
+// Inputs that must not meet other columns in a row of the matrix instructions, by
+// real part and imaginary part of a component (each a row of its own).  One that is
+// not finite in any slice of the lane's column becomes zero, and its flag makes the
+// column's results NaN; so does a rho that is not finite (a singular mass; lim is NaN
+// then), for its chirality.  A column that holds a finite value near lim or above is scaled by a power of
+// two, taken back from its results (flag 31).
+template <class R>
+constexpr R QUARANTINE_SCALE = sizeof(R) == 8 ? R(0x1p-512) : R(0x1p-64);
+template <class R>
+__device__ __forceinline__ bool finite(R v) { return fabs(v) <= (sizeof(R) == 8 ? (R)__DBL_MAX__ : (R)__FLT_MAX__); }
+template <int NS, class R>
+__device__ __forceinline__ uint32_t quarantine(cpx<R> (&y)[12], R lim, int lane) {
+  const uint64_t column = ((uint64_t(1) << NS) - 1) << (lane / NS * NS);
+  uint32_t aside = 0;
+  bool big = false;
+#pragma unroll
+  for (int c = 0; c < 24; c++) {
+    R& v = c & 1 ? y[c >> 1].im : y[c >> 1].re;
+    if (__ballot(!finite(v)) & column) aside |= 1u << c;
+    v = finite(v) ? v : R(0);
+    big = big || fabs(v) >= lim / 32;
+  }
+  if (__ballot(big) & column) {
+    aside |= 1u << 31;
+#pragma unroll
+    for (int c = 0; c < 12; c++) y[c] = cscale(QUARANTINE_SCALE<R>, y[c]);
+  }
+  return aside;
+}
+template <class R>
+__device__ __forceinline__ void release(cpx<R> (&y)[12], uint32_t aside, R rho_p, R rho_m) {
+  if (!finite(rho_p)) aside |= 0xfffu;
+  if (!finite(rho_m)) aside |= 0xfff000u;
+  const R f = aside >> 31 ? R(1) / QUARANTINE_SCALE<R> : R(1);
+#pragma unroll
+  for (int c = 0; c < 24; c++) {
+    R& v = c & 1 ? y[c >> 1].im : y[c >> 1].re;
+    v = (aside >> c) & 1 ? (R)__builtin_nan("") : f * v;
+  }
+}
+
 // y <- M y for the 12 components of every lane's 5D site; m: LDS image; scr:
 // DENSE_SCRATCH reals of this wave (16-byte aligned); rho_p / rho_m: rho of the
-// lane's right-hand side per chirality; tid: the thread's index in its block.  The rank-1 term rho u w^T rides on a
+// lane's right-hand side per chirality; lim: that of the program
+// (DenseArg); tid: the thread's index in its block.  The rank-1 term rho u w^T rides on a
 // fifth matrix instruction: lane group k contributes rho times its part of
 // w . x (slots 4 k .. 4 k + 3) as element k of the operand row, and u in every
 // row of the second operand sums the parts.  Right-hand sides of any masses
@@ -580,18 +625,17 @@ __device__ __forceinline__ void dense_stage(R* m, const double* __restrict__ tab
 // others are.  Called by whole waves: the matrix instructions ignore the lane
 // mask.
 // Below 16 slices the zeros between the columns of a row do not stop a value that
-// is not finite (0 * Inf is NaN), nor a product rho * t that is not.  A wave that
-// holds either takes its columns one at a time as well, the others' slots zero in
-// the operand, and keeps those results.  (The test is of the inputs and of rho * t,
-// not of the results: it runs beside the LDS round trip.)  Within its own column, of
-// 16 slices too, such a value may reach every slice.
+// is not finite (0 * Inf is NaN), nor a product rho * t that is not: such inputs are
+// set aside (quarantine).  (One test ahead of it all: tests on the way keep the two
+// chiralities from overlapping.)  With 16 slices such a value may reach every slice
+// of its own column, which is all that its row holds.
 // FP64 with 16 slices takes two sums of eight terms (and the rank-1 term): the error
 // against extended precision is below that of the recurrences (D 1.40 -> 1.37,
 // normal operator 3.96 -> 3.32 units of 2^-53; one sum of sixteen 1.60 and 4.18), and
 // the shorter chains take 1 % off an iteration.  TIGHT: one after the other, for a
 // caller short of registers (hop_small_kernel, which spills 28 otherwise).
 template <int NS, bool TIGHT = false, class R>
-__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m, int tid) {
+__device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr, R rho_p, R rho_m, R lim, int tid) {
   using M = Mfma<R>;
   using V = typename M::V;
   constexpr int NN = DENSE_N * M::ROW;
@@ -600,18 +644,19 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
   const int set_i = M::set_of(slot);
   const R* get = scr + set_i * M::SET + M::real_of(slot) * M::ROW + ((4 * k) ^ M::swap(set_i));
   const int src = 16 * set_i + 4 * k;  // a lane of the operand element's column
-  const R rho[2] = {__shfl(rho_p, src, 64), __shfl(rho_m, src, 64)};
   const bool same = slot / NS == 4 * k / NS;  // result slot and operand slots belong to one column
-  bool nonfinite = false;
+  uint32_t aside = 0;
   if constexpr (NS < DENSE_N) {
-    R z[2] = {R(0), R(0)};
+    R sum[2] = {R(0), R(0)};
 #pragma unroll
     for (int c = 0; c < 12; c++) {
-      z[0] = fma(y[c].re, R(0), z[0]);
-      z[1] = fma(y[c].im, R(0), z[1]);
+      sum[0] += fabs(y[c].re);
+      sum[1] += fabs(y[c].im);
     }
-    nonfinite = !(z[0] + z[1] == R(0));
+    if (__any(!(sum[0] + sum[1] < lim))) aside = quarantine<NS>(y, lim, lane);
   }
+  R rho[2] = {__shfl(rho_p, src, 64), __shfl(rho_m, src, 64)};
+  if (NS < DENSE_N) rho[0] = finite(rho[0]) ? rho[0] : R(0), rho[1] = finite(rho[1]) ? rho[1] : R(0);
 #pragma unroll
   for (int chi = 0; chi < 2; chi++) {
     const R* mc = m + chi * DENSE_IMAGE_CHI<R>;
@@ -628,55 +673,34 @@ __device__ __forceinline__ void dense_apply(cpx<R> (&y)[12], const R* m, R* scr,
 #pragma unroll
     for (int e = 0; e < 4; e++) w[e] = mc[NN + DENSE_N + 4 * k + e];
     const R u = same ? mc[NN + slot] : R(0);
-    R z = R(0);
-    // three groups of four reals; `in`: the lane's operand slots take part, else zeros
-    auto product = [&](bool in, auto&& result) {
 #pragma unroll
-      for (int g = 0; g < 3; g++) {
-        R x[4];
+    for (int g = 0; g < 3; g++) {
+      R x[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) x[e] = in ? get[4 * g * M::ROW + e] : R(0);
-        R t = w[0] * x[0];
+      for (int e = 0; e < 4; e++) x[e] = get[4 * g * M::ROW + e];
+      R t = w[0] * x[0];
 #pragma unroll
-        for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
-        t *= rho[chi];
-        if (NS < DENSE_N) z = fma(t, R(0), z);
-        V d = {R(0), R(0), R(0), R(0)};
-        if constexpr (sizeof(R) == 8 && NS == DENSE_N) {
-          V d2 = M::mul(t, u, d);
+      for (int e = 1; e < 4; e++) t = fma(w[e], x[e], t);
+      V d = {R(0), R(0), R(0), R(0)};
+      if constexpr (sizeof(R) == 8 && NS == DENSE_N) {
+        V d2 = M::mul(rho[chi] * t, u, d);
 #pragma unroll
-          for (int e = 0; e < 2; e++) d = M::mul(x[e], b[e], d);
-          if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
+        for (int e = 0; e < 2; e++) d = M::mul(x[e], b[e], d);
+        if constexpr (TIGHT) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int e = 2; e < 4; e++) d2 = M::mul(x[e], b[e], d2);
-          d = d + d2;
-        } else {
+        for (int e = 2; e < 4; e++) d2 = M::mul(x[e], b[e], d2);
+        d = d + d2;
+      } else {
 #pragma unroll
-          for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
-          d = M::mul(t, u, d);
-        }
-        result(g, d);
+        for (int e = 0; e < 4; e++) d = M::mul(x[e], b[e], d);
+        d = M::mul(rho[chi] * t, u, d);
       }
-    };
-    product(true, [&](int g, const V& d) {
       y[6 * chi + 2 * g] = {d[0], d[1]};
       y[6 * chi + 2 * g + 1] = {d[2], d[3]};
-    });
-    if constexpr (NS < DENSE_N) {
-      if (__any(nonfinite || !(z == R(0)))) {
-#pragma unroll 1
-        for (int q = 0; q < DENSE_N / NS; q++) {
-          const bool own = slot / NS == q;
-          product(4 * k / NS == q, [&](int g, const V& d) {
-            if (own) {
-              y[6 * chi + 2 * g] = {d[0], d[1]};
-              y[6 * chi + 2 * g + 1] = {d[2], d[3]};
-            }
-          });
-        }
-      }
     }
   }
+  if constexpr (NS < DENSE_N)
+    if (__any(aside != 0) || !(lim > R(0))) release(y, aside, rho_p, rho_m);
 }
 
 // ---------------------------------------------------------------------------

@@ -337,8 +337,8 @@ __device__ __forceinline__ double fused_tail(const HopArgs& a, const HopIo& io, 
   auto program = [&](int p, const DenseArg& dn, const M5Prog& prog, R* lds, cpx<R>(&v)[12]) {
     if constexpr (NS <= DENSE_N) {
       if (!dn.tab) return;
-      if constexpr (PRE) dense_apply<NS, true>(v, lds, pl.scr, rho[2 * p], rho[2 * p + 1], tid);
-      else dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], tid);
+      if constexpr (PRE) dense_apply<NS, true>(v, lds, pl.scr, rho[2 * p], rho[2 * p + 1], dense_lim<R>(dn), tid);
+      else dense_apply<NS>(v, lds, pl.scr, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], dense_lim<R>(dn), tid);
     } else {
       if (prog.n == 0) return;
       cpx<R>* buf = reinterpret_cast<cpx<R>*>(lds);

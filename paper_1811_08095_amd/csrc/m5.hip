@@ -74,7 +74,7 @@ __global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const 
     const int r = nrhs > 1 ? (int)(j % nrhs) : 0;
     dense_stage<R>(mat, dn.tab, threadIdx.x);
     __syncthreads();
-    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], threadIdx.x);
+    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], dense_lim<R>(dn), threadIdx.x);
   }
   if (!valid) return;
   if (diag) {

@@ -116,6 +116,10 @@ struct KappaArr {
 struct DenseArg {
   const double* tab;
   double rho[2 * MAXRHS];
+  // inputs whose reals stay below this (FP64, FP32 arithmetic) keep rho w^T x finite;
+  // NaN where a rho is not finite itself (a singular mass)
+  double lim64;
+  float lim32;
 };
 
 // division of 0 <= n < 2^31 by a fixed 1 <= d < 2^31 as a multiplication:

@@ -81,7 +81,7 @@ __device__ __forceinline__ void tile_program(cpx<R> (&v)[12], const TileArgs& a,
       cpx<R> w[12];
 #pragma unroll
       for (int c = 0; c < 12; c++) w[c] = v[c];
-      dense_apply<NS>(w, mat, scr, (R)a.dn.rho[r], (R)a.dn.rho[MAXRHS + r], threadIdx.x);
+      dense_apply<NS>(w, mat, scr, (R)a.dn.rho[r], (R)a.dn.rho[MAXRHS + r], dense_lim<R>(a.dn), threadIdx.x);
       const bool on = (a.dn_on >> par) & 1;
 #pragma unroll
       for (int c = 0; c < 12; c++) {

@@ -2,9 +2,12 @@
 // hopping-kernel profiler.
 #include "runtime.h"
 
+#include <algorithm>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 
 namespace odwf {
 
@@ -192,9 +195,17 @@ DenseArg dense_arg(const OpCtx& c, const M5Prog& p) {
   std::memset(&d, 0, sizeof(d));
   if (!dense_ns(c.Ns()) || p.n == 0 || p.dense < 0) return d;
   d.tab = c.S->dense + (size_t)p.dense * DENSE_LEN;
+  double most = 1.0;  // of |rho| and 1, or NaN
   for (int chi = 0; chi < 2; chi++)
-    for (int r = 0; r < c.nrhs; r++)
-      d.rho[chi * MAXRHS + r] = c.kappa[r] / (1.0 + c.kappa[r] * c.S->dense_q[p.dense][chi]);
+    for (int r = 0; r < c.nrhs; r++) {
+      const double rho = c.kappa[r] / (1.0 + c.kappa[r] * c.S->dense_q[p.dense][chi]);
+      d.rho[chi * MAXRHS + r] = rho;
+      if (!std::isfinite(rho)) most = std::numeric_limits<double>::quiet_NaN();
+      else if (std::fabs(rho) > most) most = std::fabs(rho);
+    }
+  const double reach = 4 * most * std::max(1.0, c.S->dense_w[p.dense]);  // (4: for the roundings)
+  d.lim64 = std::numeric_limits<double>::max() / reach;
+  d.lim32 = (float)(std::numeric_limits<float>::max() / reach);
   return d;
 }
 

@@ -69,6 +69,7 @@ struct odwf_solver_s {
   void* coef32 = nullptr;  // [2][NCOEF][Ns] float
   double* dense = nullptr; // [NDENSE][DENSE_LEN] dense programs (Ns <= 16)
   double dense_q[odwf::NDENSE][2] = {};  // their q per chirality
+  double dense_w[odwf::NDENSE] = {};     // their sum of |w|, the larger of the chiralities
   std::mutex mtx;
   std::map<hipStream_t, odwf::Workspace*> ws;
   odwf::Workspace& workspace(hipStream_t st);

@@ -58,6 +58,39 @@ def test_applications_keep_right_hand_sides_apart(Ns, prec, kind):
     lat.close()
 
 
+@pytest.mark.parametrize("prec", PRECS, ids=lambda p: odwf.PREC_NAMES[p])
+@pytest.mark.parametrize("Ns", [4, 8, 16])
+def test_singular_mass_stays_alone(Ns, prec):
+    """mu = -1 makes 1 + L singular: that right-hand side alone is not finite."""
+    import torch
+    lat, sol = _mk(Ns)
+    psi = torch.from_numpy(synth.make_source(DIMS, Ns, 3, 5150)).cuda()
+    for op in (odwf.OP_D, odwf.OP_DDAG, odwf.OP_SCHUR_NORMAL):
+        ref = sol.apply(op, psi, [0.3, 0.5, 0.02], prec=prec).cpu().numpy()
+        out = sol.apply(op, psi, [0.3, -2 * M0, 0.02], prec=prec).cpu().numpy()
+        assert np.isfinite(ref).all() and not np.isfinite(out[1]).all()
+        assert np.array_equal(out[[0, 2]], ref[[0, 2]]), op
+    sol.close()
+    lat.close()
+
+
+@pytest.mark.parametrize("prec", [odwf.FP64, odwf.FP32], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("Ns", [4, 8])
+def test_large_values_are_applied(Ns, prec):
+    """Finite values near the end of the range: A^{-1} is linear, and scales exactly."""
+    import torch
+    lat, sol = _mk(Ns)
+    psi = synth.make_source(DIMS, Ns, 2, 5160)
+    f = 2.0 ** (1015 if prec == odwf.FP64 else 119)
+    big = psi.copy()
+    big[0] *= f
+    ref = sol.apply(odwf.OP_M5INV, torch.from_numpy(psi).cuda(), [0.3, 0.1], prec=prec).cpu().numpy()
+    out = sol.apply(odwf.OP_M5INV, torch.from_numpy(big).cuda(), [0.3, 0.1], prec=prec).cpu().numpy()
+    assert np.array_equal(out[0], ref[0] * f) and np.array_equal(out[1], ref[1])
+    sol.close()
+    lat.close()
+
+
 @pytest.mark.parametrize("kind", ["nan", "inf", "huge"])
 @pytest.mark.parametrize("prec", PRECS, ids=lambda p: odwf.PREC_NAMES[p])
 @pytest.mark.parametrize("Ns", [4, 8, 16, 32])
