@@ -333,7 +333,8 @@ void odwf_batch_destroy(odwf_batch bt);
  * launches restricted to the active slots count with the bytes of every slot
  * (exact while all slots are active); the batch's FP64 reliable-update
  * launches, which run only for slots that requested an update, are not
- * counted. */
+ * counted.  While profiling is on, D and D^dag launch the hop parity by parity,
+ * where small lattices take both parities in one launch otherwise (same results). */
 odwf_status odwf_profile_enable(int enable);
 odwf_status odwf_profile_read(long long* launches, double* ms, double* bytes);
 

@@ -53,26 +53,22 @@ static ChunkGeom chunk_geom(int cpb, long h, int nrhs, int Ns) {
 static dim3 chunk_grid(const ChunkGeom& g) { return dim3((unsigned)((g.n + 256 * UNROLL - 1) / (256 * UNROLL)), g.nrhs); }
 __device__ __forceinline__ long chunk_first() { return (long)blockIdx.x * 256 * UNROLL + threadIdx.x; }
 
-__global__ void __launch_bounds__(256) chunk_zero_kernel(uint4* v, const CGScal* gate, int gate_mode, ChunkGeom g) {
+__global__ void __launch_bounds__(256) chunk_zero_kernel(uint4* v, ChunkGeom g) {
   const int r = blockIdx.y;
-  if (!gate_on(gate, gate_mode, r)) return;
 #pragma unroll
   for (int u = 0; u < UNROLL; u++) {
     const long k = chunk_first() + u * 256;
     if (k < g.n) v[g.at(k, r)] = make_uint4(0, 0, 0, 0);
   }
 }
-__global__ void __launch_bounds__(256) scale_zero_kernel(float* sc, const CGScal* gate, int gate_mode, long h, int nrhs,
-                                                         int Ns) {
+__global__ void __launch_bounds__(256) scale_zero_kernel(float* sc, long n) {
   const long k = (long)blockIdx.x * 256 + threadIdx.x;
-  if (k < h * nrhs * Ns && gate_on(gate, gate_mode, (int)(k / Ns % nrhs))) sc[k] = 0.f;
+  if (k < n) sc[k] = 0.f;
 }
 
-// FP64 <- FP32: dst = src or dst += src, and src = 0 behind it when clear
-__global__ void __launch_bounds__(256) chunk_32_to_64_kernel(uint4* src, uint4* dst, int accumulate, int clear,
-                                                             const CGScal* gate, int gate_mode, ChunkGeom g, int lg) {
+// FP64 += FP32, and the FP32 field = 0 behind it
+__global__ void __launch_bounds__(256) chunk_32_to_64_kernel(uint4* src, uint4* dst, ChunkGeom g, int lg) {
   const int r = blockIdx.y;
-  if (!gate_on(gate, gate_mode, r)) return;
 #pragma unroll 2
   for (int u = 0; u < UNROLL; u++) {
     const long k = chunk_first() + u * 256;
@@ -85,15 +81,12 @@ __global__ void __launch_bounds__(256) chunk_32_to_64_kernel(uint4* src, uint4* 
     unpack_chunk<SP32>(src[at], a);
 #pragma unroll
     for (int c = 0; c < 2; c++) {
-      cpx<double> b = {(double)a[c].re, (double)a[c].im};
-      if (accumulate) {
-        cpx<double> o;
-        unpack_chunk<SP64>(dst[d0 + (c << lg)], &o);
-        b = cadd(o, b);
-      }
-      dst[d0 + (c << lg)] = pack_chunk<SP64>(&b, 1.0);
+      cpx<double> o;
+      unpack_chunk<SP64>(dst[d0 + (c << lg)], &o);
+      o = cadd(o, cpx<double>{(double)a[c].re, (double)a[c].im});
+      dst[d0 + (c << lg)] = pack_chunk<SP64>(&o, 1.0);
     }
-    if (clear) src[at] = make_uint4(0, 0, 0, 0);
+    src[at] = make_uint4(0, 0, 0, 0);
   }
 }
 __global__ void __launch_bounds__(256) chunk_64_to_32_kernel(const uint4* src, uint4* dst, const CGScal* gate,
@@ -227,14 +220,12 @@ __global__ void __launch_bounds__(256) chunk_cg_step_kernel(const uint4* r_, uin
 
 template <class PS, class PD>
 __global__ void __launch_bounds__(256) vec_convert_kernel(const void* src, const float* src_sc, void* dst, float* dst_sc,
-                                   int accumulate, const CGScal* gate, int gate_mode, long h, int nrhs,
-                                   int Ns) {
+                                   int accumulate, long h, int nrhs, int Ns) {
   using RS = typename PS::real;
   using RD = typename PD::real;
   const int inner = nrhs * Ns;
   const int spb = blockDim.x / inner;
   const int sl = threadIdx.x / inner, lr = threadIdx.x % inner, r = lr / Ns, s = lr % Ns;
-  if (!gate_on(gate, gate_mode, r)) return;
   for (long j = (long)blockIdx.x * spb + sl; j < h; j += (long)gridDim.x * spb) {
     cpx<RS> a[12];
     load_site<PS>(src, src_sc, j, r, s, nrhs, Ns, a);
@@ -315,28 +306,21 @@ __global__ void __launch_bounds__(256) vec_norm2_kernel(const void* v, const flo
     default: return hipErrorInvalidValue;                                               \
   }
 
-hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st,
-                           const CGScal* gate, int gate_mode) {
+hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st) {
   const ChunkGeom g = chunk_geom(prec == PREC64 ? 1 : prec == PREC32 ? 2 : 4, h, nrhs, Ns);
-  hipLaunchKernelGGL(chunk_zero_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(v), gate, gate_mode, g);
+  hipLaunchKernelGGL(chunk_zero_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(v), g);
   if (sc)
-    hipLaunchKernelGGL(scale_zero_kernel, dim3((unsigned)((h * nrhs * Ns + 255) / 256)), dim3(256), 0, st, sc, gate,
-                       gate_mode, h, nrhs, Ns);
+    hipLaunchKernelGGL(scale_zero_kernel, dim3((unsigned)((h * nrhs * Ns + 255) / 256)), dim3(256), 0, st, sc,
+                       h * nrhs * Ns);
   return hipGetLastError();
 }
 
-template <class PS>
-static hipError_t convert_to(int prec_dst, const void* src, const float* src_sc, void* dst,
-                             float* dst_sc, int acc, const CGScal* gate, int gm, long h, int nrhs,
-                             int Ns, hipStream_t st) {
+template <class PS, class PD>
+static hipError_t convert(const void* src, const float* src_sc, void* dst, float* dst_sc, int acc, long h, int nrhs,
+                          int Ns, hipStream_t st) {
   const int block = vec_spb(nrhs, Ns) * nrhs * Ns;
-  const dim3 gr(vec_nblocks(h, nrhs, Ns));
-  switch (prec_dst) {
-    case PREC64: hipLaunchKernelGGL((vec_convert_kernel<PS, SP64>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
-    case PREC16: hipLaunchKernelGGL((vec_convert_kernel<PS, SP16>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
-    case PRECB16: hipLaunchKernelGGL((vec_convert_kernel<PS, SPB16>), gr, dim3(block), 0, st, src, src_sc, dst, dst_sc, acc, gate, gm, h, nrhs, Ns); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipLaunchKernelGGL((vec_convert_kernel<PS, PD>), dim3(vec_nblocks(h, nrhs, Ns)), dim3(block), 0, st, src, src_sc, dst,
+                     dst_sc, acc, h, nrhs, Ns);
   return hipGetLastError();
 }
 
@@ -355,26 +339,24 @@ hipError_t launch_vec_convert(int prec_src, const void* src, const float* src_sc
     hipLaunchKernelGGL(chunk_copy_kernel, chunk_grid(g), dim3(256), 0, st, s4, d4, gate, gate_mode, g);
     return hipGetLastError();
   }
-  switch (prec_src) {
-    case PREC64: return convert_to<SP64>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
-    case PREC16: return convert_to<SP16>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
-    case PRECB16: return convert_to<SPB16>(prec_dst, src, src_sc, dst, dst_sc, accumulate, gate, gate_mode, h, nrhs, Ns, st);
+  if (gate) return hipErrorInvalidValue;  // (the scaled formats have no gated conversion)
+  const int pair = prec_src * 4 + prec_dst;
+  switch (pair) {
+    case PREC64 * 4 + PREC16: return convert<SP64, SP16>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
+    case PREC64 * 4 + PRECB16: return convert<SP64, SPB16>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
+    case PREC16 * 4 + PREC64: return convert<SP16, SP64>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
+    case PRECB16 * 4 + PREC64: return convert<SPB16, SP64>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
+    case PREC16 * 4 + PREC16: return convert<SP16, SP16>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
+    case PRECB16 * 4 + PRECB16: return convert<SPB16, SPB16>(src, src_sc, dst, dst_sc, accumulate, h, nrhs, Ns, st);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, long h, int nrhs, int Ns,
-                            hipStream_t st, const CGScal* gate, int gate_mode) {
-  if (prec == PREC32) {
-    const ChunkGeom g = chunk_geom(2, h, nrhs, Ns);
-    hipLaunchKernelGGL(chunk_32_to_64_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(x),
-                       reinterpret_cast<uint4*>(y), 1, clear, gate, gate_mode, g, __builtin_ctz(Ns));
-    return hipGetLastError();
-  }
-  const hipError_t e =
-      launch_vec_convert(prec, x, x_sc, PREC64, y, nullptr, 1, h, nrhs, Ns, st, gate, gate_mode);
-  if (e != hipSuccess || !clear) return e;
-  return launch_vec_zero(prec, x, x_sc, h, nrhs, Ns, st, gate, gate_mode);
+hipError_t launch_vec_flush(void* x, void* y, long h, int nrhs, int Ns, hipStream_t st) {
+  const ChunkGeom g = chunk_geom(2, h, nrhs, Ns);
+  hipLaunchKernelGGL(chunk_32_to_64_kernel, chunk_grid(g), dim3(256), 0, st, reinterpret_cast<uint4*>(x),
+                     reinterpret_cast<uint4*>(y), g, __builtin_ctz(Ns));
+  return hipGetLastError();
 }
 
 // beta is formed inside the vector step while a block of it reads at most this

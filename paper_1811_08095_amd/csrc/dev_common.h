@@ -96,7 +96,6 @@ __device__ __forceinline__ uint16_t f_to_bf16(float f) {
   return (uint16_t)(u >> 16);
 }
 
-// unpack one 16-byte chunk into CPB complex values
 // A 16-byte load that stays one: where only the two doubles of a chunk are used,
 // the compiler takes two loads of 8 bytes, each of which passes the same cache
 // lines through L1 again.  The empty asm uses the chunk as a whole, at the point
@@ -109,6 +108,7 @@ __device__ __forceinline__ uint4 whole_chunk(u32x4 w) {
   return make_uint4(w.x, w.y, w.z, w.w);
 }
 
+// unpack one 16-byte chunk into CPB complex values
 template <class P>
 __device__ __forceinline__ void unpack_chunk(const uint4 q, cpx<typename P::real>* v);
 

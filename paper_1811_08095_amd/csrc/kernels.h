@@ -56,25 +56,21 @@ hipError_t launch_pack_gauge(const void* canon, void* const out64[2], void* cons
                              hipStream_t st);
 
 // fifth-dimension programs on a half field (m5.hip):
-// out = c0 * prog(in) + c1 * other   (other may be null); dn: the program as a
-// dense matrix where it has one (N_s <= 16), diag: the coefficients of a pure scaling
-hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc,
-                     const void* other, const float* other_sc, double c0, double c1,
-                     const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
-                     int nrhs, int Ns, hipStream_t st);
+// out = prog(in), from its dense form dn for N_s <= 16
+hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc, const M5Prog& prog,
+                     const DenseArg& dn, const void* coef, const KappaArr& kappa, long h, int nrhs, int Ns,
+                     hipStream_t st);
 
 // BLAS-1 on half fields (blas.hip); n5 = h * nrhs * Ns five-dimensional sites
 // gate / gate_mode (GateMode) restrict the work to selected right-hand sides
-hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st,
-                           const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
-// dst = src (accumulate: dst += src), converting storage precision: between FP64 and a
-// scaled format, FP64 to FP32, or a copy
+hipError_t launch_vec_zero(int prec, void* v, float* sc, long h, int nrhs, int Ns, hipStream_t st);
+// dst = src, converting storage precision: FP64 to FP32 or a copy, which may be
+// gated, or between FP64 and a scaled format (accumulate: dst += src)
 hipError_t launch_vec_convert(int prec_src, const void* src, const float* src_sc, int prec_dst,
                               void* dst, float* dst_sc, int accumulate, long h, int nrhs, int Ns,
                               hipStream_t st, const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
-// y (FP64) += x, and x = 0 behind it when clear
-hipError_t launch_vec_flush(int prec, void* x, float* x_sc, void* y, int clear, long h, int nrhs, int Ns,
-                            hipStream_t st, const CGScal* gate = nullptr, int gate_mode = GATE_NONE);
+// y (FP64) += x (FP32), and x = 0 behind it
+hipError_t launch_vec_flush(void* x, void* y, long h, int nrhs, int Ns, hipStream_t st);
 // one right-hand side of a field into one right-hand side of another (zeros if src null)
 hipError_t launch_vec_copy_rhs(int prec_src, const void* src, const float* src_sc, int nrhs_src,
                                int r_src, int prec_dst, void* dst, float* dst_sc, int nrhs_dst,

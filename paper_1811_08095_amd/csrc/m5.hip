@@ -1,20 +1,16 @@
-// Stand-alone fifth-dimension kernel on a half field:
-//     out = c0 * prog(in) + c1 * other
-// used for source preparation and reconstruction of the even-odd solve
-// (omega^{-1}, A^{-1}, (1 + L)^{-1}, ...) and for the M5INV operator.  Sites are
-// loaded in the lane layout (coalesced), transposed through LDS into columns of
-// Ns values, transformed, and written back.
+// Stand-alone fifth-dimension kernel on a half field, out = prog(in): A^{-dag} at the
+// head of S_e^dag, A^{-1} of an admitted source, and for N_s = 32 the programs that the
+// layout kernels apply below.  N_s = 32: sites are loaded in the lane layout
+// (coalesced), transposed through LDS into columns of Ns values, transformed, and
+// written back; N_s <= 16: on the matrix cores.
 #include "dev_common.h"
 #include "kernels.h"
 
 namespace odwf {
 
 template <class P, int NS>
-__global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in_sc, void* out,
-                                                 float* out_sc, const void* other,
-                                                 const float* other_sc, double c0, double c1,
-                                                 M5Prog prog, const void* coefp,
-                                                 const KappaArr kappa, long h, int nrhs, int spb) {
+__global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in_sc, void* out, float* out_sc, M5Prog prog,
+                                                 const void* coefp, const KappaArr kappa, long h, int nrhs, int spb) {
   using R = typename P::real;
   extern __shared__ __align__(16) unsigned char smem[];
   constexpr int NSP = NS + 1;
@@ -42,13 +38,7 @@ __global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in
   if (!valid) return;
   const cpx<R>* b = buf + ((size_t)(sl * nrhs + r) * 12) * NSP + s;
 #pragma unroll
-  for (int c = 0; c < 12; c++) v[c] = cscale((R)c0, b[c * NSP]);
-  if (other) {
-    cpx<R> o[12];
-    load_site<P>(other, other_sc, j, r, s, nrhs, NS, o);
-#pragma unroll
-    for (int c = 0; c < 12; c++) v[c] = cadd(v[c], cscale((R)c1, o[c]));
-  }
+  for (int c = 0; c < 12; c++) v[c] = b[c * NSP];
   store_site<P>(out, out_sc, j, r, s, nrhs, NS, v);
 }
 
@@ -57,9 +47,7 @@ __global__ void __launch_bounds__(256) m5_kernel(const void* in, const float* in
 // of a half field are consecutive, so a wave takes 64 / N_s of them.
 template <class P, int NS>
 __global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const float* in_sc, void* out, float* out_sc,
-                                                       const void* other, const float* other_sc, double c0,
-                                                       double c1, const DenseArg dn, const double* diag, long ncol,
-                                                       int nrhs) {
+                                                          const DenseArg dn, long ncol, int nrhs) {
   using R = typename P::real;
   __shared__ __align__(16) R mat[DENSE_IMAGE<R>];
   __shared__ __align__(16) R scr[4 * DENSE_SCRATCH<R>];
@@ -70,79 +58,63 @@ __global__ void __launch_bounds__(256, 2) m5_dense_kernel(const void* in, const 
 #pragma unroll
   for (int c = 0; c < 12; c++) v[c] = {R(0), R(0)};
   if (valid) load_site<P>(in, in_sc, j, 0, s, 1, NS, v);
-  if (dn.tab) {
-    const int r = nrhs > 1 ? (int)(j % nrhs) : 0;
-    dense_stage<R>(mat, dn.tab, threadIdx.x);
-    __syncthreads();
-    dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], dense_lim<R>(dn), threadIdx.x);
-  }
-  if (!valid) return;
-  if (diag) {
-    const R p = (R)diag[s], m = (R)diag[NCOEF * NS + NS - 1 - s];
-#pragma unroll
-    for (int c = 0; c < 12; c++) v[c] = cscale(c < 6 ? p : m, v[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < 12; c++) v[c] = cscale((R)c0, v[c]);
-  if (other) {
-    cpx<R> o[12];
-    load_site<P>(other, other_sc, j, 0, s, 1, NS, o);
-#pragma unroll
-    for (int c = 0; c < 12; c++) v[c] = cadd(v[c], cscale((R)c1, o[c]));
-  }
-  store_site<P>(out, out_sc, j, 0, s, 1, NS, v);
+  const int r = nrhs > 1 ? (int)(j % nrhs) : 0;
+  dense_stage<R>(mat, dn.tab, threadIdx.x);
+  __syncthreads();
+  dense_apply<NS>(v, mat, scr + (threadIdx.x >> 6) * DENSE_SCRATCH<R>, (R)dn.rho[r], (R)dn.rho[MAXRHS + r], dense_lim<R>(dn),
+                  threadIdx.x);
+  if (valid) store_site<P>(out, out_sc, j, 0, s, 1, NS, v);
 }
 
+struct M5Io {
+  const void* in;
+  const float* in_sc;
+  void* out;
+  float* out_sc;
+};
 template <class P, int NS>
-static hipError_t launch_m5_t(const void* in, const float* in_sc, void* out, float* out_sc,
-                              const void* other, const float* other_sc, double c0, double c1,
-                              const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
-                              int nrhs, hipStream_t st) {
+static hipError_t launch_m5_t(const M5Io& f, const M5Prog& prog, const DenseArg& dn, const void* coef,
+                              const KappaArr& kappa, long h, int nrhs, hipStream_t st) {
   using R = typename P::real;
   const int inner = nrhs * NS;
   if (inner > 256 || nrhs > MAXRHS) return hipErrorInvalidValue;
   if constexpr (NS <= DENSE_N) {
-    // a program is dense, diagonal (one scaling) or absent
-    if (!dn.tab && !diag && prog.n > 0) return hipErrorInvalidValue;
+    if (!dn.tab) return hipErrorInvalidValue;
     const long ncol = h * nrhs;
     const dim3 grid((unsigned)((ncol * NS + 255) / 256));
-    hipLaunchKernelGGL((m5_dense_kernel<P, NS>), grid, dim3(256), 0, st, in, in_sc, out, out_sc, other, other_sc, c0, c1,
-                       dn, diag, ncol, nrhs);
-    return hipGetLastError();
+    hipLaunchKernelGGL((m5_dense_kernel<P, NS>), grid, dim3(256), 0, st, f.in, f.in_sc, f.out, f.out_sc, dn, ncol, nrhs);
   } else {
-  const int spb = 256 / inner;
-  const int block = (spb * inner + 63) & ~63;
-  const long nb = (h + spb - 1) / spb;
-  const size_t sm = (size_t)spb * nrhs * 12 * (NS + 1) * sizeof(cpx<R>) + MAXRHS * sizeof(R);
-  hipLaunchKernelGGL((m5_kernel<P, NS>), dim3((unsigned)nb), dim3(block), sm, st, in, in_sc, out,
-                     out_sc, other, other_sc, c0, c1, prog, coef, kappa, h, nrhs, spb);
-  return hipGetLastError();
+    const int spb = 256 / inner;
+    const int block = (spb * inner + 63) & ~63;
+    const long nb = (h + spb - 1) / spb;
+    const size_t sm = (size_t)spb * nrhs * 12 * (NS + 1) * sizeof(cpx<R>) + MAXRHS * sizeof(R);
+    hipLaunchKernelGGL((m5_kernel<P, NS>), dim3((unsigned)nb), dim3(block), sm, st, f.in, f.in_sc, f.out, f.out_sc, prog,
+                       coef, kappa, h, nrhs, spb);
   }
+  return hipGetLastError();
 }
 
 template <class P>
-static hipError_t launch_m5_p(const void* in, const float* in_sc, void* out, float* out_sc,
-                              const void* other, const float* other_sc, double c0, double c1,
-                              const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h,
-                              int nrhs, int Ns, hipStream_t st) {
+static hipError_t launch_m5_p(const M5Io& f, const M5Prog& prog, const DenseArg& dn, const void* coef,
+                              const KappaArr& kappa, long h, int nrhs, int Ns, hipStream_t st) {
   switch (Ns) {
-    case 4: return launch_m5_t<P, 4>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
-    case 8: return launch_m5_t<P, 8>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
-    case 16: return launch_m5_t<P, 16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
-    case 32: return launch_m5_t<P, 32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, st);
+    case 4: return launch_m5_t<P, 4>(f, prog, dn, coef, kappa, h, nrhs, st);
+    case 8: return launch_m5_t<P, 8>(f, prog, dn, coef, kappa, h, nrhs, st);
+    case 16: return launch_m5_t<P, 16>(f, prog, dn, coef, kappa, h, nrhs, st);
+    case 32: return launch_m5_t<P, 32>(f, prog, dn, coef, kappa, h, nrhs, st);
   }
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc,
-                     const void* other, const float* other_sc, double c0, double c1,
-                     const M5Prog& prog, const DenseArg& dn, const double* diag, const void* coef, const KappaArr& kappa, long h, int nrhs,
-                     int Ns, hipStream_t st) {
+hipError_t launch_m5(int prec, const void* in, const float* in_sc, void* out, float* out_sc, const M5Prog& prog,
+                     const DenseArg& dn, const void* coef, const KappaArr& kappa, long h, int nrhs, int Ns,
+                     hipStream_t st) {
+  const M5Io f = {in, in_sc, out, out_sc};
   switch (prec) {
-    case PREC64: return launch_m5_p<SP64>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
-    case PREC32: return launch_m5_p<SP32>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
-    case PREC16: return launch_m5_p<SP16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
-    case PRECB16: return launch_m5_p<SPB16>(in, in_sc, out, out_sc, other, other_sc, c0, c1, prog, dn, diag, coef, kappa, h, nrhs, Ns, st);
+    case PREC64: return launch_m5_p<SP64>(f, prog, dn, coef, kappa, h, nrhs, Ns, st);
+    case PREC32: return launch_m5_p<SP32>(f, prog, dn, coef, kappa, h, nrhs, Ns, st);
+    case PREC16: return launch_m5_p<SP16>(f, prog, dn, coef, kappa, h, nrhs, Ns, st);
+    case PRECB16: return launch_m5_p<SPB16>(f, prog, dn, coef, kappa, h, nrhs, Ns, st);
   }
   return hipErrorInvalidValue;
 }

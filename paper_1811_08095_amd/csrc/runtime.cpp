@@ -382,13 +382,10 @@ hipError_t hop_pair(const OpCtx& c, int dag, const HV& in_e, const HV& in_o, con
   return launch_hop(a, c.prec, c.S->Ns, c.st);
 }
 
-hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p, double c0,
-              const HV* other, double c1) {
+hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p) {
   KappaArr k;
   for (int r = 0; r < MAXRHS; r++) k.v[r] = r < c.nrhs ? c.kappa[r] : 0.0;
-  return launch_m5(c.prec, in.d, in.sc, out.d, out.sc, other ? other->d : nullptr,
-                   other ? other->sc : nullptr, c0, c1, p, dense_arg(c, p), diag_of(c, p), c.coef(), k, c.h(),
-                   c.nrhs, c.Ns(), c.st);
+  return launch_m5(c.prec, in.d, in.sc, out.d, out.sc, p, dense_arg(c, p), c.coef(), k, c.h(), c.nrhs, c.Ns(), c.st);
 }
 
 // a program that runs inside the layout kernels: none, a scaling, or a dense one

@@ -143,8 +143,7 @@ inline hipError_t pack(const OpCtx& c, const void* canon, int r0, const HV* e, c
   return pack(c, canon, r0, e, o, prog_none(), prog_none());
 }
 
-hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p, double c0 = 1.0,
-              const HV* other = nullptr, double c1 = 0.0);
+hipError_t m5(const OpCtx& c, const HV& in, const HV& out, const M5Prog& p);
 
 // profiler hooks
 void prof_begin(hipStream_t st, int key);

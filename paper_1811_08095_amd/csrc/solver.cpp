@@ -338,7 +338,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
         if (seen && (!any(seen, 0) || any(seen, 1))) break;
       }
       // reliable update: y += x_s, r = f - N y in FP64, restart the FP32 residual
-      CHK(launch_vec_flush(inner, xs.d, xs.sc, e1.d, 1, h, nrhs, Ns, st));
+      CHK(launch_vec_flush(xs.d, e1.d, h, nrhs, Ns, st));
       CHK(true_residual(c64, e0, e1, o0, e2, partial, dscal, dres));
       CHK(launch_vec_convert(PREC64, e2.d, nullptr, inner, rr.d, rr.sc, 0, h, nrhs, Ns, st));
       CHK(read_scal(dscal, cur, nrhs, st));
@@ -388,7 +388,7 @@ odwf_status solve_chunk(odwf_solver S, int mode, const double* mq, const double*
       CGScal fin[MAXRHS];
       CHK(read_scal(dscal, fin, nrhs, st));
       for (int q = 0; q < nrhs; q++) inner_iters[q] += fin[q].iters;
-      CHK(launch_vec_flush(inner, xs.d, xs.sc, e1.d, 0, h, nrhs, Ns, st));
+      CHK(launch_vec_convert(inner, xs.d, xs.sc, PREC64, e1.d, nullptr, 1, h, nrhs, Ns, st));
       outer++;
       // outer residual; carry the iteration count so maxiter bounds the total
       for (int q = 0; q < nrhs; q++) cur[q].iters = inner_iters[q];
