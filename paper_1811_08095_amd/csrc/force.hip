@@ -29,9 +29,9 @@
 // used (25 loads of 16 bytes in flight a lane; three blocks a CU by LDS).  The
 // waves' sums meet at the end and the lane writes (or adds to) its link's nine
 // entries.  FP64 throughout.
-// Bound: L2 fills (1.6 GB for 0.95 GB of fields, links and forces at 16^3 x 32 x
-// 16, 4.7 TB/s) and, one after the other, the LDS passes of six waves a CU.
-// 16^3 x 32 x 16: 353 us, against 2 x 418 us of one launch per parity with the
+// Bound: L2 fills (1.66 GB for 0.95 GB of fields, links and forces at 16^3 x 32 x
+// 16, 4.9 TB/s) and, one after the other, the LDS passes of six waves a CU.
+// 16^3 x 32 x 16: 340 us, against 2 x 418 us of one launch per parity with the
 // sum over s through LDS and 278 us for the packed copies; 445 us with every x
 // neighbour brought as well, two blocks a CU and rotated slots (twice the bank
 // conflicts), 376 us with 2 x 2 (z, t) planes for the tiles of the walk.

@@ -37,6 +37,7 @@ int hop_spb(int hx, int nrhs, int Ns, int prec) {
 // other, one right-hand side: N_s = 16, 4^4 46 / 65 (FP64) and 50 / 62 (FP32);
 // 8^4 (512 blocks) 68 / 85 and 63 / 73; 8^3 x 16 (1024) 100 / 90 and 65 / 75;
 // 16^2 x 8^2 (2048) 173 / 129 and 108 / 92; N_s = 8, 10^4 (625) 82 / 90 and 58 / 75.
+// N_s = 4, 8^2 x 16^2 (512) 77 / 111 and 67 / 81, 8 x 12 x 16^2 (768) 99 / 114 and 67 / 86.
 // Three right-hand sides: N_s = 8, 6x10x6x8 (720) 81 / 87 and 58 / 72; N_s = 16,
 // 8^3 x 4 (1024) 94 / 89 and 75 / 84.
 bool hop_small(const Geom& g, int nrhs, int Ns, int prec) {
